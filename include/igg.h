@@ -246,10 +246,13 @@ int diffusion_step_ranks(const igg_field *T2, const igg_field *T, const igg_fiel
  * the buffer holding T_nt (0: T, 1: T2).  T2 must hold T's halo planes in
  * non-periodic dimensions (Fig. 1 starts it as a copy of T).  rnd: the
  * stochastic-rounding counter advances by one per step.
- *   use_graph  0: every step is launched as diffusion_step would.  1: up to
- *          8 pairs of steps T -> T2 -> T are captured once into a HIP graph
- *          on a library stream and replayed on `stream`; the steps left over
- *          run directly.  The graph is kept for later calls with identical
+ * On one rank with overlaps of 2 in its periodic dimensions and the default
+ * schedule, steps between the first and the last run in pairs of one launch
+ * (the same bits, about half the memory traffic; FP16 below 2^21 points
+ * only); both buffers end up as single steps leave them.
+ *   use_graph  0: every step is launched directly.  1: up to 16 launches of
+ *          the loop are captured once into a HIP graph on a library stream
+ *          and replayed on `stream`; the steps left over run directly.  The graph is kept for later calls with identical
  *          arguments (and pair count) and rebuilt when any differs.  For
  *          grids small enough that launch latency dominates.  Stochastic
  *          rounding needs a new counter every step, so it refuses

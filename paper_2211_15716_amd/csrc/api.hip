@@ -433,10 +433,10 @@ static int fused_step(int r, const Split &slabs, const Box &inner, hipStream_t s
     return launch_step_inner(f.dtype, f.args[r], inner, s, &slabs, f.pk);
 }
 
-// diffusion_step for the grid's nranks ranks: fields[r] is rank r's block.
-static int step_ranks(const igg_field *T2, const igg_field *T, const igg_field *Ci, double lam, double dt,
-                      double dx, double dy, double dz, const int split[3], const igg_rounding *rnd,
-                      void *stream)
+// The argument checks of diffusion_step for the grid's nranks ranks (host
+// only).
+static int check_step(const igg_field *T2, const igg_field *T, const igg_field *Ci, double lam, double dt, double dx,
+                      double dy, double dz, const int split[3], const igg_rounding *rnd)
 {
     Grid &g = grid();
     int rc;
@@ -457,15 +457,25 @@ static int step_ranks(const igg_field *T2, const igg_field *T, const igg_field *
         }
     if ((rc = check_spacings(lam, dt, dx, dy, dz))) return rc;
     if ((rc = check_split(split, g.ol))) return rc;
-    int stochastic = 0;
-    uint32_t key = 0;
     if (rnd) {
         if (rnd->reserved != 0) return fail(IGG_ERR_ARG, "rounding.reserved must be 0");
         if (rnd->mode != IGG_ROUND_NEAREST && rnd->mode != IGG_ROUND_STOCHASTIC)
             return fail(IGG_ERR_ARG, "unknown rounding mode");
-        stochastic = rnd->mode == IGG_ROUND_STOCHASTIC;
-        key = sr_key(rnd->seed, rnd->counter);
     }
+    return IGG_OK;
+}
+
+// diffusion_step for the grid's nranks ranks: fields[r] is rank r's block.
+static int step_ranks(const igg_field *T2, const igg_field *T, const igg_field *Ci, double lam, double dt,
+                      double dx, double dy, double dz, const int split[3], const igg_rounding *rnd,
+                      void *stream)
+{
+    Grid &g = grid();
+    int rc;
+    const int P = g.nranks;
+    if ((rc = check_step(T2, T, Ci, lam, dt, dx, dy, dz, split, rnd))) return rc;
+    const int stochastic = rnd && rnd->mode == IGG_ROUND_STOCHASTIC;
+    const uint32_t key = rnd ? sr_key(rnd->seed, rnd->counter) : 0;
     std::vector<StepArgs> args(P);
     for (int r = 0; r < P; ++r)
         if ((rc = step_args(r, T2, T, Ci, lam, dt, dx, dy, dz, key, stochastic, args[r]))) return rc;
@@ -509,6 +519,36 @@ static int step_ranks(const igg_field *T2, const igg_field *T, const igg_field *
         split, dtype, [&](hipStream_t st) { return launch_halo(T2, 1, st, halo_dims); },
         [&](int r, const Split &b, hipStream_t st) { return launch_step_boundary(dtype, args[r], b, st); },
         [&](int r, const Box &b, hipStream_t st) { return launch_step_inner(dtype, args[r], b, st); }, s);
+}
+
+// Whether two steps may run as one launch (launch_step_pair): one rank, the
+// default schedule, overlaps of 2 in the periodic dimensions.  Timing counts
+// single steps, so it keeps them.
+static bool pair_ok(int dtype)
+{
+    const Grid &g = grid();
+    for (int d = 0; d < 3; ++d)
+        if (g.periods[d] && g.ol[d] != 2) return false;
+    return g.nranks == 1 && g.fuse_x && g.slab_pack == 2 && (g.schedule < 0 || g.schedule == 3) && !g.timing &&
+           g.delay_where == 0 && step_pair_pays(dtype, g.n);
+}
+
+// Two checked steps T -> T2 in one launch, the state between them stored in
+// mid when given.
+static int step_pair(const igg_field *T2, const igg_field *mid, const igg_field *T, const igg_field *Ci, double lam,
+                     double dt, double dx, double dy, double dz, const igg_rounding *rnd, hipStream_t s)
+{
+    int rc;
+    StepArgs a;
+    const int stochastic = rnd && rnd->mode == IGG_ROUND_STOCHASTIC;
+    if ((rc = step_args(0, T2, T, Ci, lam, dt, dx, dy, dz, 0, stochastic, a))) return rc;
+    if ((rc = ensure_device())) return rc;
+    const Grid &g = grid();
+    const StepPairArgs p{a.T2, mid ? mid->data : nullptr, a.T, a.Ci, a.nx, a.ny, a.nz,
+                         {g.periods[0], g.periods[1], g.periods[2]}, a.a, a.rx, a.ry, a.rz,
+                         rnd ? sr_key(rnd->seed, rnd->counter) : 0, rnd ? sr_key(rnd->seed, rnd->counter + 1) : 0,
+                         stochastic, a.so};
+    return launch_step_pair(T->dtype, p, s);
 }
 
 // update_halo over the grid's ranks: fields[r * nfields + f] is field f of
@@ -949,26 +989,50 @@ int diffusion_run(const igg_field *T, const igg_field *T2, const igg_field *Ci, 
     int rc;
     *final_buf = 0;
     const igg_field *buf[2] = {T, T2};
-    auto eager = [&](int it) {
-        igg_rounding r{};
-        const igg_rounding *rp = nullptr;
-        if (rnd) {
-            r = *rnd;
-            r.counter += (uint64_t)it;
-            rp = &r;
-        }
-        const int src = it & 1;
-        return step_ranks(buf[1 - src], buf[src], Ci, lam, dt, dx, dy, dz, split, rp, stream);
+    auto round_at = [&](int it, igg_rounding &r) -> const igg_rounding * {
+        if (!rnd) return nullptr;
+        r = *rnd;
+        r.counter += (uint64_t)it;
+        return &r;
     };
-    if (!use_graph || nt < 2) {
-        for (int it = 0; it < nt; ++it)
-            if ((rc = eager(it))) return rc;
+    // Launches: single steps, and pairs of steps in one launch where they
+    // apply.  Every launch swaps the buffers, so an even number of pairs
+    // leaves T_nt and T_{nt-1} where single steps would; the first step is a
+    // single one, which gives the state the halo the pairs rely on, and the
+    // last one too, which leaves T_{nt-1} in the other buffer.
+    const int npair = nt >= 6 && pair_ok(T->dtype) ? (nt - 2) / 4 * 2 : 0;
+    int cur = 0, it = 0;
+    auto single = [&](hipStream_t st) {
+        igg_rounding r;
+        const int e = step_ranks(buf[1 - cur], buf[cur], Ci, lam, dt, dx, dy, dz, split, round_at(it, r), st);
+        cur = 1 - cur;
+        it += 1;
+        return e;
+    };
+    auto pair = [&](hipStream_t st) {
+        igg_rounding r;
+        const int e = it == 1 ? check_step(buf[1 - cur], buf[cur], Ci, lam, dt, dx, dy, dz, split, rnd) : IGG_OK;
+        if (e) return e;
+        const int e2 = step_pair(buf[1 - cur], nullptr, buf[cur], Ci, lam, dt, dx, dy, dz, round_at(it, r), st);
+        cur = 1 - cur;
+        it += 2;
+        return e2;
+    };
+    // the graph holds up to 16 launches of the loop's repeating part (an even
+    // number, so that it ends in the buffer it began with): pairs, or single
+    // steps where pairs do not apply
+    const int body = npair ? npair : nt / 2 * 2, nrec = std::min(16, body);
+    if (!use_graph || nrec < 2) {
+        if (npair) {
+            if ((rc = single(s))) return rc;
+            for (int p = 0; p < npair; ++p)
+                if ((rc = pair(s))) return rc;
+        }
+        while (it < nt)
+            if ((rc = single(s))) return rc;
         *final_buf = nt & 1;
         return IGG_OK;
     }
-    // the graph holds `pairs` pairs of steps T -> T2 -> T with these exact
-    // arguments (up to 8: one graph launch then covers 16 steps)
-    const int pairs = std::min(8, nt / 2);
     std::vector<unsigned char> key;
     auto put = [&](const void *p, size_t n) {
         const unsigned char *c = (const unsigned char *)p;
@@ -980,7 +1044,9 @@ int diffusion_run(const igg_field *T, const igg_field *T2, const igg_field *Ci, 
     put(split ? split : nosplit, 3 * sizeof(int));
     const int mode = rnd ? rnd->mode : -1;
     put(&mode, sizeof mode);
-    put(&pairs, sizeof pairs);
+    put(&nrec, sizeof nrec);
+    put(&npair, sizeof npair);
+    if (npair && (rc = single(s))) return rc;
     if (!g.run_exec || key != g.run_key) {
         // a new argument set is captured: both steps run their argument
         // checks while being recorded, and a failed check ends the capture
@@ -994,12 +1060,12 @@ int diffusion_run(const igg_field *T, const igg_field *T2, const igg_field *Ci, 
         }
         const bool timing = g.timing;
         g.timing = false;
+        const int cur0 = cur, it0 = it;
         IGG_HIP(hipStreamBeginCapture(g.cap, hipStreamCaptureModeThreadLocal));
         int rc2 = IGG_OK;
-        for (int p = 0; p < pairs && !rc2; ++p) {
-            rc2 = step_ranks(T2, T, Ci, lam, dt, dx, dy, dz, split, rnd, g.cap);
-            if (!rc2) rc2 = step_ranks(T, T2, Ci, lam, dt, dx, dy, dz, split, rnd, g.cap);
-        }
+        for (int p = 0; p < nrec && !rc2; ++p) rc2 = npair ? pair(g.cap) : single(g.cap);
+        cur = cur0;
+        it = it0;
         hipGraph_t graph = nullptr;
         hipError_t e = hipStreamEndCapture(g.cap, &graph);
         g.timing = timing;
@@ -1015,10 +1081,15 @@ int diffusion_run(const igg_field *T, const igg_field *T2, const igg_field *Ci, 
         g.run_exec = exec;
         g.run_key = key;
     }
-    const int replays = nt / (2 * pairs);
-    for (int p = 0; p < replays; ++p) IGG_HIP(hipGraphLaunch(g.run_exec, s));
-    for (int it = replays * 2 * pairs; it < nt; ++it)
-        if ((rc = eager(it))) return rc;
+    const int replays = body / nrec;
+    for (int p = 0; p < replays; ++p) {
+        IGG_HIP(hipGraphLaunch(g.run_exec, s));
+        it += nrec * (npair ? 2 : 1);
+    }
+    for (int p = replays * nrec; p < npair; ++p)
+        if ((rc = pair(s))) return rc;
+    while (it < nt)
+        if ((rc = single(s))) return rc;
     *final_buf = nt & 1;
     return IGG_OK;
 }

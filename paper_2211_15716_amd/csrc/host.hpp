@@ -155,6 +155,27 @@ int launch_step_inner(int dtype, const StepArgs &a, const Box &b, hipStream_t s,
                       const SlabPack *pk = nullptr);
 int launch_step_boundary(int dtype, const StepArgs &a, const Split &sp, hipStream_t s);
 
+// Two steps in one launch, on one rank whose periodic dimensions overlap by
+// 2: T2 = T_{n+2} from T = T_n (valid halo), halo of T2 included; with mid,
+// T_{n+1} is stored too.  The planes of dimensions without a period keep
+// what T2 and mid hold (T_n's values, as in the time loop's buffers).
+struct StepPairArgs {
+    void *T2;
+    void *mid;  // or null
+    const void *T;
+    const void *Ci;
+    int nx, ny, nz;
+    int per[3];
+    double a, rx, ry, rz;  // as StepArgs
+    uint32_t key1, key2;   // FP16 stochastic-rounding keys of the two steps
+    int stochastic;
+    SrOrigin so;
+};
+int launch_step_pair(int dtype, const StepPairArgs &a, hipStream_t s);
+// Whether it is faster than two single steps on a grid of n points (and runs
+// there at all).
+bool step_pair_pays(int dtype, const int n[3]);
+
 // The y and z halo planes of one rank that is its own neighbour in every
 // dimension, packed by the boundary-slab kernel as it computes them.
 // send[d][s] holds the plane of dimension d+1 (y, then z) sent to the lower

@@ -1,0 +1,481 @@
+// pair.hip -- two steps of the time loop in one launch.
+//
+// T_{n+1} = u is computed from T_n tile by tile, kept on chip, and T_{n+2} is
+// computed from it: T_n and Ci are read and T_{n+2} is written once for two
+// steps instead of once for each.  Every point of u and of T_{n+2} goes
+// through igg::diffuse with the operands the one-step kernels give it, so the
+// bits are those of two single steps.  A work-group recomputes the u points
+// its tile shares with its neighbours (one layer on every side).
+//
+// One rank, overlaps of 2 in the periodic dimensions.  The halo of u is
+// formed as the halo update would: in a periodic dimension the point of plane
+// 0 is the point of plane n-2 and that of plane n-1 the point of plane 1; in
+// a dimension without a period it keeps T_n's value.  The halo of T_{n+2} is
+// stored with the points it copies.
+#include "host.hpp"
+
+namespace igg {
+
+namespace {
+
+template <typename C> struct PairCoef {
+    C a, rx, ry, rz;
+};
+
+struct PairGeom {
+    int n[3];
+    int per[3];
+};
+
+// The halo points whose image is (i, j, k) in periodic dimensions of overlap
+// 2, and the point itself: f(ii, jj, kk) for each.
+template <typename F>
+__device__ __forceinline__ void pair_images(const PairGeom &g, int i, int j, int k, F &&f)
+{
+    const int is[3] = {i, g.per[0] && i == 1 ? g.n[0] - 1 : -1, g.per[0] && i == g.n[0] - 2 ? 0 : -1};
+    const int js[3] = {j, g.per[1] && j == 1 ? g.n[1] - 1 : -1, g.per[1] && j == g.n[1] - 2 ? 0 : -1};
+    const int ks[3] = {k, g.per[2] && k == 1 ? g.n[2] - 1 : -1, g.per[2] && k == g.n[2] - 2 ? 0 : -1};
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+                if (is[a] >= 0 && js[b] >= 0 && ks[c] >= 0) f(is[a], js[b], ks[c]);
+}
+
+// The plane, row or column read for index c in -1..n (others: clamped): in a
+// periodic dimension the one the halo update copies it from.  Ci's own halo is
+// never read, nor are T's edges, where a plane of a dimension without a period
+// meets a halo plane (a step leaves them as they are).
+__device__ __forceinline__ int wrap(int c, int n, int per)
+{
+    if (per) c = c <= 0 ? c + n - 2 : (c >= n - 1 ? c - (n - 2) : c);
+    return c < 0 ? 0 : (c > n - 1 ? n - 1 : c);
+}
+
+// ------------------------------------------------------------ small grids
+// One block of BX x BY x BZ points of T_{n+2} per work-group: the u points of
+// the block and one layer around it go to LDS, each from global loads of its
+// seven T points (the grid sits in the caches), then the block is computed
+// from LDS.  Bound by the chain of its loads and the launch: 32^3 FP64 4 us for
+// two steps against 16 for two single steps of two launches each, 96 x 80 x 64
+// 9 against 27, 128^3 23 against 44.
+template <typename S, int BX, int BY, int BZ, int SR, int MID>
+__global__ void __launch_bounds__(256)
+k_step2_block(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T, const S *__restrict__ Ci, PairGeom g,
+              int nbx, int nby, PairCoef<compute_t<S>> cf, uint32_t key1, uint32_t key2, SrOrigin so)
+{
+    using C = compute_t<S>;
+    constexpr int UX = BX + 2, UY = BY + 2, UZ = BZ + 2, NU = UX * UY * UZ, NO = BX * BY * BZ;
+    __shared__ C u[UZ][UY][UX];
+    const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
+    const int x0 = 1 + (int)(b % nbx) * BX, y0 = 1 + (int)(b / nbx % nby) * BY, z0 = 1 + (int)(b / nbx / nby) * BZ;
+    const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    const int64_t sy = nx, sz = (int64_t)nx * ny;
+#pragma unroll
+    for (int t = 0; t < (NU + 255) / 256; ++t) {
+        const int q = t * 256 + threadIdx.x;
+        const int ux = q % UX, uy = q / UX % UY, uz = q / (UX * UY);
+        const int x = x0 - 1 + ux, y = y0 - 1 + uy, z = z0 - 1 + uz;
+        // edges and corners of the layer are nobody's neighbours
+        const int sides = (ux == 0 || ux == UX - 1) + (uy == 0 || uy == UY - 1) + (uz == 0 || uz == UZ - 1);
+        if (q >= NU || x >= nx || y >= ny || z >= nz || sides > 1) continue;
+        const bool hx = x == 0 || x == nx - 1, hy = y == 0 || y == ny - 1, hz = z == 0 || z == nz - 1;
+        C v;
+        if ((hx && !g.per[0]) || (hy && !g.per[1]) || (hz && !g.per[2])) {
+            v = widen<C>(T[x + sy * y + sz * z]);
+        } else {
+            const int xi = hx ? wrap(x, nx, 1) : x, yi = hy ? wrap(y, ny, 1) : y, zi = hz ? wrap(z, nz, 1) : z;
+            const int64_t p = xi + sy * yi + sz * zi;
+            const C o = diffuse<C>(widen<C>(T[p]), widen<C>(T[p - 1]), widen<C>(T[p + 1]), widen<C>(T[p - sy]),
+                                   widen<C>(T[p + sy]), widen<C>(T[p - sz]), widen<C>(T[p + sz]), widen<C>(Ci[p]),
+                                   cf.a, cf.rx, cf.ry, cf.rz);
+            uint32_t r = 0;
+            if (SR) r = sr_point_bits(sr_plane_key(key1, zi, so), xi, yi, so);
+            const S s = Store<S>::put(o, r, SR);
+            v = widen<C>(s);
+            if (MID && sides == 0 && !hx && !hy && !hz)
+                pair_images(g, x, y, z, [&](int i, int j, int k) { mid[i + sy * j + sz * k] = s; });
+        }
+        u[uz][uy][ux] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NO / 256; ++t) {
+        const int q = t * 256 + threadIdx.x;
+        const int ux = 1 + q % BX, uy = 1 + q / BX % BY, uz = 1 + q / (BX * BY);
+        const int x = x0 - 1 + ux, y = y0 - 1 + uy, z = z0 - 1 + uz;
+        if (x > nx - 2 || y > ny - 2 || z > nz - 2) continue;
+        const int64_t p = x + sy * y + sz * z;
+        const C o = diffuse<C>(u[uz][uy][ux], u[uz][uy][ux - 1], u[uz][uy][ux + 1], u[uz][uy - 1][ux],
+                               u[uz][uy + 1][ux], u[uz - 1][uy][ux], u[uz + 1][uy][ux], widen<C>(Ci[p]), cf.a, cf.rx,
+                               cf.ry, cf.rz);
+        uint32_t r = 0;
+        if (SR) r = sr_point_bits(sr_plane_key(key2, z, so), x, y, so);
+        const S s = Store<S>::put(o, r, SR);
+        pair_images(g, x, y, z, [&](int i, int j, int k) { out[i + sy * j + sz * k] = s; });
+    }
+}
+
+// ------------------------------------------------------------ large grids
+// z-march over tiles of TWV vectors (16 bytes) x TH rows.  The work-group's
+// threads cover the tile and what the two steps read around it: W = TWV + 2
+// vectors (one on each side) by H = TH + 4 rows, each thread RY rows of one
+// vector, rows of a tile following each other through the waves.  At plane k
+// a thread holds T of planes k-1, k, k+1 (k+2 in flight) and u of planes
+// k-2 and k-1 (the older of each in LDS), computes u of plane k from the T tile of plane k in LDS and
+// then T_{n+2} of plane k-1 from the u tile of plane k-1: one barrier for
+// two point evaluations.  Bound by HBM bytes and the rows re-read around the
+// tiles; a 1024-thread work-group per CU (128 registers, 127 KB of LDS) keeps
+// 64 KB of loads in flight.  Time per step in a time loop, against single
+// steps: 512^3 FP64 336 us against 531, FP32 170 against 285; 256^3 FP64 42
+// against 75, FP32 25 against 49; 301 x 257 x 203 FP32 30 against 53.
+struct PairTile {
+    PairGeom g;
+    int W, HG;       // vectors and row groups of the work-group
+    int ntx, nty;    // tiles
+    int zc;          // planes per work-group
+};
+
+template <typename S, int VEC, int RY, int CROSS, int MID>
+__global__ void __launch_bounds__(1024)
+k_step2_zmarch(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T, const S *__restrict__ Ci, PairTile z,
+               PairCoef<S> cf)
+{
+    typedef S V __attribute__((ext_vector_type(VEC)));
+    constexpr uint32_t E = sizeof(S);
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    const PairGeom &g = z.g;
+    const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    const int64_t sxy = (int64_t)nx * ny;
+    const int W = z.W, H = z.HG * RY;
+    // one vector before and after the tiles: the x neighbours beyond a
+    // tile's first and last vector are read and not used
+    V *lds = reinterpret_cast<V *>(lds_raw) + 1;
+    const int plane = W * H;  // vectors of one tile
+
+    const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
+    const int bx = (int)(b % z.ntx), by = (int)(b / z.ntx % z.nty), bz = (int)(b / z.ntx / z.nty);
+    const int tid = threadIdx.x / W;
+    const bool live = tid < z.HG;
+    const int tg = live ? tid : z.HG - 1, tv = threadIdx.x - tid * W;
+    const int i = (bx * (W - 2) + tv - 1) * VEC;
+    const int jb = 1 + by * (H - 4);
+    const int kb = 1 + bz * z.zc;
+    const int ke = kb + z.zc < nz - 1 ? kb + z.zc : nz - 1;
+
+    // where a vector is read: at its own place, a period away when it lies
+    // wholly outside the row, point by point when it crosses the row's end.
+    // Element hq, where it is the row's halo point, is read from the point it
+    // copies: of Ci always, of T where the row may be a fixed one.
+    int iv = i;
+    if (i < 0) iv = g.per[0] ? i + nx - 2 : 0;
+    if (i >= nx) iv = g.per[0] ? i - (nx - 2) : 0;
+    const bool cross = i < nx && i + VEC > nx;
+    int hq = -1, hx = 0;
+    if (g.per[0] && i == 0) { hq = 0; hx = nx - 2; }
+    if (g.per[0] && i < nx && i + VEC >= nx) { hq = nx - 1 - i; hx = 1; }
+    const bool edges = g.per[0] && !(g.per[1] && g.per[2]);
+
+    uint32_t off[RY];  // byte offsets of the rows in a plane
+    int jr[RY];
+    uint32_t fixed = 0;       // points of u that keep T's value
+    uint32_t st = 0;          // rows whose results this thread stores
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+        const int lr = tg * RY + r;
+        const int j = jb - 2 + lr;
+        jr[r] = j;
+        off[r] = (uint32_t)(wrap(j, ny, g.per[1]) * nx) * E;
+        if (live && lr >= 2 && lr < H - 2 && j <= ny - 2 && tv >= 1 && tv < W - 1) st |= 1u << r;
+#pragma unroll
+        for (int q = 0; q < VEC; ++q)
+            if ((!g.per[0] && (i + q <= 0 || i + q >= nx - 1)) || (!g.per[1] && (j <= 0 || j >= ny - 1)))
+                fixed |= 1u << (r * VEC + q);
+    }
+    const uint32_t vo = (uint32_t)iv * E;
+    const bool full = i >= 1 && i + VEC <= nx - 1;
+    const bool xedge = g.per[0] && (i <= 1 || i + VEC >= nx - 1);
+
+    const int64_t pb = sxy * (int64_t)E;
+    auto rs = [&](const S *A, int k) { return buf_rsrc(A + (int64_t)k * sxy, pb); };
+    auto ldv = [&](__amdgpu_buffer_rsrc_t d, uint32_t row) -> V {
+        V v;
+        if (!CROSS || !cross) {
+            v = buf_load<V, 0>(d, row + vo);
+        } else {
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) v[q] = buf_load<S, 0>(d, row + (uint32_t)wrap(i + q, nx, g.per[0]) * E);
+        }
+        return v;
+    };
+    auto ld1 = [&](__amdgpu_buffer_rsrc_t d, uint32_t row) -> S {
+        S x = S(0);
+        if (hq >= 0) x = buf_load<S, 0>(d, row + (uint32_t)hx * E);
+        return x;
+    };
+    auto patch = [&](V v, S x) -> V {
+#pragma unroll
+        for (int q = 0; q < VEC; ++q)
+            if (q == hq) v[q] = x;
+        return v;
+    };
+    // one row of a result: the tile's points, and the halo points they fill
+    auto put_row = [&](S *A, int kk, int jj, const V &v) {
+        __amdgpu_buffer_rsrc_t d = rs(A, kk);
+        const uint32_t row = (uint32_t)(jj * nx) * E;
+        if (full) {
+            buf_store<V, 2>(v, d, row + (uint32_t)i * E);
+        } else {
+#pragma unroll
+            for (int q = 0; q < VEC; ++q)
+                if (i + q >= 1 && i + q <= nx - 2) buf_store<S, 0>(v[q], d, row + (uint32_t)(i + q) * E);
+        }
+        if (xedge) {
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) {
+                if (i + q == 1) buf_store<S, 0>(v[q], d, row + (uint32_t)(nx - 1) * E);
+                if (i + q == nx - 2) buf_store<S, 0>(v[q], d, row);
+            }
+        }
+    };
+    auto put = [&](S *A, int k, const V (&v)[RY]) {
+        const bool zimg = g.per[2] && (k == 1 || k == nz - 2);
+#pragma unroll
+        for (int r = 0; r < RY; ++r) {
+            if (!(st >> r & 1)) continue;
+            const int j = jr[r];
+            put_row(A, k, j, v[r]);
+            if (zimg || (g.per[1] && (j == 1 || j == ny - 2))) {
+#pragma unroll 1
+                for (int m = 1; m < 9; ++m) {
+                    const int a = m % 3, c = m / 3;
+                    const int jj = a == 0 ? j : (!g.per[1] ? -1 : a == 1 ? (j == 1 ? ny - 1 : -1) : (j == ny - 2 ? 0 : -1));
+                    const int kk = c == 0 ? k : (!g.per[2] ? -1 : c == 1 ? (k == 1 ? nz - 1 : -1) : (k == nz - 2 ? 0 : -1));
+                    if (kk >= 0 && jj >= 0) put_row(A, kk, jj, v[r]);
+                }
+            }
+        }
+    };
+
+    const int lbase = tg * RY * W + tv;
+    const int up = tg > 0 ? lbase - W : lbase, dn = tg < z.HG - 1 ? lbase + RY * W : lbase + (RY - 1) * W;
+    // (threads past the last row group read what the last ones do and store
+    // nothing)
+    auto dsc = [&](const S *A, int k) { return rs(A, wrap(k, nz, g.per[2])); };
+    auto ldT = [&](int k, int r) -> V {
+        const __amdgpu_buffer_rsrc_t d = dsc(T, k);
+        const V v = ldv(d, off[r]);
+        return edges ? patch(v, ld1(d, off[r])) : v;
+    };
+    V tc[RY], tp[RY], cc[RY], cp[RY], uc[RY];
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+        const V t = ldT(kb - 2, r);
+        if (live) lds[2 * plane + lbase + r * W] = t;
+        tc[r] = ldT(kb - 1, r);
+        tp[r] = ldT(kb, r);
+        const __amdgpu_buffer_rsrc_t d = dsc(Ci, kb - 1);
+        cc[r] = patch(ldv(d, off[r]), ld1(d, off[r]));
+        cp[r] = uc[r] = V{};
+    }
+    for (int k = kb - 1; k <= ke; ++k) {
+        const int buf = (k - kb + 1) & 1;
+        V *sT = lds + buf * 2 * plane, *sU = sT + plane;
+        V tn[RY], cn[RY];
+        S t1[RY], c1[RY];
+        // (the last plane's loads are read again and not used)
+        const __amdgpu_buffer_rsrc_t dT = dsc(T, k < ke ? k + 2 : k), dC = dsc(Ci, k < ke ? k + 1 : k);
+#pragma unroll
+        for (int r = 0; r < RY; ++r) {
+            tn[r] = ldv(dT, off[r]);
+            cn[r] = ldv(dC, off[r]);
+            c1[r] = ld1(dC, off[r]);
+            t1[r] = edges ? ld1(dT, off[r]) : S(0);
+        }
+        if (live) {
+#pragma unroll
+            for (int r = 0; r < RY; ++r) {
+                sT[lbase + r * W] = tc[r];
+                sU[lbase + r * W] = uc[r];
+            }
+        }
+        __syncthreads();
+        // T of plane k-1 and u of plane k-2: this thread's own, in the other
+        // tiles until the next plane is written there
+        const V *oT = lds + (buf ^ 1) * 2 * plane + lbase, *oU = oT + plane;
+        // one plane of either step from its LDS tile and the planes around it
+        auto plane_of = [&](const V *s, const V *om, const V (&c)[RY], const V (&p)[RY], const V (&ci)[RY],
+                            V (&o)[RY]) {
+            const S *e = reinterpret_cast<const S *>(s);
+            const V vu = s[up], vd = s[dn];
+#pragma unroll
+            for (int r = 0; r < RY; ++r) {
+                const int l0 = (lbase + r * W) * VEC;
+                const S xl = e[l0 - 1], xr = e[l0 + VEC];
+                const V m = om[r * W];
+                const V ym = r == 0 ? vu : c[r > 0 ? r - 1 : 0], yp = r == RY - 1 ? vd : c[r < RY - 1 ? r + 1 : r];
+#pragma unroll
+                for (int q = 0; q < VEC; ++q)
+                    o[r][q] = diffuse<S>(c[r][q], q == 0 ? xl : c[r][q > 0 ? q - 1 : 0],
+                                         q == VEC - 1 ? xr : c[r][q < VEC - 1 ? q + 1 : q], ym[q], yp[q], m[q],
+                                         p[r][q], ci[r][q], cf.a, cf.rx, cf.ry, cf.rz);
+            }
+        };
+        V un[RY], o[RY];
+        plane_of(sT, oT, tc, tp, cc, un);
+        const uint32_t fx = !g.per[2] && (k <= 0 || k >= nz - 1) ? ~0u : fixed;
+        if (fx) {
+#pragma unroll
+            for (int r = 0; r < RY; ++r)
+#pragma unroll
+                for (int q = 0; q < VEC; ++q)
+                    if (fx >> (r * VEC + q) & 1) un[r][q] = tc[r][q];
+        }
+        plane_of(sU, oU, uc, un, cp, o);
+        // the loads are waited for here, before the stores: a wait after them
+        // would wait for the stores too
+#pragma unroll
+        for (int r = 0; r < RY; ++r) {
+            __asm__ volatile("" : "+v"(tn[r]));
+            __asm__ volatile("" : "+v"(cn[r]));
+            __asm__ volatile("" : "+v"(c1[r]));
+            if (edges) __asm__ volatile("" : "+v"(t1[r]));
+        }
+        if (MID && k >= kb && k < ke) put(mid, k, un);
+        if (k > kb) put(out, k - 1, o);
+#pragma unroll
+        for (int r = 0; r < RY; ++r) {
+            tc[r] = tp[r];
+            tp[r] = edges ? patch(tn[r], t1[r]) : tn[r];
+            cp[r] = cc[r];
+            cc[r] = patch(cn[r], c1[r]);
+            uc[r] = un[r];
+        }
+    }
+}
+
+template <typename S, int BX, int BY, int BZ>
+int run_block(const StepPairArgs &a, hipStream_t s)
+{
+    using C = compute_t<S>;
+    const PairGeom g{{a.nx, a.ny, a.nz}, {a.per[0], a.per[1], a.per[2]}};
+    const int nbx = (a.nx - 2 + BX - 1) / BX, nby = (a.ny - 2 + BY - 1) / BY, nbz = (a.nz - 2 + BZ - 1) / BZ;
+    const PairCoef<C> cf{(C)a.a, (C)a.rx, (C)a.ry, (C)a.rz};
+    const dim3 grd((unsigned)((int64_t)nbx * nby * nbz));
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grd, dim3(256), 0, s, (S *)a.T2, (S *)a.mid, (const S *)a.T, (const S *)a.Ci, g, nbx,
+                           nby, cf, a.key1, a.key2, a.so);
+    };
+    if constexpr (sizeof(S) == 2) {
+        if (a.stochastic) {
+            if (a.mid) go(k_step2_block<S, BX, BY, BZ, 1, 1>);
+            else go(k_step2_block<S, BX, BY, BZ, 1, 0>);
+            IGG_HIP(hipGetLastError());
+            return IGG_OK;
+        }
+    }
+    if (a.mid) go(k_step2_block<S, BX, BY, BZ, 0, 1>);
+    else go(k_step2_block<S, BX, BY, BZ, 0, 0>);
+    IGG_HIP(hipGetLastError());
+    return IGG_OK;
+}
+
+template <typename S, int VEC, int RY>
+int run_zmarch2(const StepPairArgs &a, hipStream_t s)
+{
+    PairTile z{};
+    z.g = PairGeom{{a.nx, a.ny, a.nz}, {a.per[0], a.per[1], a.per[2]}};
+    // Tiles at most 64 vectors wide (of even widths), 800 to 1024 threads (one
+    // work-group per CU: two of half the size read more rows around their
+    // tiles and were never faster), and the number of rows and planes for
+    // which the launch ends soonest: rounds of 256 work-groups, each of zc
+    // planes and about two more to fill the pipeline, a plane costing a fixed
+    // time and one proportional to its points.  Over 7 grids from 150 x 200 x
+    // 320 to 512^3 the choice is within 5% of the fastest of 340 shapes
+    // (256^3 FP64: 82.6 us for 240 work-groups of 22 planes, 89 for 256 of 32
+    // with lower tiles, 110 for 320 of 16).
+    const int nv = (a.nx - 2) / VEC + 1;  // vectors up to that of the last inner point
+    z.ntx = (nv + 63) / 64;
+    z.W = (nv + z.ntx - 1) / z.ntx + 2;
+    double best = 0;
+    for (int hg = 1024 / z.W; hg >= 1 && hg * RY >= 6 && (hg + 1) * z.W > 800; --hg) {
+        const int th = hg * RY - 4;
+        const int64_t cols = (int64_t)z.ntx * ((a.ny - 2 + th - 1) / th);
+        for (int zc = 6; zc <= 64; ++zc) {
+            const int64_t wg = cols * ((a.nz - 2 + zc - 1) / zc);
+            const double cost = (double)((wg + 255) / 256) * (zc + 2) * (211 + th * (z.W - 2));
+            if (best == 0 || cost < best) {
+                best = cost;
+                z.HG = hg;
+                z.zc = zc;
+            }
+        }
+    }
+    const int TH = z.HG * RY - 4;
+    z.nty = (a.ny - 2 + TH - 1) / TH;
+    const int64_t blocks = (int64_t)z.ntx * z.nty * ((a.nz - 2 + z.zc - 1) / z.zc);
+    const size_t lds = ((size_t)4 * z.W * z.HG * RY + 2) * VEC * sizeof(S);
+    const int tpb = (z.W * z.HG + 63) / 64 * 64;
+    const PairCoef<S> cf{(S)a.a, (S)a.rx, (S)a.ry, (S)a.rz};
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(tpb), lds, s, (S *)a.T2, (S *)a.mid, (const S *)a.T,
+                           (const S *)a.Ci, z, cf);
+    };
+    if (a.nx % VEC == 0) {
+        if (a.mid) go(k_step2_zmarch<S, VEC, RY, 0, 1>);
+        else go(k_step2_zmarch<S, VEC, RY, 0, 0>);
+    } else {
+        if (a.mid) go(k_step2_zmarch<S, VEC, RY, 1, 1>);
+        else go(k_step2_zmarch<S, VEC, RY, 1, 0>);
+    }
+    IGG_HIP(hipGetLastError());
+    return IGG_OK;
+}
+
+}  // namespace
+
+// Whether a pair is launched for this grid, and by which kernel.  Regions of
+// zmarch_min_points() points (2^21) and more march (128^3 FP64, 2.0e6 points:
+// 22.6 us a launch either way; 96 x 80 x 64: 9 us by blocks, 23 marching).
+// FP16 marches in single steps: its step is bound by issue, which pairs do
+// not lessen.
+static bool pair_marches(int dtype, const int n[3])
+{
+    const int64_t pts = (int64_t)(n[0] - 2) * (n[1] - 2) * (n[2] - 2);
+    return dtype != IGG_F16 && pts >= zmarch_min_points();
+}
+
+bool step_pair_pays(int dtype, const int n[3])
+{
+    const int64_t pts = (int64_t)(n[0] - 2) * (n[1] - 2) * (n[2] - 2);
+    if (pts < zmarch_min_points()) return true;
+    // the z-march kernel reads a whole vector a period away at either end of
+    // a row, and addresses a plane with 32-bit offsets
+    return dtype != IGG_F16 && n[0] >= 16 && (int64_t)n[0] * n[1] * elem_bytes(dtype) < ((int64_t)1 << 31);
+}
+
+// Blocks of 16 x 4 x 4 points below 2^20 points, for more work-groups (32^3
+// FP64: 4 us a launch against 9 with 16 x 8 x 8; 300 x 70 x 50: 14.4 against
+// 16), 16 x 8 x 8 above, which recompute less of u (128^3: 22.9 against 25.4).
+template <typename S>
+static int pair_blocks(const StepPairArgs &a, hipStream_t s)
+{
+    const int64_t pts = (int64_t)(a.nx - 2) * (a.ny - 2) * (a.nz - 2);
+    return pts < ((int64_t)1 << 20) ? run_block<S, 16, 4, 4>(a, s) : run_block<S, 16, 8, 8>(a, s);
+}
+
+int launch_step_pair(int dtype, const StepPairArgs &a, hipStream_t s)
+{
+    const int n[3] = {a.nx, a.ny, a.nz};
+    if (!pair_marches(dtype, n)) {
+        if (dtype == IGG_F64) return pair_blocks<double>(a, s);
+        if (dtype == IGG_F32) return pair_blocks<float>(a, s);
+        return pair_blocks<_Float16>(a, s);
+    }
+    if (dtype == IGG_F64) return run_zmarch2<double, 2, 2>(a, s);
+    return run_zmarch2<float, 4, 2>(a, s);
+}
+
+}  // namespace igg

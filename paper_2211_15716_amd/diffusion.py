@@ -41,14 +41,12 @@ def forward(T, Ci, nt, lam, dt, dx, dy, dz, split=(16, 2, 2), work=None, sr_seed
     # non-periodic dimensions are never written by the step, so both buffers
     # must carry them from the start
     T2 = T.clone() if work is None else work
-    a, b = T, T2
-    for it in range(nt):
-        rnd = None
-        if T.dtype == torch.float16 and sr_seed is not None:
-            rnd = igg.rounding("stochastic", sr_seed, counter0 + it)
-        igg.diffusion_step(b, a, Ci, lam, dt, dx, dy, dz, split=split, rnd=rnd, stream=stream)
-        a, b = b, a
-    return a
+    if nt < 1:
+        return T
+    rnd = None
+    if T.dtype == torch.float16 and sr_seed is not None:
+        rnd = igg.rounding("stochastic", sr_seed, counter0)
+    return igg.diffusion_run(T, T2, Ci, lam, dt, dx, dy, dz, nt, split=split, rnd=rnd, graph=False, stream=stream)
 
 
 def forward_with(prob, T, Ci, nt, stream=None):
