@@ -27,21 +27,34 @@ struct PairGeom {
     int per[3];
 };
 
-// The halo points whose image is (i, j, k) in periodic dimensions of overlap
-// 2, and the point itself: f(ii, jj, kk) for each.
-template <typename F>
-__device__ __forceinline__ void pair_images(const PairGeom &g, int i, int j, int k, F &&f)
+// Stores v at (i, j, k) and at the halo points whose image it is in periodic
+// dimensions of overlap 2.
+template <typename S>
+__device__ __forceinline__ void pair_store(const PairGeom &g, int i, int j, int k, S *A, S v)
 {
-    const int is[3] = {i, g.per[0] && i == 1 ? g.n[0] - 1 : -1, g.per[0] && i == g.n[0] - 2 ? 0 : -1};
-    const int js[3] = {j, g.per[1] && j == 1 ? g.n[1] - 1 : -1, g.per[1] && j == g.n[1] - 2 ? 0 : -1};
-    const int ks[3] = {k, g.per[2] && k == 1 ? g.n[2] - 1 : -1, g.per[2] && k == g.n[2] - 2 ? 0 : -1};
+    const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    const int64_t sy = nx, sz = (int64_t)nx * ny;
+    S *P = A + (i + sy * j + sz * k);
+    *P = v;
+    const bool xe = g.per[0] && (i == 1 || i == nx - 2), ye = g.per[1] && (j == 1 || j == ny - 2);
+    const bool ze = g.per[2] && (k == 1 || k == nz - 2);
+    if (!xe && !ye && !ze) return;
+    // the distance to the image in each dimension, twice where both halo
+    // planes copy the point (n = 3)
+    const int64_t dx[3] = {0, xe && i == 1 ? nx - 2 : 0, xe && i == nx - 2 ? -(nx - 2) : 0};
+    const int64_t dy[3] = {0, ye && j == 1 ? sy * (ny - 2) : 0, ye && j == ny - 2 ? -sy * (ny - 2) : 0};
+    const int64_t dz[3] = {0, ze && k == 1 ? sz * (nz - 2) : 0, ze && k == nz - 2 ? -sz * (nz - 2) : 0};
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
+    for (int c = 0; c < 3; ++c) {
+        if (c && !dz[c]) continue;
 #pragma unroll
-        for (int b = 0; b < 3; ++b)
+        for (int b = 0; b < 3; ++b) {
+            if (b && !dy[b]) continue;
 #pragma unroll
             for (int a = 0; a < 3; ++a)
-                if (is[a] >= 0 && js[b] >= 0 && ks[c] >= 0) f(is[a], js[b], ks[c]);
+                if (!a ? (b || c) : dx[a] != 0) P[dx[a] + dy[b] + dz[c]] = v;
+        }
+    }
 }
 
 // The plane, row or column read for index c in -1..n (others: clamped): in a
@@ -58,9 +71,12 @@ __device__ __forceinline__ int wrap(int c, int n, int per)
 // One block of BX x BY x BZ points of T_{n+2} per work-group: the u points of
 // the block and one layer around it go to LDS, each from global loads of its
 // seven T points (the grid sits in the caches), then the block is computed
-// from LDS.  Bound by the chain of its loads and the launch: 32^3 FP64 4 us for
-// two steps against 16 for two single steps of two launches each, 96 x 80 x 64
-// 9 against 27, 128^3 23 against 44.
+// from LDS.  Bound by its instructions, the chain of its loads and the launch:
+// 32^3 FP64 3.4 us for two steps against 16 for two single steps of two
+// launches each, 96 x 80 x 64 9.2 against 27, 128^3 22 against 44.  Slower: a
+// T tile in LDS too (its own index arithmetic; 17 and 61 us at the last two
+// sizes with a rolled image loop), and the loads of three points at a time
+// issued together (56 registers instead of 30; 10.0 and 24.6).
 template <typename S, int BX, int BY, int BZ, int SR, int MID>
 __global__ void __launch_bounds__(256)
 k_step2_block(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T, const S *__restrict__ Ci, PairGeom g,
@@ -96,7 +112,7 @@ k_step2_block(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T,
             const S s = Store<S>::put(o, r, SR);
             v = widen<C>(s);
             if (MID && sides == 0 && !hx && !hy && !hz)
-                pair_images(g, x, y, z, [&](int i, int j, int k) { mid[i + sy * j + sz * k] = s; });
+                pair_store(g, x, y, z, mid, s);
         }
         u[uz][uy][ux] = v;
     }
@@ -113,8 +129,7 @@ k_step2_block(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T,
                                cf.ry, cf.rz);
         uint32_t r = 0;
         if (SR) r = sr_point_bits(sr_plane_key(key2, z, so), x, y, so);
-        const S s = Store<S>::put(o, r, SR);
-        pair_images(g, x, y, z, [&](int i, int j, int k) { out[i + sy * j + sz * k] = s; });
+        pair_store(g, x, y, z, out, Store<S>::put(o, r, SR));
     }
 }
 
@@ -450,7 +465,7 @@ static bool pair_marches(int dtype, const int n[3])
 bool step_pair_pays(int dtype, const int n[3])
 {
     const int64_t pts = (int64_t)(n[0] - 2) * (n[1] - 2) * (n[2] - 2);
-    if (pts < zmarch_min_points()) return true;
+    if (pts < zmarch_min_points()) return (int64_t)n[0] * n[1] * n[2] * elem_bytes(dtype) < ((int64_t)1 << 31);
     // the z-march kernel reads a whole vector a period away at either end of
     // a row, and addresses a plane with 32-bit offsets
     return dtype != IGG_F16 && n[0] >= 16 && (int64_t)n[0] * n[1] * elem_bytes(dtype) < ((int64_t)1 << 31);
@@ -458,7 +473,8 @@ bool step_pair_pays(int dtype, const int n[3])
 
 // Blocks of 16 x 4 x 4 points below 2^20 points, for more work-groups (32^3
 // FP64: 4 us a launch against 9 with 16 x 8 x 8; 300 x 70 x 50: 14.4 against
-// 16), 16 x 8 x 8 above, which recompute less of u (128^3: 22.9 against 25.4).
+// 16), 16 x 8 x 8 above, which recompute less of u (128^3: 22.9 against 25.4;
+// the four before the stores tested for halo images once).
 template <typename S>
 static int pair_blocks(const StepPairArgs &a, hipStream_t s)
 {
