@@ -264,6 +264,24 @@ int diffusion_run(const igg_field *T, const igg_field *T2, const igg_field *Ci, 
                   double dx, double dy, double dz, const int split[3], const igg_rounding *rnd, int nt,
                   int use_graph, int *final_buf, void *stream);
 
+/* Steps of the time loop that one launch can take on this grid for fields of
+ * element type dtype: 2 where diffusion_step_pair applies and pays (one rank,
+ * overlaps of 2 in the periodic dimensions, the default schedule, no kernel
+ * timing; FP16 on grids below 2^21 points only), else 1.  0 without a grid or
+ * for an unknown dtype. */
+int igg_steps_per_launch(int dtype);
+
+/* Two steps of Fig. 1's time loop in one launch: T2 = T_{n+2} from T = T_n,
+ * and mid = T_{n+1} too where mid is not null, each with the bits and the
+ * halo planes two calls of diffusion_step give them (rnd: counter and
+ * counter + 1).  T's halo planes must hold the points they copy (any step's
+ * result does); the planes of dimensions without a period are read from T,
+ * and T2 and mid must hold the same.
+ * Errors: as diffusion_step; IGG_ERR_STATE where igg_steps_per_launch is 1. */
+int diffusion_step_pair(const igg_field *T2, const igg_field *mid, const igg_field *T, const igg_field *Ci,
+                        double lam, double dt, double dx, double dy, double dz, const int split[3],
+                        const igg_rounding *rnd, void *stream);
+
 /* Stable time step of Fig. 1: dt = min(dx^2,dy^2,dz^2)/lam/maximum(Ci)/6.1,
  * the maximum taken in FP64 over every point of Ci on the GPU.
  * Synchronises `stream`.  Errors: as igg_reduce, IGG_ERR_ARG for lam <= 0. */

@@ -1094,6 +1094,30 @@ int diffusion_run(const igg_field *T, const igg_field *T2, const igg_field *Ci, 
     return IGG_OK;
 }
 
+int igg_steps_per_launch(int dtype)
+{
+    if (!grid().init || dtype < IGG_F64 || dtype > IGG_F16) return 0;
+    return pair_ok(dtype) ? 2 : 1;
+}
+
+int diffusion_step_pair(const igg_field *T2, const igg_field *mid, const igg_field *T, const igg_field *Ci, double lam,
+                        double dt, double dx, double dy, double dz, const int split[3], const igg_rounding *rnd,
+                        void *stream)
+{
+    Grid &g = grid();
+    if (!g.init) return fail(IGG_ERR_STATE, "the global grid is not initialised");
+    if (g.nranks > 1) return fail(IGG_ERR_STATE, "the grid holds several virtual ranks: use diffusion_step_ranks");
+    if (!T2 || !T || !Ci) return fail(IGG_ERR_ARG, "null field");
+    int rc;
+    if ((rc = check_step(T2, T, Ci, lam, dt, dx, dy, dz, split, rnd))) return rc;
+    if (mid) {
+        if ((rc = check_step(mid, T, Ci, lam, dt, dx, dy, dz, split, rnd))) return rc;
+        if (overlaps_mem(*T2, *mid)) return fail(IGG_ERR_ALIAS, "T2 shares memory with mid");
+    }
+    if (!pair_ok(T->dtype)) return fail(IGG_ERR_STATE, "two steps in one launch do not apply on this grid");
+    return step_pair(T2, mid, T, Ci, lam, dt, dx, dy, dz, rnd, (hipStream_t)stream);
+}
+
 int diffusion_dt(const igg_field *Ci, double lam, double dx, double dy, double dz, double *dt,
                  void *stream)
 {

@@ -71,6 +71,11 @@ class Problem:
         igg.diffusion_step(out, T, Ci, self.lam, self.dt, self.dx, self.dy, self.dz, split=self.split,
                            stream=stream)
 
+    def step_pair(self, out, mid, T, Ci, stream=None):
+        """Two steps in one launch, the state between them in mid unless None."""
+        igg.diffusion_step_pair(out, mid, T, Ci, self.lam, self.dt, self.dx, self.dy, self.dz, split=self.split,
+                                stream=stream)
+
     def adjoint(self, lam_n, lam_np1, Tn, Ci, gCi, stream=None):
         igg.diffusion_step_adjoint(lam_n, lam_np1, Tn, Ci, gCi, self.lam, self.dt, self.dx, self.dy, self.dz,
                                    split=self.split, stream=stream)
@@ -209,6 +214,27 @@ def _fuse_stores(ops):
     return out
 
 
+def _pairs(prob, T0):
+    """Whether the sweep may take two of prob's steps in one launch: prob's
+    step is Problem's own, on one block of a grid where the library does."""
+    return (isinstance(T0, torch.Tensor) and isinstance(prob, Problem) and type(prob).step is Problem.step
+            and "step" not in vars(prob) and igg.steps_per_launch(T0) == 2)
+
+
+def _pair_stores(ops):
+    """Merge ("advance_store", a, b) followed by ("advance_store", b, b+1)
+    into ("advance_store2", a, b+1), whose last two steps are one launch that
+    writes both snapshots (not from state 0, see Sweep)."""
+    out = []
+    for op in ops:
+        if (op[0] == "advance_store" and out and out[-1][0] == "advance_store" and out[-1][2] == op[1]
+                and op[2] == op[1] + 1 and op[1] > 1):
+            out[-1] = ("advance_store2", out[-1][1], op[2])
+        else:
+            out.append(op)
+    return out
+
+
 class Sweep:
     """Runs a checkpointing schedule (paper_2211_15716_amd.checkpoint) on the
     GPU.  Snapshots are device tensors (lists of per-rank blocks with a
@@ -217,7 +243,10 @@ class Sweep:
     that is stored right after it is computed is computed into its snapshot
     buffer directly, which is a freed snapshot's buffer when one is free (its
     halo planes in non-periodic dimensions hold T0's, which no step writes).
-    Counts forward and adjoint steps."""
+    Where the library takes two steps in one launch, states that nobody needs
+    are skipped and neighbouring snapshots are written by one launch; the
+    step from T0 is a single one, which gives every later state the halo such
+    launches rely on.  Counts forward and adjoint steps."""
 
     def __init__(self, prob, Ci, T0, ops):
         self.p, self.Ci, self.ops = prob, Ci, ops
@@ -228,16 +257,40 @@ class Sweep:
         self.advances = 0
         self.adjoints = 0
         self.peak = 1
-        self.fwd, self.rev = _split_ops(_fuse_stores(ops))
+        self.pairs = _pairs(prob, T0)
+        ops = _fuse_stores(ops)
+        self.fwd, self.rev = [_pair_stores(p) if self.pairs else p for p in _split_ops(ops)]
 
-    def _advance(self, a, b):
+    def _advance(self, a, b, fresh=False):
+        """From state a to state b; with fresh, b is written to a new
+        snapshot buffer instead of a work buffer."""
         assert self.cur_n == a, (a, self.cur_n)
-        for _ in range(a, b):
-            dst = self.work[0] if self.cur is not self.work[0] else self.work[1]
-            self.p.step(dst, self.cur, self.Ci)
+        while a < b:
+            two = self.pairs and a > 0 and b - a >= 2
+            last = a + 1 + two == b
+            if fresh and last:
+                dst = self._snapshot()
+            else:
+                dst = self.work[0] if self.cur is not self.work[0] else self.work[1]
+            if two:
+                self.p.step_pair(dst, None, self.cur, self.Ci)
+            else:
+                self.p.step(dst, self.cur, self.Ci)
             self.cur = dst
-            self.advances += 1
+            self.advances += 1 + two
+            a += 1 + two
         self.cur_n = b
+
+    def _snapshot(self):
+        """A buffer for a new snapshot: a freed one's, or a new one."""
+        for q, buf in enumerate(self.pool):
+            if buf is not self.cur:
+                return self.pool.pop(q)
+        return _fresh_like(self.cur)
+
+    def _keep(self, n, buf):
+        self.store[n] = buf
+        self.peak = max(self.peak, len(self.store))
 
     def _do(self, op):
         kind = op[0]
@@ -246,20 +299,17 @@ class Sweep:
         elif kind == "advance":
             self._advance(op[1], op[2])
         elif kind == "advance_store":
+            self._advance(op[1], op[2], fresh=True)
+            self._keep(op[2], self.cur)
+        elif kind == "advance_store2":
             a, b = op[1], op[2]
-            self._advance(a, b - 1)
-            dst = None
-            for q, buf in enumerate(self.pool):
-                if buf is not self.cur:
-                    dst = self.pool.pop(q)
-                    break
-            if dst is None:
-                dst = _fresh_like(self.cur)
-            self.p.step(dst, self.cur, self.Ci)
-            self.advances += 1
+            self._advance(a, b - 2)
+            mid, dst = self._snapshot(), self._snapshot()
+            self.p.step_pair(dst, mid, self.cur, self.Ci)
+            self.advances += 2
+            self._keep(b - 1, mid)
+            self._keep(b, dst)
             self.cur, self.cur_n = dst, b
-            self.store[b] = dst
-            self.peak = max(self.peak, len(self.store))
         elif kind == "store":
             assert self.cur_n == op[1]
             self.store[op[1]] = _clone(self.cur)

@@ -36,7 +36,7 @@ EXPORTS = ["igg_init_global_grid", "igg_global_size", "igg_topology", "igg_updat
            "igg_timing_enable", "igg_timing_read", "igg_last_error", "igg_version",
            "igg_nranks", "igg_rank_coords", "igg_neighbors", "igg_update_halo_ranks", "diffusion_step_ranks",
            "diffusion_step_adjoint_ranks", "diffusion_flux_step_ranks", "diffusion_flux_step_adjoint_ranks",
-           "diffusion_run", "igg_stream_probe", "igg_reduce_noalloc", "igg_adjoint_seed"]
+           "diffusion_run", "igg_steps_per_launch", "diffusion_step_pair", "igg_stream_probe", "igg_reduce_noalloc", "igg_adjoint_seed"]
 
 
 class IggError(RuntimeError):
@@ -85,6 +85,8 @@ def load():
     lib.diffusion_step_ranks.argtypes = [_PF] * 3 + [d] * 5 + [_PI, ctypes.POINTER(Rounding), vp]
     lib.diffusion_run.argtypes = [_PF] * 3 + [d] * 5 + [_PI, ctypes.POINTER(Rounding), ctypes.c_int, ctypes.c_int,
                                                         _PI, vp]
+    lib.igg_steps_per_launch.argtypes = [ctypes.c_int]
+    lib.diffusion_step_pair.argtypes = [_PF] * 4 + [d] * 5 + [_PI, ctypes.POINTER(Rounding), vp]
     lib.diffusion_dt.argtypes = [_PF, d, d, d, d, ctypes.POINTER(d), vp]
     lib.diffusion_step_adjoint.argtypes = [_PF] * 5 + [d] * 5 + [_PI, vp]
     lib.diffusion_step_adjoint_ranks.argtypes = [_PF] * 5 + [d] * 5 + [_PI, vp]
@@ -277,6 +279,21 @@ def diffusion_run(T, T2, Ci, lam, dt, dx, dy, dz, nt, split=(16, 2, 2), rnd=None
                                 float(dy), float(dz), _int3(split), r, int(nt), 1 if graph else 0, ctypes.byref(fb),
                                 _stream(stream)))
     return T2 if fb.value else T
+
+
+def steps_per_launch(T):
+    """Steps of the time loop one launch can take on fields like T (1 or 2)."""
+    return load().igg_steps_per_launch(_dtype_code(T))
+
+
+def diffusion_step_pair(T2, mid, T, Ci, lam, dt, dx, dy, dz, split=(16, 2, 2), rnd=None, stream=None):
+    """Two steps in one launch: T2 from T, the state between them in mid
+    (None: not kept); needs steps_per_launch(T) == 2."""
+    f2, fm, f, fc = field(T2), field(mid) if mid is not None else None, field(T), field(Ci)
+    r = ctypes.byref(rnd) if rnd is not None else None
+    _check(load().diffusion_step_pair(ctypes.byref(f2), ctypes.byref(fm) if fm is not None else None, ctypes.byref(f),
+                                      ctypes.byref(fc), float(lam), float(dt), float(dx), float(dy), float(dz),
+                                      _int3(split), r, _stream(stream)))
 
 
 def diffusion_dt(Ci, lam, dx, dy, dz, stream=None):
