@@ -208,16 +208,19 @@ int igg_finalize_global_grid(void);
  *               the helper (the paper's arrangement);
  *            0  slabs first on `stream`, the update on the helper stream;
  *            2  slabs, update and inner region as one chain on `stream`;
- *            3  on one rank that is periodic in every dimension: slabs and
- *               inner region in one launch on `stream`, whose first
- *               work-groups compute the slabs and store the y and z halo
- *               planes of T2 as they go (with IGG_SLAB_PACK=1 they fill send
- *               buffers that one copy then unpacks).
- *          Default: 3 where it applies (measured fastest at 512^3, below the
- *          unsplit step); otherwise 1 for inner regions of 2^21 points and
- *          more in FP64/FP32, 2 for smaller ones and for FP16.
- *          NULL = no overlap: the whole step, then the halo update, on
- *          `stream`.
+ *            3  on one rank: slabs and inner region in one launch on
+ *               `stream`, whose first work-groups compute the slabs and
+ *               store the y and z halo planes of T2 as they go (with
+ *               IGG_SLAB_PACK=1 and every dimension periodic they fill send
+ *               buffers that one copy then unpacks).  Fields of at most 96
+ *               MiB in three arrays take one launch of a kernel that needs
+ *               no slabs.
+ *          Default: 3 where it applies; otherwise 1 for inner regions of
+ *          2^21 points and more in FP64/FP32, 2 for smaller ones and for
+ *          FP16.
+ *          NULL = no overlap asked for: on one rank the same launch with
+ *          slabs of the least width, otherwise (and with a schedule set) the
+ *          whole step, then the halo update, on `stream`.
  *   rnd    FP16 store rounding, NULL = round to nearest even (ignored for
  *          FP64/FP32).
  * Arithmetic: FP64 for IGG_F64; FP32 for IGG_F32 and IGG_F16 with dt*lam and

@@ -389,6 +389,18 @@ static bool self_halo_ok()
     return g.nranks == 1 && g.fuse_x && g.slab_pack == 2 && g.periods[0] && g.periods[1] && g.periods[2];
 }
 
+// Whether a step of `points` points takes the small-grid kernel: three arrays
+// of at most 96 MiB (160^3 FP64, 98 MB: 28.5 us with either kernel on inputs
+// that were not in the caches, 20.7 against 29.2 in a time loop; 155 x 333 x
+// 90 FP64, 111 MB: 33.5 against 30.8 and 24.3 against 32.7; 256^3 FP32, 201
+// MB: 61 against 41 and 38.8 against 46.7), or the points that
+// IGG_ZMARCH_MIN_POINTS asks for.
+static bool step_is_small(int dtype, int64_t points)
+{
+    const int64_t zm = zmarch_min_points();
+    return zm == kZmarchMinPoints ? points * 3 * elem_bytes(dtype) <= ((int64_t)96 << 20) : points < zm;
+}
+
 // The step's launch arguments for rank r: its arrays, the fused x exchange
 // into its x neighbours' arrays, and its origin in the global index space.
 static int step_args(int r, const igg_field *T2, const igg_field *T, const igg_field *Ci, double lam,
@@ -488,6 +500,40 @@ static int step_ranks(const igg_field *T2, const igg_field *T, const igg_field *
     const int halo_dims = g.fuse_x ? 6 : 7;
     const int dtype = T[0].dtype;
     hipStream_t s = (hipStream_t)stream;
+    // One rank, x exchange in the stores, no schedule asked for: one launch.
+    // Small grids take a kernel of their own; on larger ones the slab waves
+    // store the y and z halo planes as they compute the points those planes
+    // copy (an unsplit step takes slabs of the least width).  Where only some
+    // dimensions have a period, the edges follow.  Against slabs, halo update
+    // and inner region in launches of their own: 256^3 FP64 without periods
+    // 83.5 -> 74.7 us, with two 84.6 -> 76.3, unsplit 80.0 -> 73.5.
+    if (P == 1 && g.fuse_x && g.slab_pack == 2 && (g.schedule < 0 || g.schedule == 3)) {
+        const Box all{1, g.n[0] - 1, 1, g.n[1] - 1, 1, g.n[2] - 1};
+        const int *widths = split ? split : g.ol;
+        Split sp;
+        plan_split(g.n, widths, sp);
+        sp.inner.i0 = all.i0;
+        sp.inner.i1 = all.i1;
+        if (step_is_small(dtype, box_points(sp.inner))) {
+            if ((rc = timing_mark(s, 0))) return rc;
+            if ((rc = launch_step_small(dtype, args[0], s))) return rc;
+            if ((rc = timing_mark(s, 0))) return rc;
+            if (g.timing) { g.t_launches++; g.t_points += box_points(all); }
+            return test_delay(3, s);
+        }
+        SlabPack pk{};
+        for (int d = 0; d < 3; ++d) {
+            pk.ol[d] = g.ol[d];
+            pk.per[d] = g.periods[d];
+        }
+        pk.direct = 1;
+        FusedStep ctx{dtype, args.data(), &pk};
+        return run_split(
+            widths, dtype, [&](hipStream_t st) { return launch_step_edges(dtype, args[0], st); },
+            [&](int r, const Split &b, hipStream_t st) { return launch_step_slabs(dtype, args[r], b, &pk, st); },
+            [&](int r, const Box &b, hipStream_t st) { return launch_step_inner(dtype, args[r], b, st); }, s, true,
+            fused_step, &ctx);
+    }
     if (!split) {
         Box all{1, g.n[0] - 1, 1, g.n[1] - 1, 1, g.n[2] - 1};
         for (int r = 0; r < P; ++r) {
@@ -505,7 +551,10 @@ static int step_ranks(const igg_field *T2, const igg_field *T, const igg_field *
         SlabPack pk{};
         for (int d = 0; d < 2; ++d)
             for (int side = 0; side < 2; ++side) pk.send[d][side] = halo_send_plane(0, d, side);
-        for (int d = 0; d < 3; ++d) pk.ol[d] = g.ol[d];
+        for (int d = 0; d < 3; ++d) {
+            pk.ol[d] = g.ol[d];
+            pk.per[d] = 1;
+        }
         pk.direct = g.slab_pack == 2;
         FusedStep ctx{dtype, args.data(), &pk};
         return run_split(

@@ -155,6 +155,14 @@ int launch_step_inner(int dtype, const StepArgs &a, const Box &b, hipStream_t s,
                       const SlabPack *pk = nullptr);
 int launch_step_boundary(int dtype, const StepArgs &a, const Split &sp, hipStream_t s);
 
+// The step on one rank in one launch, halo update of T2 included, for grids
+// too small for z-march tiles.
+int launch_step_small(int dtype, const StepArgs &a, hipStream_t s);
+// The points of T2's y and z halo planes in the planes of dimensions without
+// a period, which the halo update copies but no step computes (nothing to do
+// unless some dimensions have a period and others none).
+int launch_step_edges(int dtype, const StepArgs &a, hipStream_t s);
+
 // Two steps in one launch, on one rank whose periodic dimensions overlap by
 // 2: T2 = T_{n+2} from T = T_n (valid halo), halo of T2 included; with mid,
 // T_{n+1} is stored too.  The planes of dimensions without a period keep
@@ -177,7 +185,7 @@ int launch_step_pair(int dtype, const StepPairArgs &a, hipStream_t s);
 bool step_pair_pays(int dtype, const int n[3]);
 
 // The y and z halo planes of one rank that is its own neighbour in every
-// dimension, packed by the boundary-slab kernel as it computes them.
+// periodic dimension, packed by the boundary-slab kernel as it computes them.
 // send[d][s] holds the plane of dimension d+1 (y, then z) sent to the lower
 // (s = 0: plane ol-1) or the upper (s = 1: plane n-ol) neighbour, x
 // fastest: nx*nz elements (y) or nx*ny (z).  Every entry, the plane's own
@@ -186,6 +194,7 @@ bool step_pair_pays(int dtype, const int n[3]);
 struct SlabPack {
     void *send[2][2];
     int ol[3];
+    int per[3];  // 0: no planes of this dimension, no images in it
     int direct;  // 1: store straight into the halo planes of T2 (no send buffers, no unpack)
 };
 // The y and z slabs of sp (kind 1) with one wavefront per row run, marching

@@ -32,6 +32,17 @@ template <typename S> struct VecOf<S, 1> {
     typedef S type;
 };
 
+// The same in memory: rows of any length start at any element, so vectors
+// are read and written at element alignment (the same instructions; a vector
+// that runs over its row's end reads the start of the next row, which is not
+// used).
+template <typename S, int VEC> struct MemVecOf {
+    typedef S type __attribute__((ext_vector_type(VEC), aligned(sizeof(S))));
+};
+template <typename S> struct MemVecOf<S, 1> {
+    typedef S type;
+};
+
 template <typename S, int VEC>
 __device__ __forceinline__ S lane_elem(const typename VecOf<S, VEC>::type &v, int q)
 {
@@ -135,9 +146,9 @@ template <typename S, int VEC>
 __device__ __forceinline__ void slab_put_row(S *row, int i, bool xin, bool full, int i0, int i1,
                                              const typename VecOf<S, VEC>::type &out)
 {
-    using V = typename VecOf<S, VEC>::type;
+    using M = typename MemVecOf<S, VEC>::type;
     if (full) {
-        *reinterpret_cast<V *>(row + i) = out;
+        *reinterpret_cast<M *>(row + i) = out;
     } else if (xin) {
 #pragma unroll
         for (int q = 0; q < VEC; ++q)
@@ -156,6 +167,7 @@ __device__ __forceinline__ void slab_body(S *__restrict__ T2, const S *__restric
     constexpr int stochastic = SR;
     using C = compute_t<S>;
     using V = typename VecOf<S, VEC>::type;
+    using M = typename MemVecOf<S, VEC>::type;
     constexpr int RUN = 64 * VEC;
     if (w >= ss.waves) return;
     int q = 0;
@@ -187,13 +199,13 @@ __device__ __forceinline__ void slab_body(S *__restrict__ T2, const S *__restric
 
     auto ld = [&](int64_t off) -> V {
         V v{};
-        if (xin) v = *reinterpret_cast<const V *>(T + off + i);
+        if (xin) v = *reinterpret_cast<const M *>(T + off + i);
         return v;
     };
     // Ci is read once per step: non-temporal
     auto ld_ci = [&](int64_t off) -> V {
         V v{};
-        if (xin) v = __builtin_nontemporal_load(reinterpret_cast<const V *>(Ci + off + i));
+        if (xin) v = __builtin_nontemporal_load(reinterpret_cast<const M *>(Ci + off + i));
         return v;
     };
     // the x neighbour beyond the run's end: lane 0 holds x0-1, lane 63 x0+RUN
@@ -250,7 +262,7 @@ __device__ __forceinline__ void slab_body(S *__restrict__ T2, const S *__restric
         }
         S *dst = T2 + p;
         if (full) {
-            __builtin_nontemporal_store(out, reinterpret_cast<V *>(dst + i));
+            __builtin_nontemporal_store(out, reinterpret_cast<M *>(dst + i));
         } else if (xin) {
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
@@ -350,6 +362,7 @@ k_step_zmarch(S *__restrict__ T2, const S *__restrict__ T, const S *__restrict__
     constexpr int stochastic = SR;
     using C = compute_t<S>;
     using V = typename VecOf<S, VEC>::type;
+    using M = typename MemVecOf<S, VEC>::type;
     // Interior columns of the LDS tile from P0, halo columns at P0-1 and
     // P0+TW.  Where a vector is 16 bytes of C (FP64, and FP16 widened to
     // FP32) the interior starts 16-byte aligned, so each vector is one LDS
@@ -414,6 +427,10 @@ k_step_zmarch(S *__restrict__ T2, const S *__restrict__ T, const S *__restrict__
         col[r] = (int64_t)jc * nx + i;
         crow[r] = jr[r] < bb.j1;
     }
+    // The plane above the box's last one is read for the rows computed only;
+    // other rows read the row before theirs there, so that a vector running
+    // over its row's end stays inside the array in the last plane too.
+    auto above = [&](int k, int r) { return col[r] - (k >= bb.k1 && !crow[r] ? nx : 0); };
     // y-halo row of this thread row (thread rows 0 and TY-1 only)
     const bool hy = ty == 0 || ty == TY - 1;
     const int jh = (ty == 0) ? jb - 1 : (jb + TH > ny - 1 ? ny - 1 : jb + TH);
@@ -428,14 +445,14 @@ k_step_zmarch(S *__restrict__ T2, const S *__restrict__ T, const S *__restrict__
 
     auto ldv = [&](const S *A, int k, int64_t c) -> V {
         V v{};
-        if (xin) v = *reinterpret_cast<const V *>(A + (int64_t)k * sxy + c);
+        if (xin) v = *reinterpret_cast<const M *>(A + (int64_t)k * sxy + c);
         return v;
     };
     // Ci and T2 are touched once per step: non-temporal loads and stores keep
     // them from displacing the T lines that neighbouring tiles reuse
     auto ldv_nt = [&](const S *A, int k, int64_t c) -> V {
         V v{};
-        if (xin) v = __builtin_nontemporal_load(reinterpret_cast<const V *>(A + (int64_t)k * sxy + c));
+        if (xin) v = __builtin_nontemporal_load(reinterpret_cast<const M *>(A + (int64_t)k * sxy + c));
         return v;
     };
 
@@ -446,7 +463,7 @@ k_step_zmarch(S *__restrict__ T2, const S *__restrict__ T, const S *__restrict__
     for (int r = 0; r < RY; ++r) {
         tm[r] = ldv(T, kb - 1, col[r]);
         tc[r] = ldv(T, kb, col[r]);
-        tp[r] = ldv(T, kb + 1, col[r]);
+        tp[r] = ldv(T, kb + 1, above(kb + 1, r));
         ci[r] = crow[r] ? ldv_nt(Ci, kb, col[r]) : V{};
         hx[r] = own_h ? T[(int64_t)kb * sxy + col[r] - i + xh] : S(0);
     }
@@ -516,7 +533,7 @@ k_step_zmarch(S *__restrict__ T2, const S *__restrict__ T, const S *__restrict__
             if (!crow[r]) continue;
             S *dst = T2 + (int64_t)k * sxy + col[r];
             if (xin && i >= bb.i0 && i + VEC <= bb.i1) {
-                __builtin_nontemporal_store(out[r], reinterpret_cast<V *>(dst));
+                __builtin_nontemporal_store(out[r], reinterpret_cast<M *>(dst));
             } else if (xin) {
 #pragma unroll
                 for (int q = 0; q < VEC; ++q)
@@ -544,7 +561,7 @@ k_step_zmarch(S *__restrict__ T2, const S *__restrict__ T, const S *__restrict__
         S hn[RY];
 #pragma unroll
         for (int r = 0; r < RY; ++r) {
-            tn[r] = more ? ldv(T, k + 2, col[r]) : V{};
+            tn[r] = more ? ldv(T, k + 2, above(k + 2, r)) : V{};
             cn[r] = (more && crow[r]) ? ldv_nt(Ci, k + 1, col[r]) : V{};
             hn[r] = (more && own_h) ? T[(int64_t)(k + 1) * sxy + col[r] - i + xh] : S(0);
         }
@@ -621,7 +638,7 @@ k_step_zmarch(S *__restrict__ T2, const S *__restrict__ T, const S *__restrict__
                         if (i + q >= c0 && i + q < c1) dst[q] = lane_elem<S, VEC>(out, q);
                 }
             } else if (xin && i >= bb.i0 && i + VEC <= bb.i1) {
-                __builtin_nontemporal_store(out, reinterpret_cast<V *>(dst));
+                __builtin_nontemporal_store(out, reinterpret_cast<M *>(dst));
             } else if (xin) {
 #pragma unroll
                 for (int q = 0; q < VEC; ++q)
@@ -706,6 +723,9 @@ static const ZLaunch kInner = {8, "IGG_ZCHUNK", 2, "IGG_XCD_REMAP", 4096};
 // FP32 inner region: 16 planes, contiguous ranges of tile rows per XCD
 // (at 512^3 the 32-row tiles take 8: 2048 work-groups)
 static const ZLaunch kInnerRanges = {16, "IGG_ZCHUNK", 3, "IGG_XCD_REMAP", 2048};
+// FP32 in tiles of half the width: chunks halved below 8192 work-groups (4
+// planes: 320^3 80.5 us, 8 planes 85.4; 384^3 130.2 and 135.9)
+static const ZLaunch kNarrowF32 = {16, "IGG_ZCHUNK", 3, "IGG_XCD_REMAP", 8192};
 // FP16 inner region: the same with chunks halved below 8192 work-groups (8
 // planes at 512^3: 1.5% faster than 16 in a ping-pong time loop)
 static const ZLaunch kInnerF16 = {16, "IGG_ZCHUNK", 3, "IGG_XCD_REMAP", 8192};
@@ -773,12 +793,14 @@ static SlabSet make_slabset(const StepArgs &a, const Box *b, int nb, const SlabP
                     ss.bstride[d] = nx;
                 }
                 const int dim = d + 1;
-                ss.src[d][side] = side == 0 ? pk->ol[dim] - 1 : (dim == 1 ? a.ny : a.nz) - pk->ol[dim];
+                ss.src[d][side] = !pk->per[dim] ? -1
+                                  : side == 0   ? pk->ol[dim] - 1
+                                                : (dim == 1 ? a.ny : a.nz) - pk->ol[dim];
             }
         const int n3[3] = {a.nx, a.ny, a.nz};
         for (int d = 0; d < 3; ++d) {
-            ss.img[d][0] = pk->ol[d] - 1;
-            ss.img[d][1] = n3[d] - pk->ol[d];
+            ss.img[d][0] = pk->per[d] ? pk->ol[d] - 1 : -1;
+            ss.img[d][1] = pk->per[d] ? n3[d] - pk->ol[d] : -1;
         }
     }
     return ss;
@@ -881,6 +903,16 @@ static int run_zmarch(const StepArgs &a, const Box *b, int nbox, hipStream_t s, 
 
 static bool aligned(const void *p, int bytes) { return ((uintptr_t)p % (uintptr_t)bytes) == 0; }
 
+// Rows of any length and alignment are read in vectors, which may run over
+// into the next row but not beyond it.  Against one point per lane: 511^3
+// FP64 672 -> 567 us, FP32 373 -> 303, FP16 with stochastic rounding 322 ->
+// 193; 401 x 300 x 250 161 -> 150, 92 -> 85, 102 -> 64.
+template <typename S, int VEC>
+static bool row_ok(const StepArgs &a)
+{
+    return a.nx >= VEC;
+}
+
 template <typename S, int VEC>
 static bool vec_ok(const StepArgs &a)
 {
@@ -897,8 +929,8 @@ static bool vec_ok(const StepArgs &a)
 // and 512^3; 16-byte loads over 512-point rows, or four rows per thread,
 // 6-19% slower at 512^3: more registers, fewer waves).
 // These shapes and work-group mappings measured fastest on MI355X at 512^3.
-// Rows whose length does not allow vector loads take one point per lane;
-// regions below zmarch_min_points() take the box kernel.
+// Rows shorter than a vector take one point per lane; regions below
+// zmarch_min_points() take the box kernel.
 // One inner-region launch, with the slab waves of yz (nyz boxes) run by
 // the launch's first work-groups when nyz > 0.
 template <typename S, int VEC, int BX, int TY, int RY>
@@ -914,6 +946,21 @@ static int run_inner(const StepArgs &a, const Box &b, hipStream_t s, const ZLaun
     const int mc = sizeof(S) == 8 ? (box_count(b) >= ((int64_t)1 << 26) ? 8 : 2) : sizeof(S) == 4 ? 2 : 4;
     const SlabSet ss = make_slabset<S, VEC>(a, yz, nyz, pk, mc);
     return run_zmarch<S, VEC, BX, TY, RY>(a, &b, 1, s, L, nullptr, &ss);
+}
+
+// Whether tiles of half the width (32 lanes a row) leave so many fewer lanes
+// past the rows' ends that they pay: at least a fifth of the lanes (FP64 and
+// FP32; FP16 a sixth, being bound by issue).  FP32 301 x 257 x 203 53 -> 44
+// us, 320^3 96 -> 80, 384^3 147 -> 130, 520 x 300 x 300 (a sixth) 122 -> 123;
+// FP16 with stochastic rounding 46 -> 36, 81 -> 58, 114 -> 79, 93 -> 84; FP64
+// 192 x 300 x 300 87 -> 77.  Where both widths fit alike the wide ones read
+// fewer bytes around their tiles (511^3 FP32 303 against 354).
+template <typename S, int VEC>
+static bool narrow_pays(const Box &b)
+{
+    const int64_t n = b.i1 - b.i0 / VEC * VEC, wide = 64 * VEC, half = 32 * VEC;
+    const int64_t lw = (n + wide - 1) / wide * wide, lh = (n + half - 1) / half * half;
+    return sizeof(S) == 2 ? lh * 6 <= lw * 5 : lh * 5 <= lw * 4;
 }
 
 int launch_step_inner(int dtype, const StepArgs &a, const Box &b, hipStream_t s, const Split *slabs,
@@ -932,7 +979,8 @@ int launch_step_inner(int dtype, const StepArgs &a, const Box &b, hipStream_t s,
         return box_count(b) > 0 ? launch_step_boxes(dtype, a, &b, 1, s) : IGG_OK;
     }
     if (dtype == IGG_F64) {
-        if (vec_ok<double, 2>(a)) {
+        if (row_ok<double, 2>(a)) {
+            if (narrow_pays<double, 2>(b)) return run_inner<double, 2, 32, 8, 2>(a, b, s, kInner, yz, nyz, pk);
             // a 128 x 16 tile over 512 threads of 2 rows (108 registers, 4
             // waves per SIMD): 2-3% faster at 256^3 and 384^3 than 4 rows per
             // thread, 5% slower at 512^3, so regions below 2^26 points take it
@@ -947,7 +995,8 @@ int launch_step_inner(int dtype, const StepArgs &a, const Box &b, hipStream_t s,
         return run_inner<double, 1, 64, 8, 2>(a, b, s, kInner, yz, nyz, pk);
     }
     if (dtype == IGG_F32) {
-        if (vec_ok<float, 4>(a)) {
+        if (row_ok<float, 4>(a)) {
+            if (narrow_pays<float, 4>(b)) return run_inner<float, 4, 32, 8, 2>(a, b, s, kNarrowF32, yz, nyz, pk);
             // 256 x 32 tiles over 1024 threads of 2 rows for regions of at
             // least 2^26 points (4% faster than 256 x 16 tiles at 512^3)
             if (box_count(b) >= ((int64_t)1 << 26))
@@ -956,7 +1005,9 @@ int launch_step_inner(int dtype, const StepArgs &a, const Box &b, hipStream_t s,
         }
         return run_inner<float, 1, 64, 8, 2>(a, b, s, kInner, yz, nyz, pk);
     }
-    if (vec_ok<_Float16, 4>(a)) return run_inner<_Float16, 4, 64, 4, 2>(a, b, s, kInnerF16, yz, nyz, pk);
+    if (row_ok<_Float16, 4>(a) && narrow_pays<_Float16, 4>(b))
+        return run_inner<_Float16, 4, 32, 8, 2>(a, b, s, kInnerF16, yz, nyz, pk);
+    if (row_ok<_Float16, 4>(a)) return run_inner<_Float16, 4, 64, 4, 2>(a, b, s, kInnerF16, yz, nyz, pk);
     return run_inner<_Float16, 1, 64, 8, 2>(a, b, s, kInnerF16, yz, nyz, pk);
 }
 
@@ -1040,14 +1091,14 @@ int launch_step_slabs(int dtype, const StepArgs &a, const Split &sp, const SlabP
     if (n == 0) return IGG_OK;
     if (n > 4) return fail(IGG_ERR_ARG, "internal: more than four y/z slabs");
     if (dtype == IGG_F64) {
-        if (vec_ok<double, 2>(a)) return run_slabs<double, 2>(a, yz, n, pk, s);
+        if (row_ok<double, 2>(a)) return run_slabs<double, 2>(a, yz, n, pk, s);
         return run_slabs<double, 1>(a, yz, n, pk, s);
     }
     if (dtype == IGG_F32) {
-        if (vec_ok<float, 4>(a)) return run_slabs<float, 4>(a, yz, n, pk, s);
+        if (row_ok<float, 4>(a)) return run_slabs<float, 4>(a, yz, n, pk, s);
         return run_slabs<float, 1>(a, yz, n, pk, s);
     }
-    if (vec_ok<_Float16, 8>(a)) return run_slabs<_Float16, 8>(a, yz, n, pk, s);
+    if (row_ok<_Float16, 8>(a)) return run_slabs<_Float16, 8>(a, yz, n, pk, s);
     return run_slabs<_Float16, 1>(a, yz, n, pk, s);
 }
 
