@@ -137,20 +137,23 @@ k_step2_block(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T,
 // z-march over tiles of TWV vectors (16 bytes) x TH rows.  The work-group's
 // threads cover the tile and what the two steps read around it: W = TWV + 2
 // vectors (one on each side) by H = TH + 4 rows, each thread RY rows of one
-// vector, rows of a tile following each other through the waves.  At plane k
+// vector: first the tile's columns, rows following each other through the
+// waves, then the vectors beside it.  At plane k
 // a thread holds T of planes k-1, k, k+1 (k+2 in flight) and u of planes
 // k-2 and k-1 (the older of each in LDS), computes u of plane k from the T tile of plane k in LDS and
 // then T_{n+2} of plane k-1 from the u tile of plane k-1: one barrier for
 // two point evaluations.  Bound by HBM bytes and the rows re-read around the
 // tiles; a 1024-thread work-group per CU (128 registers, 127 KB of LDS) keeps
 // 64 KB of loads in flight.  Time per step in a time loop, against single
-// steps: 512^3 FP64 336 us against 531, FP32 170 against 285; 256^3 FP64 42
-// against 75, FP32 25 against 49; 301 x 257 x 203 FP32 30 against 53.
+// steps: 512^3 FP64 319 us against 527, FP32 172 against 285; 256^3 FP64 44
+// against 73, FP32 23 against 47; 301 x 257 x 203 FP32 25 against 48.
 struct PairTile {
     PairGeom g;
     int W, HG;       // vectors and row groups of the work-group
     int ntx, nty;    // tiles
     int zc;          // planes per work-group
+    int nt;          // 1: non-temporal stores
+    int deal;        // 1: tile rows dealt to the XCDs in turn, 0: in ranges
 };
 
 template <typename S, int VEC, int RY, int CROSS, int MID>
@@ -170,11 +173,21 @@ k_step2_zmarch(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T
     V *lds = reinterpret_cast<V *>(lds_raw) + 1;
     const int plane = W * H;  // vectors of one tile
 
-    const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
+    uint32_t b = blockIdx.x;
+    if (!z.deal) {
+        b = (uint32_t)xcd_remap(b, gridDim.x);
+    } else {
+        const uint32_t ntx = (uint32_t)z.ntx, P8 = gridDim.x / ntx / 8 * 8;
+        if (b < ntx * P8) {
+            const uint32_t x = b % 8, slot = b / 8;
+            b = slot % ntx + ntx * (x + 8 * (slot / ntx));
+        }
+    }
     const int bx = (int)(b % z.ntx), by = (int)(b / z.ntx % z.nty), bz = (int)(b / z.ntx / z.nty);
-    const int tid = threadIdx.x / W;
-    const bool live = tid < z.HG;
-    const int tg = live ? tid : z.HG - 1, tv = threadIdx.x - tid * W;
+    const int t = threadIdx.x, th = t - z.HG * (W - 2);  // th >= 0: a vector beside the tile
+    const bool live = th < 2 * z.HG;
+    const int tg = min(th < 0 ? t / (W - 2) : th >> 1, z.HG - 1);
+    const int tv = th < 0 ? 1 + t % (W - 2) : (th & 1 ? W - 1 : 0);
     const int i = (bx * (W - 2) + tv - 1) * VEC;
     const int jb = 1 + by * (H - 4);
     const int kb = 1 + bz * z.zc;
@@ -241,7 +254,8 @@ k_step2_zmarch(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T
         __amdgpu_buffer_rsrc_t d = rs(A, kk);
         const uint32_t row = (uint32_t)(jj * nx) * E;
         if (full) {
-            buf_store<V, 2>(v, d, row + (uint32_t)i * E);
+            if (z.nt) buf_store<V, 2>(v, d, row + (uint32_t)i * E);
+            else buf_store<V, 0>(v, d, row + (uint32_t)i * E);
         } else {
 #pragma unroll
             for (int q = 0; q < VEC; ++q)
@@ -402,35 +416,48 @@ int run_zmarch2(const StepPairArgs &a, hipStream_t s)
 {
     PairTile z{};
     z.g = PairGeom{{a.nx, a.ny, a.nz}, {a.per[0], a.per[1], a.per[2]}};
-    // Tiles at most 64 vectors wide (of even widths), 800 to 1024 threads (one
-    // work-group per CU: two of half the size read more rows around their
-    // tiles and were never faster), and the number of rows and planes for
-    // which the launch ends soonest: rounds of 256 work-groups, each of zc
-    // planes and about two more to fill the pipeline, a plane costing a fixed
-    // time and one proportional to its points.  Over 7 grids from 150 x 200 x
-    // 320 to 512^3 the choice is within 5% of the fastest of 340 shapes
-    // (256^3 FP64: 82.6 us for 240 work-groups of 22 planes, 89 for 256 of 32
-    // with lower tiles, 110 for 320 of 16).
+    // The tile and the planes per work-group for which the launch ends
+    // soonest: rounds of 256 work-groups (one of 700 to 1024 threads per CU;
+    // two of half the size read more rows around their tiles), each of zc
+    // planes and about one more to fill the pipeline, a plane costing a fixed
+    // time, one for its points and a little for its width.  Tiles start at
+    // whole 128-byte lines of a row (512^3 FP64: 650 us a launch against 661
+    // with the vectors beside the tile in the same waves as the tile's).
+    // Over 13 grids from 160^3 to 512^3 the choice is 4% slower than the
+    // fastest of about 200 shapes on average and 11% at worst; a launch of
+    // just over 256 work-groups instead costs up to twice the time.
     const int nv = (a.nx - 2) / VEC + 1;  // vectors up to that of the last inner point
-    z.ntx = (nv + 63) / 64;
-    z.W = (nv + z.ntx - 1) / z.ntx + 2;
     double best = 0;
-    for (int hg = 1024 / z.W; hg >= 1 && hg * RY >= 6 && (hg + 1) * z.W > 800; --hg) {
-        const int th = hg * RY - 4;
-        const int64_t cols = (int64_t)z.ntx * ((a.ny - 2 + th - 1) / th);
-        for (int zc = 6; zc <= 64; ++zc) {
-            const int64_t wg = cols * ((a.nz - 2 + zc - 1) / zc);
-            const double cost = (double)((wg + 255) / 256) * (zc + 2) * (211 + th * (z.W - 2));
-            if (best == 0 || cost < best) {
-                best = cost;
-                z.HG = hg;
-                z.zc = zc;
+    for (int target = 128; target >= 32; target /= 2) {
+        const int ntx = (nv + target - 1) / target, W = ((nv + ntx - 1) / ntx + 7) / 8 * 8 + 2;
+        if (best > 0 && W < 42) continue;
+        for (int hg = 1024 / W; hg * RY >= 6 && hg * W > 700 - W; --hg) {
+            const int th = hg * RY - 4;
+            const int64_t cols = (int64_t)ntx * ((a.ny - 2 + th - 1) / th);
+            for (int zc = 6; zc <= 64; ++zc) {
+                const int64_t wg = cols * ((a.nz - 2 + zc - 1) / zc);
+                const double cost = (double)((wg + 255) / 256) * (zc + 1) * (400 + th * (W - 2) + 2 * W);
+                if (best == 0 || cost < best) {
+                    best = cost;
+                    z.ntx = ntx;
+                    z.W = W;
+                    z.HG = hg;
+                    z.zc = zc;
+                }
             }
         }
     }
     const int TH = z.HG * RY - 4;
     z.nty = (a.ny - 2 + TH - 1) / TH;
     const int64_t blocks = (int64_t)z.ntx * z.nty * ((a.nz - 2 + z.zc - 1) / z.zc);
+    // Stores that stay in the caches where T, T2 and Ci fit the 256 MB
+    // last-level cache together (256^3 FP32 47 us a launch against 52, 320 x
+    // 200 x 150 FP64 52 against 54; 320 x 300 x 170 FP64, 392 MB, 90 against
+    // 86), and for launches of several rounds tile rows dealt to the XCDs in
+    // turn instead of in ranges (512^3 FP64 630 against 639, FP32 322 against
+    // 338; 256^3 FP64, one round, 87 against 84).
+    z.nt = (int64_t)a.nx * a.ny * a.nz * 3 * (int64_t)sizeof(S) > ((int64_t)240 << 20);
+    z.deal = blocks > 512;
     const size_t lds = ((size_t)4 * z.W * z.HG * RY + 2) * VEC * sizeof(S);
     const int tpb = (z.W * z.HG + 63) / 64 * 64;
     const PairCoef<S> cf{(S)a.a, (S)a.rx, (S)a.ry, (S)a.rz};
