@@ -174,8 +174,7 @@ int ensure_device()
     int64_t cap = std::max(m0, std::max(m1, m2)) * 8;
     g.halo_cap = (size_t)((cap + 255) / 256 * 256);
     IGG_HIP(hipMalloc((void **)&g.halo_buf, g.halo_cap * 2 * 2 * IGG_MAX_FIELDS * g.nranks));
-    IGG_HIP(hipMalloc((void **)&g.red_part, 8192 * sizeof(double)));
-    IGG_HIP(hipHostMalloc((void **)&g.red_host, 64 * sizeof(double), hipHostMallocDefault));
+    IGG_HIP(hipHostMalloc((void **)&g.red_host, 1024 * sizeof(double), hipHostMallocDefault));
     g.device = dev;
     g.dev_ready = true;
     return IGG_OK;
@@ -191,7 +190,6 @@ static int release_device()
     };
     chk(hipStreamSynchronize(g.side), "hipStreamSynchronize(side)");
     chk(hipFree(g.halo_buf), "hipFree(halo_buf)");
-    chk(hipFree(g.red_part), "hipFree(red_part)");
     chk(hipHostFree(g.red_host), "hipHostFree(red_host)");
     chk(hipEventDestroy(g.ev_fork), "hipEventDestroy");
     chk(hipEventDestroy(g.ev_join), "hipEventDestroy");
@@ -694,13 +692,12 @@ static int adjoint_step(int form, const igg_field *lam_n, const igg_field *lam_n
         // adjoint runs its chain serially anyway, so the boundary has nothing
         // to overlap)
         AdjArgs a0 = args[0];
-        const bool sized = lam_n[0].size[1] == g.n[1] && lam_n[0].size[2] == g.n[2];
-        if (sized) a0.yz = YZImg{1, g.ol[1] - 1, g.n[1] - g.ol[1], g.ol[2] - 1, g.n[2] - g.ol[2], g.n[1], g.n[2]};
+        a0.yz = YZImg{1, g.ol[1] - 1, g.n[1] - g.ol[1], g.ol[2] - 1, g.n[2] - g.ol[2], g.n[1], g.n[2]};
         if ((rc = timing_mark(s, 0))) return rc;
         if ((rc = launch_adjoint_inner(dt_, a0, all, s))) return rc;
         if ((rc = timing_mark(s, 0))) return rc;
         if (g.timing) { g.t_launches++; g.t_points += box_points(all); }
-        return sized ? IGG_OK : launch_halo_self_yz(lam_n[0], s);
+        return IGG_OK;
     }
     if (!split) {
         for (int r = 0; r < P; ++r) {
@@ -1296,9 +1293,10 @@ int igg_adjoint_seed(const igg_field *T, const igg_field *T_obs, const igg_field
     }
     if ((rc = ensure_device())) return rc;
     hipStream_t s = (hipStream_t)stream;
-    if ((rc = launch_seed(T, T_obs, *lam, loss, s))) return rc;
+    int parts = 0;
+    if ((rc = launch_seed(T, T_obs, *lam, loss ? &parts : nullptr, s))) return rc;
     if (halo && (rc = launch_halo(lam, 1, s))) return rc;
-    return loss ? read_reduce_result(loss, s) : IGG_OK;
+    return loss ? read_seed_loss(parts, loss, s) : IGG_OK;
 }
 
 int igg_reduce_noalloc(int op, const igg_field *a, const igg_field *b, double *out_dev, void *stream)

@@ -11,10 +11,11 @@
 //
 // The process holds every rank of the topology (one, or several virtual
 // ranks as separate blocks on this device), so the exchange is a device copy
-// from a rank's send buffer into its neighbour's receive buffer; a periodic
-// dimension of one rank is its own neighbour on both sides.  One launch per
-// dimension and rank runs all three phases: each thread packs its elements,
-// exchanges them and unpacks them into the neighbour's halo.
+// from a rank's send buffer into its neighbour's receive buffer.  One launch
+// per dimension and rank runs all three phases: each thread packs its
+// elements, exchanges them and unpacks them into the neighbour's halo.  One
+// rank is its own neighbour in every periodic dimension, and one launch fills
+// its halo without buffers (launch_halo_one).
 #include "host.hpp"
 
 namespace igg {
@@ -160,59 +161,118 @@ int launch_unpack_self(const igg_field &f, const SlabPack &pk, hipStream_t s)
     return IGG_OK;
 }
 
-// Gather form of the y and z halo update for a rank that is its own
-// neighbour: plane q of the four (y side 0: j = ny-1, side 1: j = 0; z
-// likewise) is filled point by point from the image of each point, the
-// index map img(0) = n-ol, img(n-1) = ol-1, img(c) = c otherwise, applied in
-// every dimension.  Images are inner points, which the step wrote, so the
-// four planes are independent and one launch fills them.
-struct SelfHalo {
+// ------------------------------------------------------------- one rank
+// The halo update of a rank that is its own neighbour in the periodic
+// dimensions: the dimension-ordered exchange of whole planes leaves at a halo
+// point the value at its image, the index map img(0) = n-ol, img(n-1) = ol-1,
+// img(c) = c otherwise, applied in every updated dimension.  Images are not
+// halo points of those dimensions, so every halo point of every field and
+// dimension is filled at once, each from one read.  Bound by the launch and by
+// the x planes, which are two elements of every row.
+struct GatherField {
     unsigned char *base;
-    int nx, ny, nz;
-    int ol[3];
+    int n[3];
+    int lo[3], hi[3];  // images of n-1 and 0
     int esz;
 };
+struct GatherSet {
+    GatherField f[IGG_MAX_FIELDS];
+    int dims;  // bit d: dimension d is updated (and periodic)
+    int rows_blocks;  // work-groups of the y and z planes; the rest take the x planes
+};
 
-__device__ __forceinline__ int self_img(int c, int n, int ol) { return c == 0 ? n - ol : (c == n - 1 ? ol - 1 : c); }
+__device__ __forceinline__ int halo_img(int c, int n, int lo, int hi) { return c == 0 ? hi : (c == n - 1 ? lo : c); }
 
 template <typename E>
-__global__ void __launch_bounds__(256) k_halo_gather_yz(SelfHalo h)
+__device__ __forceinline__ void gather_field(const GatherField &f, int dims, int rb)
 {
-    E *A = reinterpret_cast<E *>(h.base);
-    const int q = blockIdx.y;  // 0, 1: y planes (ny-1, 0); 2, 3: z planes (nz-1, 0)
-    const int64_t nx = h.nx, sxy = (int64_t)h.nx * h.ny;
-    const int nb = q < 2 ? h.nz : h.ny;
-    const int64_t count = nx * nb;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < count;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int a = (int)(e % nx), b = (int)(e / nx);
-        const int sa = self_img(a, h.nx, h.ol[0]);
-        int64_t dst, src;
-        if (q < 2) {
-            const int j = q == 0 ? h.ny - 1 : 0;
-            dst = (int64_t)b * sxy + (int64_t)j * nx + a;
-            src = (int64_t)self_img(b, h.nz, h.ol[2]) * sxy + (int64_t)self_img(j, h.ny, h.ol[1]) * nx + sa;
-        } else {
-            const int k = q == 2 ? h.nz - 1 : 0;
-            dst = (int64_t)k * sxy + (int64_t)b * nx + a;
-            src = (int64_t)self_img(k, h.nz, h.ol[2]) * sxy + (int64_t)self_img(b, h.ny, h.ol[1]) * nx + sa;
+    constexpr int VEC = 16 / (int)sizeof(E);
+    typedef E V __attribute__((ext_vector_type(VEC)));
+    typedef E M __attribute__((ext_vector_type(VEC), aligned(sizeof(E))));
+    E *A = reinterpret_cast<E *>(f.base);
+    const int nx = f.n[0], ny = f.n[1], nz = f.n[2];
+    const int64_t sxy = (int64_t)nx * ny;
+    const bool dx = dims & 1, dy = dims & 2, dz = dims & 4;
+    auto src_row = [&](int j, int k) -> const E * {
+        const int js = dy ? halo_img(j, ny, f.lo[1], f.hi[1]) : j, ks = dz ? halo_img(k, nz, f.lo[2], f.hi[2]) : k;
+        return A + ks * sxy + (int64_t)js * nx;
+    };
+    if ((int)blockIdx.x < rb) {
+        // y and z planes: vectors of their rows (2 nz rows of the y planes,
+        // then 2 ny of the z planes)
+        const uint32_t nv = (uint32_t)((nx + VEC - 1) / VEC), yr = dy ? 2u * nz : 0u, zr = dz ? 2u * ny : 0u;
+        const uint32_t count = nv * (yr + zr);
+        for (uint32_t e = blockIdx.x * 256 + threadIdx.x; e < count; e += (uint32_t)rb * 256) {
+            const uint32_t row = e / nv;
+            const int i = (int)(e - row * nv) * VEC;
+            int j, k;
+            if (row < yr) {
+                j = row & 1 ? ny - 1 : 0;
+                k = (int)(row >> 1);
+            } else {
+                j = (int)((row - yr) >> 1);
+                k = (row - yr) & 1 ? nz - 1 : 0;
+            }
+            E *D = A + k * sxy + (int64_t)j * nx;
+            const E *P = src_row(j, k);
+            if (i + VEC <= nx) {
+                V v = *reinterpret_cast<const M *>(P + i);
+                if (dx && i == 0) v[0] = P[f.hi[0]];
+                if (dx && i + VEC == nx) v[VEC - 1] = P[f.lo[0]];
+                *reinterpret_cast<M *>(D + i) = v;
+            } else {
+                for (int q = i; q < nx; ++q) D[q] = P[dx ? halo_img(q, nx, f.lo[0], f.hi[0]) : q];
+            }
         }
-        A[dst] = A[src];
+    } else if (dx) {
+        // x planes: both ends of every row that is in no updated y or z plane
+        const uint32_t j0 = dy ? 1 : 0, k0 = dz ? 1 : 0, h = ny - 2 * j0, count = h * (nz - 2 * k0);
+        const uint32_t step = (gridDim.x - rb) * 256;
+        for (uint32_t e = (blockIdx.x - rb) * 256 + threadIdx.x; e < count; e += step) {
+            const uint32_t k = e / h;
+            E *D = A + (int64_t)(k + k0) * sxy + (int64_t)(e - k * h + j0) * nx;
+            const E a = D[f.hi[0]], b = D[f.lo[0]];
+            D[0] = a;
+            D[nx - 1] = b;
+        }
     }
 }
 
-int launch_halo_self_yz(const igg_field &f, hipStream_t s)
+__global__ void __launch_bounds__(256) k_halo_gather(GatherSet gs)
+{
+    const GatherField &f = gs.f[blockIdx.y];
+    switch (f.esz) {
+    case 8: gather_field<uint64_t>(f, gs.dims, gs.rows_blocks); break;
+    case 4: gather_field<uint32_t>(f, gs.dims, gs.rows_blocks); break;
+    default: gather_field<uint16_t>(f, gs.dims, gs.rows_blocks); break;
+    }
+}
+
+static int launch_halo_one(const igg_field *fl, int nf, hipStream_t s, int dims)
 {
     Grid &g = grid();
-    SelfHalo h{(unsigned char *)f.data, (int)f.size[0], (int)f.size[1], (int)f.size[2], {0, 0, 0},
-               elem_bytes(f.dtype)};
-    for (int d = 0; d < 3; ++d) h.ol[d] = g.ol[d] + (int)(f.size[d] - g.n[d]);
-    const int64_t maxcount = (int64_t)h.nx * std::max(h.ny, h.nz);
-    const int64_t b = (maxcount + 255) / 256;
-    const dim3 grd((unsigned)std::min<int64_t>(std::max<int64_t>(b, 1), 1024), 4);
-    if (h.esz == 8) hipLaunchKernelGGL(k_halo_gather_yz<uint64_t>, grd, dim3(256), 0, s, h);
-    else if (h.esz == 4) hipLaunchKernelGGL(k_halo_gather_yz<uint32_t>, grd, dim3(256), 0, s, h);
-    else hipLaunchKernelGGL(k_halo_gather_yz<uint16_t>, grd, dim3(256), 0, s, h);
+    GatherSet gs{};
+    for (int d = 0; d < 3; ++d)
+        if (((dims >> d) & 1) && g.periods[d]) gs.dims |= 1 << d;
+    if (gs.dims == 0) return IGG_OK;
+    int64_t rows = 0, cols = 0;
+    for (int q = 0; q < nf; ++q) {
+        GatherField &f = gs.f[q];
+        f.base = (unsigned char *)fl[q].data;
+        f.esz = elem_bytes(fl[q].dtype);
+        for (int d = 0; d < 3; ++d) {
+            f.n[d] = (int)fl[q].size[d];
+            const int ol = g.ol[d] + (f.n[d] - g.n[d]);
+            f.lo[d] = ol - 1;
+            f.hi[d] = f.n[d] - ol;
+        }
+        const int64_t nv = ((int64_t)f.n[0] * f.esz + 15) / 16;
+        rows = std::max(rows, nv * ((gs.dims & 2 ? 2 * f.n[2] : 0) + (gs.dims & 4 ? 2 * f.n[1] : 0)));
+        cols = std::max(cols, gs.dims & 1 ? (int64_t)f.n[1] * f.n[2] : 0);
+    }
+    auto blocks = [](int64_t n) { return (int)std::min<int64_t>((n + 255) / 256, 2048); };
+    gs.rows_blocks = blocks(rows);
+    hipLaunchKernelGGL(k_halo_gather, dim3((unsigned)(gs.rows_blocks + blocks(cols)), nf), dim3(256), 0, s, gs);
     IGG_HIP(hipGetLastError());
     return IGG_OK;
 }
@@ -220,6 +280,7 @@ int launch_halo_self_yz(const igg_field &f, hipStream_t s)
 int launch_halo(const igg_field *fl, int nf, hipStream_t s, int dims)
 {
     Grid &g = grid();
+    if (g.nranks == 1) return launch_halo_one(fl, nf, s, dims);
     for (int d = 0; d < 3; ++d) {
         if (!((dims >> d) & 1)) continue;  // done elsewhere (fused into the step)
         for (int r = 0; r < g.nranks; ++r) {

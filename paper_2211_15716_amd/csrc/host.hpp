@@ -68,8 +68,7 @@ struct Grid {
     unsigned char *halo_buf = nullptr;  // send and receive planes of every rank
     size_t halo_cap = 0;                // bytes of one side of one field (one plane)
 
-    double *red_part = nullptr;  // per-block partial results
-    double *red_host = nullptr;  // pinned host result
+    double *red_host = nullptr;  // pinned host memory: per-block partial results
 
     int schedule = -1;  // 1: slabs + update on the helper stream, 0: slabs first on the caller
                         // stream, 2: one chain on the caller stream, -1: 1 or 2 by size
@@ -204,12 +203,6 @@ int launch_step_slabs(int dtype, const StepArgs &a, const Split &sp, const SlabP
 // is copied into the halo plane of f it fills (y plane side 0 -> j = ny-1,
 // side 1 -> j = 0; z likewise), one launch for the four planes.
 int launch_unpack_self(const igg_field &f, const SlabPack &pk, hipStream_t s);
-// The y and z halo update of f for one rank that is its own neighbour in
-// every dimension, in one launch: every point of the y and z halo planes
-// takes the value of its image among the inner points, which is what the
-// dimension-ordered update leaves there (the x halo columns of inner rows
-// must already hold their images; the step kernels store them).
-int launch_halo_self_yz(const igg_field &f, hipStream_t s);
 // Send buffer of rank r, slot f (a field index of the halo update), side.
 unsigned char *halo_send_plane(int r, int f, int side);
 
@@ -270,11 +263,12 @@ int launch_flux_inner(int dtype, const FluxArgs &a, const Box &b, hipStream_t s)
 
 
 int launch_reduce(int op, const igg_field &a, const igg_field *b, double *out, hipStream_t s);
-// lam = a - b (or a, or 0) on the inner points of lam, zero on its halo;
-// with loss, the FP64 loss 0.5*sum (a-b)^2 is left for read_reduce_result.
-int launch_seed(const igg_field *a, const igg_field *b, const igg_field &lam, double *loss, hipStream_t s);
-// The value the last reduction left on the device, after synchronising s.
-int read_reduce_result(double *out, hipStream_t s);
+// lam = a - b (or a, or 0) on the inner points of lam, zero on its halo; with
+// parts, *parts partial sums of the FP64 loss 0.5*sum (a-b)^2 are left for
+// read_seed_loss.
+int launch_seed(const igg_field *a, const igg_field *b, const igg_field &lam, int *parts, hipStream_t s);
+// The loss from the last seed's partial sums, after synchronising s.
+int read_seed_loss(int parts, double *out, hipStream_t s);
 // The same reduction into *out_dev (device memory), with the partial results
 // in the library's static device array instead of the grid's buffers: no
 // allocation, no synchronisation.

@@ -1,9 +1,10 @@
 // reduce.hip -- FP64 reductions over a field (maximum(Ci) of Fig. 1, loss,
 // conservation and dot-product sums).  Values are widened to FP64 before
-// they are combined; rows are dealt to a fixed number of work-groups and
-// combined in a fixed tree, so a call's bits do not vary between runs.
+// they are combined; rows are dealt to a fixed number of waves and combined
+// in a fixed tree, so a call's bits do not vary between runs.
 #include <mutex>
 #include <string>
+#include <type_traits>
 
 #include "host.hpp"
 
@@ -12,7 +13,7 @@ namespace igg {
 constexpr int RED_THREADS = 256;
 constexpr int RED_BLOCKS = 1024;
 
-__device__ __forceinline__ double combine(int op, double x, double y)
+__host__ __device__ __forceinline__ double combine(int op, double x, double y)
 {
     if (op == IGG_RED_MIN) return (x < y || x != x) ? x : y;
     if (op == IGG_RED_MAX || op == IGG_RED_MAX_ABS_DIFF || op == IGG_RED_MAX_ABS)
@@ -20,7 +21,7 @@ __device__ __forceinline__ double combine(int op, double x, double y)
     return x + y;
 }
 
-__device__ __forceinline__ double identity(int op)
+__host__ __device__ __forceinline__ double identity(int op)
 {
     if (op == IGG_RED_MIN) return __builtin_inf();
     if (op == IGG_RED_MAX || op == IGG_RED_MAX_ABS_DIFF || op == IGG_RED_MAX_ABS) return -__builtin_inf();
@@ -28,14 +29,14 @@ __device__ __forceinline__ double identity(int op)
 }
 
 template <typename S>
-__device__ __forceinline__ double term(int op, const S *a, const S *b, int64_t p)
+__device__ __forceinline__ double term(int op, S a, S b)
 {
-    double x = (double)(compute_t<S>)a[p];
+    const double x = (double)(compute_t<S>)a, y = (double)(compute_t<S>)b;
     switch (op) {
-    case IGG_RED_SUM_RATIO: return x / (double)(compute_t<S>)b[p];
-    case IGG_RED_HALF_SQDIFF: { double d = x - (double)(compute_t<S>)b[p]; return 0.5 * (d * d); }
-    case IGG_RED_DOT: return x * (double)(compute_t<S>)b[p];
-    case IGG_RED_MAX_ABS_DIFF: return __builtin_fabs(x - (double)(compute_t<S>)b[p]);
+    case IGG_RED_SUM_RATIO: return x / y;
+    case IGG_RED_HALF_SQDIFF: { double d = x - y; return 0.5 * (d * d); }
+    case IGG_RED_DOT: return x * y;
+    case IGG_RED_MAX_ABS_DIFF: return __builtin_fabs(x - y);
     case IGG_RED_MAX_ABS: return __builtin_fabs(x);
     default: return x;
     }
@@ -52,23 +53,113 @@ __device__ __forceinline__ double block_combine(int op, double v, double *sh)
     return sh[0];
 }
 
-// Rows (j, k) of the region go to work-groups round-robin; each thread
-// walks its row with a stride of the block size.
-template <typename S>
-__global__ void __launch_bounds__(RED_THREADS)
-k_reduce(const S *__restrict__ a, const S *__restrict__ b, int op, int nx, int ny, int i0, int i1,
-         int j0, int j1, int k0, int k1, double *__restrict__ part)
+// The rows (j, k) of a region of h x depth rows and nx points per row, i0 to
+// i1 of each, dealt to the waves of the launch in turn (ROWS at a time, so
+// that their loads are in flight together) and walked in vectors of 16 bytes:
+// load(q, p, n) reads the n points at offset p into slot q, use(q, p, n)
+// takes them, in an order that depends on the region and the launch only.
+// n is VEC, or 1 at the end of a row.
+struct RedRegion {
+    int nx, ny, i0, i1, j0, k0, h;
+    int64_t rows;
+    int dj, dk;  // rows and planes from one of a wave's rows to its next
+};
+template <int VEC, int ROWS, typename Load, typename Use>
+__device__ __forceinline__ void red_walk(const RedRegion &g, Load &&load, Use &&use)
 {
-    __shared__ double sh[RED_THREADS];
-    double acc = identity(op);
-    const int64_t h = j1 - j0;
-    const int64_t rows = h * (k1 - k0);
-    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
-        const int j = j0 + (int)(r % h), k = k0 + (int)(r / h);
-        const int64_t base = (int64_t)k * nx * ny + (int64_t)j * nx;
-        for (int i = i0 + threadIdx.x; i < i1; i += RED_THREADS) acc = combine(op, acc, term<S>(op, a, b, base + i));
+    const int lane = threadIdx.x & 63;
+    const int64_t waves = (int64_t)gridDim.x * (RED_THREADS / 64);
+    int64_t r = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (RED_THREADS / 64) + (threadIdx.x >> 6)));
+    int j = (int)(r % g.h), k = (int)(r / g.h);
+    for (; r < g.rows; r += ROWS * waves) {
+        int64_t base[ROWS];
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q) {
+            base[q] = ((int64_t)(g.k0 + k) * g.ny + g.j0 + j) * g.nx;
+            j += g.dj;
+            k += g.dk;
+            if (j >= g.h) {
+                j -= g.h;
+                ++k;
+            }
+        }
+        const int nr = r + (ROWS - 1) * waves < g.rows ? ROWS : (int)((g.rows - r + waves - 1) / waves);
+        for (int i = g.i0 + lane * VEC; i < g.i1; i += 64 * VEC) {
+            if (i + VEC <= g.i1) {
+#pragma unroll
+                for (int q = 0; q < ROWS; ++q)
+                    if (q < nr) load(q, base[q] + i, std::integral_constant<int, VEC>());
+#pragma unroll
+                for (int q = 0; q < ROWS; ++q)
+                    if (q < nr) use(q, base[q] + i, std::integral_constant<int, VEC>());
+            } else {
+                for (int e = i; e < g.i1; ++e)
+#pragma unroll
+                    for (int q = 0; q < ROWS; ++q)
+                        if (q < nr) {
+                            load(q, base[q] + e, std::integral_constant<int, 1>());
+                            use(q, base[q] + e, std::integral_constant<int, 1>());
+                        }
+            }
+        }
     }
-    double v = block_combine(op, acc, sh);
+}
+
+template <typename S> struct RedVec {
+    static constexpr int N = 16 / (int)sizeof(S);
+    typedef S type __attribute__((ext_vector_type(N)));
+    typedef S mem __attribute__((ext_vector_type(N), aligned(sizeof(S))));  // rows start at any element
+};
+
+// Rows of one array, or of two, that a wave reads together.
+constexpr int RED_ROWS1 = 8, RED_ROWS2 = 4;
+
+// A thread's accumulators into one.
+template <int N>
+__device__ __forceinline__ double red_lanes(int op, const double (&acc)[N])
+{
+    double v = acc[0];
+#pragma unroll
+    for (int e = 1; e < N; ++e) v = combine(op, v, acc[e]);
+    return v;
+}
+
+// Bound by the loads it has in flight (8 KB of one array or of two per wave)
+// and the ramp of a launch; the operation is a template argument because a
+// branch per point cost as much as the loads.  256 x 250 x 241 FP64: maximum
+// 56 -> 31 us, sum 53 -> 29 (123 MB), dot product 59 -> 43 (247 MB); 512^3:
+// maximum 363 -> 219 us (4.9 TB/s), dot product 423 -> 367 (5.9 TB/s), against
+// one row per work-group and one point per lane.
+template <typename S, int OP>
+__global__ void __launch_bounds__(RED_THREADS)
+k_reduce(const S *__restrict__ a, const S *__restrict__ b, RedRegion g, double *__restrict__ part)
+{
+    using R = RedVec<S>;
+    constexpr bool TWO = OP == IGG_RED_SUM_RATIO || OP == IGG_RED_HALF_SQDIFF || OP == IGG_RED_DOT ||
+                         OP == IGG_RED_MAX_ABS_DIFF;
+    constexpr int ROWS = TWO ? RED_ROWS2 : RED_ROWS1;
+    __shared__ double sh[RED_THREADS];
+    double acc[R::N];  // one per element of a vector
+#pragma unroll
+    for (int e = 0; e < R::N; ++e) acc[e] = identity(OP);
+    typename R::type va[ROWS], vb[ROWS];
+    red_walk<R::N, ROWS>(
+        g,
+        [&](int q, int64_t p, auto n) {
+            if constexpr (n.value > 1) {
+                va[q] = *reinterpret_cast<const typename R::mem *>(a + p);
+                if (TWO) vb[q] = *reinterpret_cast<const typename R::mem *>(b + p);
+            } else {
+                va[q][0] = a[p];
+                if (TWO) vb[q][0] = b[p];
+            }
+        },
+        [&](int q, int64_t, auto n) {
+#pragma unroll
+            for (int e = 0; e < n.value; ++e)
+                acc[e] = combine(OP, acc[e], term<S>(OP, va[q][e], TWO ? vb[q][e] : S(0)));
+        });
+    double v = block_combine(OP, red_lanes<R::N>(OP, acc), sh);
     if (threadIdx.x == 0) part[blockIdx.x] = v;
 }
 
@@ -83,86 +174,137 @@ k_reduce_final(int op, int n, const double *__restrict__ part, double *__restric
     if (threadIdx.x == 0) *result = v;
 }
 
-// The two launches of a reduction: partial results of at most RED_BLOCKS
-// work-groups into part[0..blocks), then their combination into *result.
-template <typename S>
-static int launch_two(int op, const igg_field &a, const igg_field *b, double *part, int part_cap, double *result,
-                      hipStream_t s)
+static RedRegion red_region(const igg_field &a, bool all, int &blocks)
 {
-    const int nx = (int)a.size[0], ny = (int)a.size[1], nz = (int)a.size[2];
-    const bool all = op == IGG_RED_MAX || op == IGG_RED_MIN;
-    int i0 = all ? 0 : 1, i1 = all ? nx : nx - 1;
-    int j0 = all ? 0 : 1, j1 = all ? ny : ny - 1;
-    int k0 = all ? 0 : 1, k1 = all ? nz : nz - 1;
-    int64_t rows = (int64_t)(j1 - j0) * (k1 - k0);
-    int blocks = (int)(rows < RED_BLOCKS ? (rows < 1 ? 1 : rows) : RED_BLOCKS);
-    if (blocks > part_cap)
-        return fail(IGG_ERR_SIZE, "reduction needs " + std::to_string(blocks) + " partial results, the buffer holds " +
+    RedRegion g{};
+    const int nx = (int)a.size[0], ny = (int)a.size[1], nz = (int)a.size[2], in = all ? 0 : 1;
+    g.nx = nx;
+    g.ny = ny;
+    g.i0 = g.j0 = g.k0 = in;
+    g.i1 = nx - in;
+    g.h = ny - 2 * in;
+    g.rows = (int64_t)g.h * (nz - 2 * in);
+    const int64_t want = (g.rows + RED_THREADS / 64 - 1) / (RED_THREADS / 64);
+    blocks = (int)(want < RED_BLOCKS ? (want < 1 ? 1 : want) : RED_BLOCKS);
+    const int64_t waves = (int64_t)blocks * (RED_THREADS / 64);
+    g.dj = (int)(waves % g.h);
+    g.dk = (int)(waves / g.h);
+    return g;
+}
+
+// Partial results of `blocks` work-groups (at most RED_BLOCKS) into part.
+template <typename S>
+static int launch_part(int op, const igg_field &a, const igg_field *b, double *part, int part_cap, int *blocks,
+                       hipStream_t s)
+{
+    const RedRegion g = red_region(a, op == IGG_RED_MAX || op == IGG_RED_MIN, *blocks);
+    if (*blocks > part_cap)
+        return fail(IGG_ERR_SIZE, "reduction needs " + std::to_string(*blocks) + " partial results, the buffer holds " +
                                       std::to_string(part_cap));
-    hipLaunchKernelGGL(k_reduce<S>, dim3(blocks), dim3(RED_THREADS), 0, s, (const S *)a.data,
-                       b ? (const S *)b->data : (const S *)nullptr, op, nx, ny, i0, i1, j0, j1, k0, k1, part);
-    IGG_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(RED_THREADS), 0, s, op, blocks, (const double *)part, result);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(*blocks), dim3(RED_THREADS), 0, s, (const S *)a.data,
+                           b ? (const S *)b->data : (const S *)nullptr, g, part);
+    };
+    switch (op) {
+    case IGG_RED_MAX: go(k_reduce<S, IGG_RED_MAX>); break;
+    case IGG_RED_MIN: go(k_reduce<S, IGG_RED_MIN>); break;
+    case IGG_RED_SUM: go(k_reduce<S, IGG_RED_SUM>); break;
+    case IGG_RED_SUM_RATIO: go(k_reduce<S, IGG_RED_SUM_RATIO>); break;
+    case IGG_RED_HALF_SQDIFF: go(k_reduce<S, IGG_RED_HALF_SQDIFF>); break;
+    case IGG_RED_DOT: go(k_reduce<S, IGG_RED_DOT>); break;
+    case IGG_RED_MAX_ABS_DIFF: go(k_reduce<S, IGG_RED_MAX_ABS_DIFF>); break;
+    case IGG_RED_MAX_ABS: go(k_reduce<S, IGG_RED_MAX_ABS>); break;
+    default: return fail(IGG_ERR_ARG, "unknown reduction");
+    }
     IGG_HIP(hipGetLastError());
     return IGG_OK;
 }
 
-static int launch_typed(int op, const igg_field &a, const igg_field *b, double *part, int part_cap, double *result,
+static int launch_typed(int op, const igg_field &a, const igg_field *b, double *part, int part_cap, int *blocks,
                         hipStream_t s)
 {
     if (b && b->dtype != a.dtype) return fail(IGG_ERR_DTYPE, "a and b must share one dtype");
-    if (a.dtype == IGG_F64) return launch_two<double>(op, a, b, part, part_cap, result, s);
-    if (a.dtype == IGG_F32) return launch_two<float>(op, a, b, part, part_cap, result, s);
-    return launch_two<_Float16>(op, a, b, part, part_cap, result, s);
+    if (a.dtype == IGG_F64) return launch_part<double>(op, a, b, part, part_cap, blocks, s);
+    if (a.dtype == IGG_F32) return launch_part<float>(op, a, b, part, part_cap, blocks, s);
+    return launch_part<_Float16>(op, a, b, part, part_cap, blocks, s);
 }
 
+// k_reduce_final on the host, in the same order (the same bits).
+static double combine_host(int op, int n, const double *part)
+{
+    double acc[RED_THREADS];
+    for (int t = 0; t < RED_THREADS; ++t) {
+        acc[t] = identity(op);
+        for (int q = t; q < n; q += RED_THREADS) acc[t] = combine(op, acc[t], part[q]);
+    }
+    for (int w = RED_THREADS / 2; w > 0; w >>= 1)
+        for (int t = 0; t < w; ++t) acc[t] = combine(op, acc[t], acc[t + w]);
+    return acc[0];
+}
+
+// The work-groups write their partial results straight to pinned host memory
+// (8 KB) and the host combines them: no second launch and no copy between
+// the reduction and the synchronisation its caller asks for.
 int launch_reduce(int op, const igg_field &a, const igg_field *b, double *out, hipStream_t s)
 {
     Grid &g = grid();
-    int rc;
-    if ((rc = launch_typed(op, a, b, g.red_part, RED_BLOCKS, g.red_part + RED_BLOCKS, s))) return rc;
-    IGG_HIP(hipMemcpyAsync(g.red_host, g.red_part + RED_BLOCKS, sizeof(double), hipMemcpyDeviceToHost, s));
+    int rc, blocks = 0;
+    if ((rc = launch_typed(op, a, b, g.red_host, RED_BLOCKS, &blocks, s))) return rc;
     IGG_HIP(hipStreamSynchronize(s));
-    *out = g.red_host[0];
+    *out = combine_host(op, blocks, g.red_host);
     return IGG_OK;
 }
 
 // ------------------------------------------------------- adjoint seed
 // lam = a - b on the inner points (a alone without b, zero without a), zero
-// on every halo point; with want_loss, the partial sums of 0.5*(a-b)^2 for
-// k_reduce_final.  The inner rows are dealt to work-groups and walked by the
-// threads exactly as k_reduce walks them for IGG_RED_HALF_SQDIFF, so the
-// loss has the bits of that reduction.  The halo rows and columns are
-// zeroed in a second walk.
+// on every halo point; with want_loss, the partial sums of 0.5*(a-b)^2.  The
+// inner rows are walked exactly as k_reduce walks them for
+// IGG_RED_HALF_SQDIFF, so the loss has the bits of that reduction.  The halo
+// rows and columns are zeroed in a second walk.
 template <typename S>
 __global__ void __launch_bounds__(RED_THREADS)
-k_seed(const S *__restrict__ a, const S *__restrict__ b, S *__restrict__ lam, int nx, int ny, int nz,
+k_seed(const S *__restrict__ a, const S *__restrict__ b, S *__restrict__ lam, int nz, RedRegion g,
        double *__restrict__ part)
 {
     using C = compute_t<S>;
+    using R = RedVec<S>;
     __shared__ double sh[RED_THREADS];
-    double acc = 0.0;
-    const int64_t h = ny - 2;
-    const int64_t rows = h * (nz - 2);
-    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
-        const int j = 1 + (int)(r % h), k = 1 + (int)(r / h);
-        const int64_t base = (int64_t)k * nx * ny + (int64_t)j * nx;
-        for (int i = 1 + threadIdx.x; i < nx - 1; i += RED_THREADS) {
-            const int64_t p = base + i;
-            S v = S(0);
-            if (a) {
-                if (b) {
-                    v = (S)((C)a[p] - (C)b[p]);
-                    const double d = (double)(C)a[p] - (double)(C)b[p];
-                    acc += 0.5 * (d * d);
-                } else {
-                    v = a[p];
+    double acc[R::N] = {};
+    const int nx = g.nx, ny = g.ny;
+    typename R::type va[RED_ROWS2], vb[RED_ROWS2];
+    red_walk<R::N, RED_ROWS2>(
+        g,
+        [&](int q, int64_t p, auto n) {
+            if (!a) return;
+            if constexpr (n.value > 1) {
+                va[q] = *reinterpret_cast<const typename R::mem *>(a + p);
+                if (b) vb[q] = *reinterpret_cast<const typename R::mem *>(b + p);
+            } else {
+                va[q][0] = a[p];
+                if (b) vb[q][0] = b[p];
+            }
+        },
+        [&](int q, int64_t p, auto n) {
+            typename R::type v{};
+#pragma unroll
+            for (int e = 0; e < n.value; ++e) {
+                if (a && b) {
+                    v[e] = (S)((C)va[q][e] - (C)vb[q][e]);
+                    const double d = (double)(C)va[q][e] - (double)(C)vb[q][e];
+                    acc[e] += 0.5 * (d * d);
+                } else if (a) {
+                    v[e] = va[q][e];
                 }
             }
-            lam[p] = v;
-        }
-        if (threadIdx.x == 0) lam[base] = S(0);
-        if (threadIdx.x == 1) lam[base + nx - 1] = S(0);
+            if constexpr (n.value > 1) *reinterpret_cast<typename R::mem *>(lam + p) = v;
+            else lam[p] = v[0];
+        });
+    const int64_t t = (int64_t)blockIdx.x * RED_THREADS + threadIdx.x, nt = (int64_t)gridDim.x * RED_THREADS;
+    // halo columns of the inner rows
+    for (int64_t r = t; r < g.rows; r += nt) {
+        const int64_t base = ((1 + r / g.h) * ny + 1 + r % g.h) * nx;
+        lam[base] = S(0);
+        lam[base + nx - 1] = S(0);
     }
     // halo rows: j = 0 and ny-1 of every plane, then every row of planes 0 and nz-1
     const int64_t hrows = 2 * (int64_t)nz + 2 * (int64_t)(ny - 2);
@@ -180,42 +322,37 @@ k_seed(const S *__restrict__ a, const S *__restrict__ b, S *__restrict__ lam, in
         for (int i = threadIdx.x; i < nx; i += RED_THREADS) lam[base + i] = S(0);
     }
     if (part) {
-        double v = block_combine(IGG_RED_HALF_SQDIFF, acc, sh);
+        double v = block_combine(IGG_RED_HALF_SQDIFF, red_lanes<R::N>(IGG_RED_HALF_SQDIFF, acc), sh);
         if (threadIdx.x == 0) part[blockIdx.x] = v;
     }
 }
 
-int launch_seed(const igg_field *a, const igg_field *b, const igg_field &lam, double *loss, hipStream_t s)
+template <typename S>
+static int seed_typed(const igg_field *a, const igg_field *b, const igg_field &lam, double *part, int *blocks,
+                      hipStream_t s)
 {
-    Grid &g = grid();
-    const int nx = (int)lam.size[0], ny = (int)lam.size[1], nz = (int)lam.size[2];
-    const int64_t rows = (int64_t)(ny - 2) * (nz - 2);
-    const int blocks = (int)(rows < RED_BLOCKS ? (rows < 1 ? 1 : rows) : RED_BLOCKS);
-    double *part = loss ? g.red_part : nullptr;
-    if (lam.dtype == IGG_F64)
-        hipLaunchKernelGGL(k_seed<double>, dim3(blocks), dim3(RED_THREADS), 0, s, a ? (const double *)a->data : nullptr,
-                           b ? (const double *)b->data : nullptr, (double *)lam.data, nx, ny, nz, part);
-    else if (lam.dtype == IGG_F32)
-        hipLaunchKernelGGL(k_seed<float>, dim3(blocks), dim3(RED_THREADS), 0, s, a ? (const float *)a->data : nullptr,
-                           b ? (const float *)b->data : nullptr, (float *)lam.data, nx, ny, nz, part);
-    else
-        hipLaunchKernelGGL(k_seed<_Float16>, dim3(blocks), dim3(RED_THREADS), 0, s,
-                           a ? (const _Float16 *)a->data : nullptr, b ? (const _Float16 *)b->data : nullptr,
-                           (_Float16 *)lam.data, nx, ny, nz, part);
-    IGG_HIP(hipGetLastError());
-    if (!loss) return IGG_OK;
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(RED_THREADS), 0, s, (int)IGG_RED_HALF_SQDIFF, blocks,
-                       (const double *)g.red_part, g.red_part + RED_BLOCKS);
+    const RedRegion g = red_region(lam, false, *blocks);
+    hipLaunchKernelGGL(k_seed<S>, dim3(*blocks), dim3(RED_THREADS), 0, s, a ? (const S *)a->data : nullptr,
+                       b ? (const S *)b->data : nullptr, (S *)lam.data, (int)lam.size[2], g, part);
     IGG_HIP(hipGetLastError());
     return IGG_OK;
 }
 
-int read_reduce_result(double *out, hipStream_t s)
+int launch_seed(const igg_field *a, const igg_field *b, const igg_field &lam, int *parts, hipStream_t s)
 {
-    Grid &g = grid();
-    IGG_HIP(hipMemcpyAsync(g.red_host, g.red_part + RED_BLOCKS, sizeof(double), hipMemcpyDeviceToHost, s));
+    double *part = parts ? grid().red_host : nullptr;
+    int blocks = 0;
+    const int rc = lam.dtype == IGG_F64   ? seed_typed<double>(a, b, lam, part, &blocks, s)
+                   : lam.dtype == IGG_F32 ? seed_typed<float>(a, b, lam, part, &blocks, s)
+                                          : seed_typed<_Float16>(a, b, lam, part, &blocks, s);
+    if (parts) *parts = blocks;
+    return rc;
+}
+
+int read_seed_loss(int parts, double *out, hipStream_t s)
+{
     IGG_HIP(hipStreamSynchronize(s));
-    *out = g.red_host[0];
+    *out = combine_host(IGG_RED_HALF_SQDIFF, parts, grid().red_host);
     return IGG_OK;
 }
 
@@ -255,9 +392,12 @@ static int scratch_on_current_device(double **ptr)
 int launch_reduce_noalloc(int op, const igg_field &a, const igg_field *b, double *out_dev, hipStream_t s)
 {
     double *part = nullptr;
-    int rc;
+    int rc, blocks = 0;
     if ((rc = scratch_on_current_device(&part))) return rc;
-    return launch_typed(op, a, b, part, kNoallocScratch, out_dev, s);
+    if ((rc = launch_typed(op, a, b, part, kNoallocScratch, &blocks, s))) return rc;
+    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(RED_THREADS), 0, s, op, blocks, (const double *)part, out_dev);
+    IGG_HIP(hipGetLastError());
+    return IGG_OK;
 }
 
 }  // namespace igg
