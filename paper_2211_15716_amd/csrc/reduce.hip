@@ -2,6 +2,10 @@
 // conservation and dot-product sums).  Values are widened to FP64 before
 // they are combined; rows are dealt to a fixed number of waves and combined
 // in a fixed tree, so a call's bits do not vary between runs.
+#include <string.h>
+
+#include <atomic>
+#include <chrono>
 #include <mutex>
 #include <string>
 #include <type_traits>
@@ -160,7 +164,8 @@ k_reduce(const S *__restrict__ a, const S *__restrict__ b, RedRegion g, double *
                 acc[e] = combine(OP, acc[e], term<S>(OP, va[q][e], TWO ? vb[q][e] : S(0)));
         });
     double v = block_combine(OP, red_lanes<R::N>(OP, acc), sh);
-    if (threadIdx.x == 0) part[blockIdx.x] = v;
+    // (the host may be waiting for it)
+    if (threadIdx.x == 0) __hip_atomic_store(part + blockIdx.x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Combines the n partial results in `part` and writes the value to *result.
@@ -243,14 +248,38 @@ static double combine_host(int op, int n, const double *part)
 }
 
 // The work-groups write their partial results straight to pinned host memory
-// (8 KB) and the host combines them: no second launch and no copy between
-// the reduction and the synchronisation its caller asks for.
+// (8 KB) and the host combines them: no second launch and no copy.  The host
+// watches for them itself for up to 2 ms: the stream's work before them has
+// ended when all have arrived, and a wait for the stream takes about 10 us
+// longer to return.  A slot still holding its mark by then (a long queue, an
+// error, or a field that holds that very NaN) is left to a wait for the stream.
+constexpr uint64_t kRedMark = 0x7ff8c0de5eed0001ull;
+static int wait_parts(const double *part, int n, hipStream_t s)
+{
+    const volatile uint64_t *p = reinterpret_cast<const volatile uint64_t *>(part);
+    const auto end = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+    for (int q = 0; q < n; ++q)
+        for (int spin = 0; p[q] == kRedMark; ++spin)
+            if ((spin & 63) == 63 && std::chrono::steady_clock::now() > end) {
+                IGG_HIP(hipStreamSynchronize(s));
+                return IGG_OK;
+            }
+    std::atomic_thread_fence(std::memory_order_acquire);
+    return IGG_OK;
+}
+static void mark_parts(double *part)
+{
+    for (int q = 0; q < RED_BLOCKS; ++q) memcpy(part + q, &kRedMark, sizeof kRedMark);
+    std::atomic_thread_fence(std::memory_order_release);
+}
+
 int launch_reduce(int op, const igg_field &a, const igg_field *b, double *out, hipStream_t s)
 {
     Grid &g = grid();
     int rc, blocks = 0;
+    mark_parts(g.red_host);
     if ((rc = launch_typed(op, a, b, g.red_host, RED_BLOCKS, &blocks, s))) return rc;
-    IGG_HIP(hipStreamSynchronize(s));
+    if ((rc = wait_parts(g.red_host, blocks, s))) return rc;
     *out = combine_host(op, blocks, g.red_host);
     return IGG_OK;
 }
