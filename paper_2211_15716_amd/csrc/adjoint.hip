@@ -99,9 +99,74 @@ k_adj_boxes(C *__restrict__ lam_n, const C *__restrict__ lp, const C *__restrict
         });
 }
 
+// One thread per column of NZ inner points, 256 consecutive points of a plane
+// per work-group (grids that sit in the caches, as k_step_small).  Bound by
+// the loads' latency and the launch; two points a thread (128^3 FP64 23.4 us,
+// one 26.4, four 24.7) against the box kernel's or the z-march's 33.9; 160^3
+// FP32 29.0 -> 19.9, 352 x 53 x 59 FP64 24.7 -> 16.2.
+struct AdjSmall {
+    int nx, ny, nz;
+    int nbp;  // work-groups per plane
+    XHalo xh;
+    YZImg yz;
+};
+template <typename C, int FORM, int NZ>
+__global__ void __launch_bounds__(256)
+k_adj_small(C *__restrict__ lam_n, const C *__restrict__ lp, const C *__restrict__ Tn, const C *__restrict__ Ci,
+            C *__restrict__ gCi, AdjSmall g, C a, C rx, C ry, C rz, C lamf)
+{
+    const int nx = g.nx, ny = g.ny, nz = g.nz;
+    const uint32_t b = (uint32_t)xcd_remap(blockIdx.x, gridDim.x);
+    const uint32_t bp = b % (uint32_t)g.nbp, bz = b / (uint32_t)g.nbp;
+    const uint32_t q = bp * 256 + threadIdx.x, w = (uint32_t)(nx - 2);
+    const int j = 1 + (int)(q / w), i = 1 + (int)(q % w), k0 = 1 + (int)bz * NZ;
+    if (j > ny - 2) return;
+    const int64_t sy = nx, sz = (int64_t)nx * ny, p0 = i + sy * j + sz * k0;
+    C l[NZ + 2], m[NZ + 2], t[NZ + 2], c[NZ + 2];
+    // (planes past the last inner one read the last ones again)
+#pragma unroll
+    for (int z = 0; z < NZ + 2; ++z) {
+        const int64_t p = p0 + sz * (min(k0 - 1 + z, nz - 1) - k0);
+        l[z] = lp[p];
+        c[z] = Ci[p];
+        t[z] = Tn[p];
+    }
+#pragma unroll
+    for (int z = 0; z < NZ + 2; ++z) m[z] = c[z] * l[z];
+    C mn[NZ][4], tn[NZ][4], gc[NZ];
+#pragma unroll
+    for (int z = 0; z < NZ; ++z) {
+        const int64_t p = p0 + sz * (min(k0 + z, nz - 2) - k0);
+        const int64_t o[4] = {p - 1, p + 1, p - sy, p + sy};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            mn[z][e] = Ci[o[e]] * lp[o[e]];
+            tn[z][e] = Tn[o[e]];
+        }
+        gc[z] = gCi[p];
+    }
+#pragma unroll
+    for (int z = 0; z < NZ; ++z) {
+        const int k = k0 + z;
+        if (k > nz - 2) break;
+        C ln, gg = gc[z];
+        adj_cell<C, FORM>(l[z + 1], m[z + 1], mn[z][0], mn[z][1], mn[z][2], mn[z][3], m[z], m[z + 2], t[z + 1],
+                          tn[z][0], tn[z][1], tn[z][2], tn[z][3], t[z], t[z + 2], a, rx, ry, rz, lamf, ln, gg);
+        const int64_t row = sz * k + sy * j;
+        auto put = [&](int64_t r) {
+            lam_n[r + i] = ln;
+            if (g.xh.on_lo && i == g.xh.lo) lam_n[r + nx - 1 + g.xh.d_lo] = ln;
+            if (g.xh.on_hi && i == g.xh.hi) lam_n[r + g.xh.d_hi] = ln;
+        };
+        put(row);
+        gCi[row + i] = gg;
+        if (g.yz.on) yz_images(g.yz, j, k, [&](int jj, int kk) { put(sz * kk + sy * jj); });
+    }
+}
+
 struct AdjTile {
     Box b;
-    int nx, ny;
+    int nx, ny, nz;
     int xa;
     int ntx, nty;
     int zc;
@@ -202,8 +267,11 @@ k_adj_zmarch(C *__restrict__ lam_n, const C *__restrict__ lp, const C *__restric
     // registers) with 32-bit byte offsets in the plane (the launcher keeps
     // planes below 2 GiB): no 64-bit address registers per lane, which
     // leaves room under the 128-register cap for the deferred products below
+    // (rows of any length: a vector that runs over its row's end reads the
+    // start of the next row, which is not used; the descriptor lets it run
+    // into the next plane, and past the array's end it reads zero)
     const int64_t pb = sxy * (int64_t)sizeof(C);
-    auto rs = [&](const C *A, int k) { return buf_rsrc(A + (int64_t)k * sxy, pb); };
+    auto rs = [&](const C *A, int k) { return buf_rsrc(A + (int64_t)k * sxy, pb + (k < z.nz - 1 ? 16 : 0)); };
     auto ld = [&](const C *A, int k, int64_t c) -> V {
         V v{};
         if (xin) v = buf_load<V, 0>(rs(A, k), (uint32_t)(c * (int64_t)sizeof(C)));
@@ -310,6 +378,13 @@ k_adj_zmarch(C *__restrict__ lam_n, const C *__restrict__ lp, const C *__restric
                 set_el<C, VEC>(lo, q, ln);
                 set_el<C, VEC>(go, q, gg);
             }
+            if constexpr (RY == 1) {
+                // the loads are waited for here: a wait after the stores
+                // would wait for the stores too
+                __asm__ volatile("" : "+v"(cn[r]), "+v"(ln2[r]), "+v"(tn[r]), "+v"(gn[r]));
+                __asm__ volatile("" : "+v"(hc_n[r]), "+v"(hl_n[r]), "+v"(hT_n[r]));
+                __asm__ volatile("" : "+v"(yc_n), "+v"(yl_n), "+v"(yT_n));
+            }
             const int64_t p = (int64_t)k * sxy + col[r];
             if (xin && i >= z.b.i0 && i + VEC <= z.b.i1) {
                 const uint32_t ob = (uint32_t)(col[r] * (int64_t)sizeof(C));
@@ -395,14 +470,16 @@ static int run_zmarch(const AdjArgs &a, const Box &b, hipStream_t s)
     z.b = b;
     z.nx = a.nx;
     z.ny = a.ny;
+    z.nz = a.nz;
     z.xa = (b.i0 / VEC) * VEC;
     z.ntx = (b.i1 - z.xa + TW - 1) / TW;
     z.nty = (b.j1 - b.j0 + TH - 1) / TH;
     int depth = b.k1 - b.k0;
     int zc = env_int("IGG_ADJ_ZCHUNK", 0);
-    // chunks of at most 8 planes: 2% faster than 16 at 256^3 (FP64, 4-row
-    // tiles) and 3% at 512^3
-    if (zc < 1) zc = zchunk_for_groups((int64_t)z.ntx * z.nty, depth, 8);
+    // chunks of at most 8 planes: 3% faster than 16 at 512^3; FP64 in 4-row
+    // tiles 6 (256^3 155.9 us against 160.5 with 8 and 158.5 with 16, 301 x
+    // 257 x 203 160.5 against 164.3)
+    if (zc < 1) zc = zchunk_for_groups((int64_t)z.ntx * z.nty, depth, sizeof(C) == 8 && TH == 4 ? 6 : 8);
     z.zc = zc;
     z.remap = env_int("IGG_ADJ_REMAP", 2);
     // blocks of 4 x-rows of tiles per XCD, so y-neighbour tiles share an
@@ -420,16 +497,6 @@ static int run_zmarch(const AdjArgs &a, const Box &b, hipStream_t s)
     return IGG_OK;
 }
 
-static bool aligned(const void *p, int bytes) { return ((uintptr_t)p % (uintptr_t)bytes) == 0; }
-
-template <typename C, int VEC = 2>
-static bool vec2_ok(const AdjArgs &a)
-{
-    const int vb = VEC * (int)sizeof(C);
-    return a.nx % VEC == 0 && aligned(a.lam_n, vb) && aligned(a.lp, vb) && aligned(a.Tn, vb) &&
-           aligned(a.Ci, vb) && aligned(a.gCi, vb);
-}
-
 // 1 KB tile rows of 4 rows, 256 threads, one row per thread (the two
 // staged fields need many registers), 16-byte loads: FP64 128 points per
 // row (10% faster than 512-byte rows of 16 at 256^3 and 512^3 on MI355X;
@@ -437,8 +504,9 @@ static bool vec2_ok(const AdjArgs &a)
 // in flight moved to the rotation, 16-row tiles of 1024 threads pay at
 // 512^3, see below),
 // FP32 256 points (24% faster than 8-byte loads on 512-byte rows at 512^3
-// and 768^3).  Narrower vectors, then one point per lane, where the row
-// length or alignment does not allow 16-byte loads.  The FP64 kernel is
+// and 768^3).  Rows of any length and alignment are read in vectors (255 x
+// 190 x 131 FP64 77 -> 67 us, FP32 43 -> 36, 301 x 257 x 203 FP64 195 -> 161,
+// against one point per lane).  The FP64 kernel is
 // held to 128 registers, which fits without spills and lets 4 waves share
 // each SIMD instead of 3: the kernel is partly latency-bound, and that made
 // it 11% faster at 256^3 and 5% at 512^3 (unsplit; both forms).
@@ -447,7 +515,6 @@ static int adjoint_inner(int dtype, const AdjArgs &a, const Box &b, hipStream_t 
 {
     if (dtype == IGG_F64)
     {
-        if (!vec2_ok<double>(a)) return run_zmarch<double, 1, 64, 8, 2, FORM>(a, b, s);
         const int waves = env_int("IGG_ADJ_WAVES", 4);
         if (waves != 4) return run_zmarch<double, 2, 64, 4, 1, FORM>(a, b, s);
         // regions of 2^26 points and more: 16-row tiles over 1024 threads
@@ -456,16 +523,38 @@ static int adjoint_inner(int dtype, const AdjArgs &a, const Box &b, hipStream_t 
         if (box_count(b) >= ((int64_t)1 << 26)) return run_zmarch<double, 2, 64, 16, 1, FORM, 4>(a, b, s);
         return run_zmarch<double, 2, 64, 4, 1, FORM, 4>(a, b, s);
     }
-    if (vec2_ok<float, 4>(a)) return run_zmarch<float, 4, 64, 4, 1, FORM>(a, b, s);
-    return vec2_ok<float>(a) ? run_zmarch<float, 2, 64, 8, 1, FORM>(a, b, s)
-                             : run_zmarch<float, 1, 64, 8, 2, FORM>(a, b, s);
+    // 128-point rows where they leave a fifth fewer lanes past the rows' ends
+    // (301 x 257 x 203 117 -> 94 us, 384^3 305 -> 267; where both fit alike
+    // 512^3 600 against 628, 401 x 300 x 250 180 against 193)
+    const int n = b.i1 - b.i0 / 4 * 4, wide = (n + 255) / 256 * 256, half = (n + 127) / 128 * 128;
+    return half * 5 <= wide * 4 ? run_zmarch<float, 2, 64, 4, 1, FORM>(a, b, s)
+                                : run_zmarch<float, 4, 64, 4, 1, FORM>(a, b, s);
+}
+
+template <typename C, int FORM>
+static int run_small(const AdjArgs &a, hipStream_t s)
+{
+    constexpr int NZ = 2;
+    const AdjSmall g{a.nx, a.ny, a.nz, (int)(((int64_t)(a.nx - 2) * (a.ny - 2) + 255) / 256), a.xh, a.yz};
+    const int64_t blocks = (int64_t)g.nbp * ((a.nz - 2 + NZ - 1) / NZ);
+    hipLaunchKernelGGL((k_adj_small<C, FORM, NZ>), dim3((unsigned)blocks), dim3(256), 0, s, (C *)a.lam_n,
+                       (const C *)a.lp, (const C *)a.Tn, (const C *)a.Ci, (C *)a.gCi, g, (C)a.a, (C)a.rx, (C)a.ry,
+                       (C)a.rz, (C)a.lamf);
+    IGG_HIP(hipGetLastError());
+    return IGG_OK;
+}
+
+int launch_adjoint_small(int dtype, const AdjArgs &a, hipStream_t s)
+{
+    if (a.form == 1) return dtype == IGG_F64 ? run_small<double, 1>(a, s) : run_small<float, 1>(a, s);
+    return dtype == IGG_F64 ? run_small<double, 0>(a, s) : run_small<float, 0>(a, s);
 }
 
 int launch_adjoint_inner(int dtype, const AdjArgs &a, const Box &b, hipStream_t s)
 {
     // the z-march kernel addresses a plane with 32-bit offsets (2 GiB at most)
     const int64_t plane = (int64_t)a.nx * a.ny * (dtype == IGG_F64 ? 8 : 4);
-    if (box_count(b) < zmarch_min_points() || plane >= ((int64_t)1 << 31))
+    if (box_count(b) < zmarch_min_points() || plane + 16 >= ((int64_t)1 << 31) || a.nx < 4)
         return launch_adjoint_boxes(dtype, a, &b, 1, s);
     return a.form == 1 ? adjoint_inner<1>(dtype, a, b, s) : adjoint_inner<0>(dtype, a, b, s);
 }

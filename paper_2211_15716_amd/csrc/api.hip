@@ -378,14 +378,15 @@ static int run_split(const int *split, int dtype, HaloLaunch halo, BoundaryLaunc
     return IGG_OK;
 }
 
-// One rank that is its own neighbour in every dimension, with the x
+// One rank, its own neighbour in every periodic dimension, with the x
 // exchange in the stores and the y/z halo filled without send buffers
 // (IGG_SLAB_PACK=2).
 static bool self_halo_ok()
 {
     const Grid &g = grid();
-    return g.nranks == 1 && g.fuse_x && g.slab_pack == 2 && g.periods[0] && g.periods[1] && g.periods[2];
+    return g.nranks == 1 && g.fuse_x && g.slab_pack == 2;
 }
+
 
 // Whether a step of `points` points takes the small-grid kernel: three arrays
 // of at most 96 MiB (160^3 FP64, 98 MB: 28.5 us with either kernel on inputs
@@ -397,6 +398,16 @@ static bool step_is_small(int dtype, int64_t points)
 {
     const int64_t zm = zmarch_min_points();
     return zm == kZmarchMinPoints ? points * 3 * elem_bytes(dtype) <= ((int64_t)96 << 20) : points < zm;
+}
+
+// The same for the adjoint: five arrays of at most 96 MiB (128^3 FP64, 84 MB:
+// 23.4 us against 32.1; 160^3 FP32, 82 MB: 19.9 against 30.3; 200 x 180 x 100
+// FP64, 144 MB: 54.2 against 41.6 on inputs that were not in the caches, 37.6
+// against 42.1 in a loop).
+static bool adjoint_is_small(int dtype, int64_t points)
+{
+    const int64_t zm = zmarch_min_points();
+    return zm == kZmarchMinPoints ? points * 5 * elem_bytes(dtype) <= ((int64_t)96 << 20) : points < zm;
 }
 
 // The step's launch arguments for rank r: its arrays, the fused x exchange
@@ -505,7 +516,7 @@ static int step_ranks(const igg_field *T2, const igg_field *T, const igg_field *
     // dimensions have a period, the edges follow.  Against slabs, halo update
     // and inner region in launches of their own: 256^3 FP64 without periods
     // 83.5 -> 74.7 us, with two 84.6 -> 76.3, unsplit 80.0 -> 73.5.
-    if (P == 1 && g.fuse_x && g.slab_pack == 2 && (g.schedule < 0 || g.schedule == 3)) {
+    if (self_halo_ok() && (g.schedule < 0 || g.schedule == 3)) {
         const Box all{1, g.n[0] - 1, 1, g.n[1] - 1, 1, g.n[2] - 1};
         const int *widths = split ? split : g.ol;
         Split sp;
@@ -527,7 +538,7 @@ static int step_ranks(const igg_field *T2, const igg_field *T, const igg_field *
         pk.direct = 1;
         FusedStep ctx{dtype, args.data(), &pk};
         return run_split(
-            widths, dtype, [&](hipStream_t st) { return launch_step_edges(dtype, args[0], st); },
+            widths, dtype, [&](hipStream_t st) { return launch_step_edges(dtype, T2[0].data, g.n, st); },
             [&](int r, const Split &b, hipStream_t st) { return launch_step_slabs(dtype, args[r], b, &pk, st); },
             [&](int r, const Box &b, hipStream_t st) { return launch_step_inner(dtype, args[r], b, st); }, s, true,
             fused_step, &ctx);
@@ -685,19 +696,27 @@ static int adjoint_step(int form, const igg_field *lam_n, const igg_field *lam_n
     hipStream_t s = (hipStream_t)stream;
     const int halo_dims = g.fuse_x ? 6 : 7;
     Box all{1, g.n[0] - 1, 1, g.n[1] - 1, 1, g.n[2] - 1};
-    if (split && self_halo_ok() && (g.schedule < 0 || g.schedule == 3)) {
-        // one rank, periodic in every dimension: one launch over every inner
-        // point, which also stores the x halo of lam_n and, for every inner
-        // point that is the image of y/z halo points, those points (the
-        // adjoint runs its chain serially anyway, so the boundary has nothing
-        // to overlap)
+    if (self_halo_ok() && (g.schedule < 0 || g.schedule == 3)) {
+        // one rank: one launch over every inner point, which also stores the
+        // x halo of lam_n and, for every inner point that is the image of y/z
+        // halo points, those points (the adjoint runs its chain serially
+        // anyway, so the boundary has nothing to overlap)
         AdjArgs a0 = args[0];
-        a0.yz = YZImg{1, g.ol[1] - 1, g.n[1] - g.ol[1], g.ol[2] - 1, g.n[2] - g.ol[2], g.n[1], g.n[2]};
+        a0.yz = YZImg{1, -1, -1, -1, -1, g.n[1], g.n[2]};
+        if (g.periods[1]) {
+            a0.yz.jl = g.ol[1] - 1;
+            a0.yz.jh = g.n[1] - g.ol[1];
+        }
+        if (g.periods[2]) {
+            a0.yz.kl = g.ol[2] - 1;
+            a0.yz.kh = g.n[2] - g.ol[2];
+        }
         if ((rc = timing_mark(s, 0))) return rc;
-        if ((rc = launch_adjoint_inner(dt_, a0, all, s))) return rc;
+        const bool small = adjoint_is_small(dt_, box_points(all));
+        if ((rc = small ? launch_adjoint_small(dt_, a0, s) : launch_adjoint_inner(dt_, a0, all, s))) return rc;
         if ((rc = timing_mark(s, 0))) return rc;
         if (g.timing) { g.t_launches++; g.t_points += box_points(all); }
-        return IGG_OK;
+        return launch_step_edges(dt_, lam_n[0].data, g.n, s);
     }
     if (!split) {
         for (int r = 0; r < P; ++r) {

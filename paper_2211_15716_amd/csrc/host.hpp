@@ -157,10 +157,10 @@ int launch_step_boundary(int dtype, const StepArgs &a, const Split &sp, hipStrea
 // The step on one rank in one launch, halo update of T2 included, for grids
 // too small for z-march tiles.
 int launch_step_small(int dtype, const StepArgs &a, hipStream_t s);
-// The points of T2's y and z halo planes in the planes of dimensions without
+// The points of a field's y and z halo planes in the planes of dimensions without
 // a period, which the halo update copies but no step computes (nothing to do
 // unless some dimensions have a period and others none).
-int launch_step_edges(int dtype, const StepArgs &a, hipStream_t s);
+int launch_step_edges(int dtype, void *A, const int n[3], hipStream_t s);
 
 // Two steps in one launch, on one rank whose periodic dimensions overlap by
 // 2: T2 = T_{n+2} from T = T_n (valid halo), halo of T2 included; with mid,
@@ -207,7 +207,8 @@ int launch_unpack_self(const igg_field &f, const SlabPack &pk, hipStream_t s);
 unsigned char *halo_send_plane(int r, int f, int side);
 
 // The y and z halo planes of lam_n filled by the adjoint kernels' stores,
-// on one rank that is its own neighbour in every dimension: halo row ny-1
+// on one rank that is its own neighbour in every periodic dimension (jl, jh
+// or kl, kh are -1 where y or z has no period): halo row ny-1
 // is the image of row jl = ol-1, row 0 that of row jh = ny-ol (z likewise,
 // kl and kh), and a point's image has the same x index (its x-halo copies
 // come with the x exchange).  Each point of the four planes has one image
@@ -233,6 +234,9 @@ struct AdjArgs {
 };
 int launch_adjoint_boxes(int dtype, const AdjArgs &a, const Box *b, int nb, hipStream_t s);
 int launch_adjoint_inner(int dtype, const AdjArgs &a, const Box &b, hipStream_t s);
+// Every inner point and the halo its stores fill, for grids that sit in the
+// caches.
+int launch_adjoint_small(int dtype, const AdjArgs &a, hipStream_t s);
 
 // x exchange of the four flux-form fields fused into the flux pass: T2, qy
 // and qz (nx points in x, overlap ol) send column ol-1 to the lower x

@@ -148,11 +148,10 @@ k_step_small(S *__restrict__ T2, const S *__restrict__ T, const S *__restrict__ 
     }
 }
 
-OneGeom geom(const StepArgs &a)
+OneGeom geom(const int n[3])
 {
     const Grid &gr = grid();
     OneGeom g;
-    const int n[3] = {a.nx, a.ny, a.nz};
     for (int d = 0; d < 3; ++d) {
         g.n[d] = n[d];
         g.per[d] = gr.periods[d];
@@ -180,7 +179,8 @@ template <typename S, int NZ>
 int run_small(const StepArgs &a, hipStream_t s)
 {
     using C = compute_t<S>;
-    const OneGeom g = geom(a);
+    const int n[3] = {a.nx, a.ny, a.nz};
+    const OneGeom g = geom(n);
     const int nbp = (int)(((int64_t)(a.nx - 2) * (a.ny - 2) + 255) / 256);
     int64_t blocks = (int64_t)nbp * ((a.nz - 2 + NZ - 1) / NZ);
     OneEdges ed;
@@ -203,13 +203,13 @@ int run_small(const StepArgs &a, hipStream_t s)
 }
 
 template <typename S>
-int run_edges(const StepArgs &a, hipStream_t s)
+int run_edges(void *A, const int n[3], hipStream_t s)
 {
     OneEdges ed;
-    const OneGeom g = geom(a);
+    const OneGeom g = geom(n);
     const int64_t blocks = one_edges(g, 0, 256, ed);
     if (blocks == 0) return IGG_OK;
-    hipLaunchKernelGGL(k_step_edges<S>, dim3((unsigned)blocks), dim3(256), 0, s, (S *)a.T2, g, ed);
+    hipLaunchKernelGGL(k_step_edges<S>, dim3((unsigned)blocks), dim3(256), 0, s, (S *)A, g, ed);
     IGG_HIP(hipGetLastError());
     return IGG_OK;
 }
@@ -231,11 +231,11 @@ int launch_step_small(int dtype, const StepArgs &a, hipStream_t s)
     return small_typed<_Float16>(a, s);
 }
 
-int launch_step_edges(int dtype, const StepArgs &a, hipStream_t s)
+int launch_step_edges(int dtype, void *A, const int n[3], hipStream_t s)
 {
-    if (dtype == IGG_F64) return run_edges<double>(a, s);
-    if (dtype == IGG_F32) return run_edges<float>(a, s);
-    return run_edges<_Float16>(a, s);
+    if (dtype == IGG_F64) return run_edges<double>(A, n, s);
+    if (dtype == IGG_F32) return run_edges<float>(A, n, s);
+    return run_edges<_Float16>(A, n, s);
 }
 
 }  // namespace igg
