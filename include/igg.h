@@ -337,10 +337,11 @@ int diffusion_step_adjoint_ranks(const igg_field *lam_n, const igg_field *lam_np
  * x, the x exchange of all four fields; the values equal a face pass
  * followed by a cell pass.
  *   split  boundary widths as in diffusion_step, each >= overlap + 1 (the
- *          face fields overlap by one more plane in their own dimension);
- *          the y and z slabs are computed first, the halo update of the four
- *          fields follows them on the helper stream beside the inner
- *          region.  NULL = no overlap.
+ *          face fields overlap by one more plane in their own dimension).  On
+ *          one rank every cell is computed in one launch and the halo of the
+ *          four fields in another; otherwise (and with a schedule set) the y
+ *          and z slabs are computed first, and the halo update follows them
+ *          on the helper stream beside the inner region.  NULL = no overlap.
  * Errors: as diffusion_step (IGG_ERR_ARG for a split width below ol+1). */
 int diffusion_flux_step(const igg_field *T2, const igg_field *T, const igg_field *Ci,
                         const igg_field *qx, const igg_field *qy, const igg_field *qz, double lam,

@@ -93,11 +93,62 @@ k_flux_fused_boxes(C *__restrict__ T2, C *__restrict__ qx, C *__restrict__ qy, C
     flux_extra_stores<C>(T2, qx, qy, qz, i, j, k, p, px, py, g, xh, v2, qxl, qxu, qyl, qyu, qzl, qzu);
 }
 
+// One thread per column of NZ inner cells, 256 consecutive cells of a plane per
+// work-group (grids that sit in the caches, as k_step_small).
+template <typename C, int NZ>
+__global__ void __launch_bounds__(256)
+k_flux_small(C *__restrict__ T2, C *__restrict__ qx, C *__restrict__ qy, C *__restrict__ qz, const C *__restrict__ T,
+             const C *__restrict__ Ci, FaceGeom g, FluxXH xh, int nbp, C lam, C dt, C rdx, C rdy, C rdz)
+{
+    const int nx = g.nx, ny = g.ny, nz = g.nz;
+    const uint32_t b = (uint32_t)xcd_remap(blockIdx.x, gridDim.x);
+    const uint32_t bp = b % (uint32_t)nbp, bz = b / (uint32_t)nbp;
+    const uint32_t q = bp * 256 + threadIdx.x, w = (uint32_t)(nx - 2);
+    const int j = 1 + (int)(q / w), i = 1 + (int)(q % w), k0 = 1 + (int)bz * NZ;
+    if (j > ny - 2) return;
+    const int64_t sy = nx, sz = (int64_t)nx * ny, p0 = i + sy * j + sz * k0;
+    C t[NZ + 2], nb[NZ][4], ci[NZ];
+    // (planes past the last inner one read the last ones again)
+#pragma unroll
+    for (int z = 0; z < NZ + 2; ++z) t[z] = T[p0 + sz * (min(k0 - 1 + z, nz - 1) - k0)];
+#pragma unroll
+    for (int z = 0; z < NZ; ++z) {
+        const int64_t p = p0 + sz * (min(k0 + z, nz - 2) - k0);
+        nb[z][0] = T[p - 1];
+        nb[z][1] = T[p + 1];
+        nb[z][2] = T[p - sy];
+        nb[z][3] = T[p + sy];
+        ci[z] = Ci[p];
+    }
+#pragma unroll
+    for (int z = 0; z < NZ; ++z) {
+        const int k = k0 + z;
+        if (k > nz - 2) break;
+        const C t0 = t[z + 1];
+        const C qxl = face_flux<C>(t0, nb[z][0], lam, rdx), qxu = face_flux<C>(nb[z][1], t0, lam, rdx);
+        const C qyl = face_flux<C>(t0, nb[z][2], lam, rdy), qyu = face_flux<C>(nb[z][3], t0, lam, rdy);
+        const C qzl = face_flux<C>(t0, t[z], lam, rdz), qzu = face_flux<C>(t[z + 2], t0, lam, rdz);
+        const C v2 = fma_(-dt * ci[z], flux_div<C>(qxl, qxu, qyl, qyu, qzl, qzu, rdx, rdy, rdz), t0);
+        const int64_t p = i + sy * j + sz * k;
+        const int64_t px = i + (int64_t)(nx + 1) * (j + (int64_t)ny * k);
+        const int64_t py = i + (int64_t)nx * (j + (int64_t)(ny + 1) * k);
+        T2[p] = v2;
+        qx[px] = qxl;
+        qy[py] = qyl;
+        qz[p] = qzl;
+        if (i == nx - 2 || j == ny - 2 || k == nz - 2 ||
+            ((xh.on_lo || xh.on_hi) && (i <= xh.ol || i >= nx - xh.ol)))
+            flux_extra_stores<C>(T2, qx, qy, qz, i, j, k, p, px, py, g, xh, v2, qxl, qxu, qyl, qyu, qzl, qzu);
+    }
+}
+
 template <typename C, int VEC> struct FVec {
     typedef C type __attribute__((ext_vector_type(VEC)));
+    typedef C mem __attribute__((ext_vector_type(VEC), aligned(sizeof(C))));  // rows start at any element
 };
 template <typename C> struct FVec<C, 1> {
     typedef C type;
+    typedef C mem;
 };
 template <typename C, int VEC>
 __device__ __forceinline__ C fel(const typename FVec<C, VEC>::type &v, int q)
@@ -129,13 +180,14 @@ struct FluxTile {
 // kernel's scheme).  T2, qy, qz leave as vectors where the cells of a
 // vector all lie in the box; qx rows are nx+1 long, so its stores are per
 // cell.
-template <typename C, int VEC, int BX, int TY, int RY>
-__global__ void __launch_bounds__(BX *TY)
+template <typename C, int VEC, int BX, int TY, int RY, int WAVES>
+__global__ void __launch_bounds__(BX *TY) __attribute__((amdgpu_waves_per_eu(WAVES)))
 k_flux_fused_zmarch(C *__restrict__ T2, C *__restrict__ qx, C *__restrict__ qy, C *__restrict__ qz,
                     const C *__restrict__ T, const C *__restrict__ Ci, FluxTile z, C lam, C dt, C rdx, C rdy,
                     C rdz)
 {
     using V = typename FVec<C, VEC>::type;
+    using M = typename FVec<C, VEC>::mem;
     constexpr int TW = BX * VEC, TH = TY * RY, LH = TH + 2, LW = TW + 2;
     __shared__ C tile[2][LH][LW];
     const int tx = threadIdx.x % BX, ty = threadIdx.x / BX;
@@ -178,12 +230,17 @@ k_flux_fused_zmarch(C *__restrict__ T2, C *__restrict__ qx, C *__restrict__ qy, 
 
     auto ld = [&](const C *A, int k, int64_t c) -> V {
         V v{};
-        if (xin) v = *reinterpret_cast<const V *>(A + (int64_t)k * sxy + c);
+        if (xin) v = *reinterpret_cast<const M *>(A + (int64_t)k * sxy + c);
         return v;
     };
+    // A vector that runs over its row's end reads the start of the next row,
+    // which is not used.  The plane above the box's last one is read for the
+    // rows computed only; other rows read the row before theirs there, which
+    // keeps such vectors inside the array in the last plane too.
+    auto above = [&](int k, int r) { return col[r] - (k >= z.b.k1 && !crow[r] ? nx : 0); };
     auto ld_nt = [&](const C *A, int k, int64_t c) -> V {
         V v{};
-        if (xin) v = __builtin_nontemporal_load(reinterpret_cast<const V *>(A + (int64_t)k * sxy + c));
+        if (xin) v = __builtin_nontemporal_load(reinterpret_cast<const M *>(A + (int64_t)k * sxy + c));
         return v;
     };
 
@@ -193,7 +250,7 @@ k_flux_fused_zmarch(C *__restrict__ T2, C *__restrict__ qx, C *__restrict__ qy, 
     for (int r = 0; r < RY; ++r) {
         tm[r] = ld(T, kb - 1, col[r]);
         tc[r] = ld(T, kb, col[r]);
-        tp[r] = ld(T, kb + 1, col[r]);
+        tp[r] = ld(T, kb + 1, above(kb + 1, r));
         ci[r] = crow[r] ? ld_nt(Ci, kb, col[r]) : V{};
         hx[r] = own_h ? T[(int64_t)kb * sxy + col[r] - i + xh] : C(0);
     }
@@ -206,7 +263,7 @@ k_flux_fused_zmarch(C *__restrict__ T2, C *__restrict__ qx, C *__restrict__ qy, 
         C hn[RY];
 #pragma unroll
         for (int r = 0; r < RY; ++r) {
-            tn[r] = more ? ld(T, k + 2, col[r]) : V{};
+            tn[r] = more ? ld(T, k + 2, above(k + 2, r)) : V{};
             cn[r] = (more && crow[r]) ? ld_nt(Ci, k + 1, col[r]) : V{};
             hn[r] = (more && own_h) ? T[(int64_t)(k + 1) * sxy + col[r] - i + xh] : C(0);
         }
@@ -250,15 +307,24 @@ k_flux_fused_zmarch(C *__restrict__ T2, C *__restrict__ qx, C *__restrict__ qy, 
                 oyu[q] = qyu;
                 ozu[q] = qzu;
             }
+            if constexpr (RY == 1) {
+                // the loads are waited for here: a wait after the stores
+                // would wait for the stores too
+                __asm__ volatile("" : "+v"(tn[0]), "+v"(cn[0]), "+v"(hn[0]), "+v"(yn));
+            }
             const int j = jr[r];
             const int64_t p = (int64_t)k * sxy + col[r];
             const int64_t px = i + (int64_t)(nx + 1) * (j + (int64_t)ny * k);
             const int64_t py = i + (int64_t)nx * (j + (int64_t)(ny + 1) * k);
             const bool full = i >= z.b.i0 && i + VEC <= z.b.i1;
             if (full) {
-                __builtin_nontemporal_store(o2, reinterpret_cast<V *>(T2 + p));
-                __builtin_nontemporal_store(oy, reinterpret_cast<V *>(qy + py));
-                __builtin_nontemporal_store(oz, reinterpret_cast<V *>(qz + p));
+                __builtin_nontemporal_store(o2, reinterpret_cast<M *>(T2 + p));
+                __builtin_nontemporal_store(oy, reinterpret_cast<M *>(qy + py));
+                __builtin_nontemporal_store(oz, reinterpret_cast<M *>(qz + p));
+                V ox;
+#pragma unroll
+                for (int q = 0; q < VEC; ++q) fset<C, VEC>(ox, q, oxl[q]);
+                *reinterpret_cast<M *>(qx + px) = ox;
             }
 #pragma unroll
             for (int q = 0; q < VEC; ++q) {
@@ -268,8 +334,8 @@ k_flux_fused_zmarch(C *__restrict__ T2, C *__restrict__ qx, C *__restrict__ qy, 
                     T2[p + q] = fel<C, VEC>(o2, q);
                     qy[py + q] = fel<C, VEC>(oy, q);
                     qz[p + q] = fel<C, VEC>(oz, q);
+                    qx[px + q] = oxl[q];
                 }
-                qx[px + q] = oxl[q];
                 if (ii == nx - 2 || j == ny - 2 || k == z.g.nz - 2 ||
                     ((z.xh.on_lo || z.xh.on_hi) && (ii <= z.xh.ol || ii >= nx - z.xh.ol)))
                     flux_extra_stores<C>(T2, qx, qy, qz, ii, j, k, p + q, px + q, py + q, z.g, z.xh,
@@ -309,7 +375,7 @@ static int run_fused_boxes(const FluxArgs &a, const Box *b, int nb, hipStream_t 
     return IGG_OK;
 }
 
-template <typename C, int VEC, int BX, int TY, int RY>
+template <typename C, int VEC, int BX, int TY, int RY, int WAVES = 1>
 static int run_fused_zmarch(const FluxArgs &a, const Box &b, hipStream_t s)
 {
     constexpr int TW = BX * VEC, TH = TY * RY;
@@ -329,19 +395,30 @@ static int run_fused_zmarch(const FluxArgs &a, const Box &b, hipStream_t s)
     z.remap = env_int_flux("IGG_FLUX_REMAP", 2);
     const int64_t blocks = (int64_t)z.ntx * z.nty * ((depth + zc - 1) / zc);
     if (blocks <= 0) return IGG_OK;
-    hipLaunchKernelGGL((k_flux_fused_zmarch<C, VEC, BX, TY, RY>), dim3((unsigned)blocks), dim3(BX * TY), 0, s,
+    hipLaunchKernelGGL((k_flux_fused_zmarch<C, VEC, BX, TY, RY, WAVES>), dim3((unsigned)blocks), dim3(BX * TY), 0, s,
                        (C *)a.T2, (C *)a.qx, (C *)a.qy, (C *)a.qz, (const C *)a.T, (const C *)a.Ci, z, (C)a.lam,
                        (C)a.dt, (C)a.rdx, (C)a.rdy, (C)a.rdz);
     IGG_HIP(hipGetLastError());
     return IGG_OK;
 }
 
-// 16-byte vectors of `vec` cells: rows a whole number of vectors long and
-// every cell-sized array (and qy, qz) 16-byte aligned
-static bool flux_vec_ok(const FluxArgs &a, int vec)
+template <typename C>
+static int run_small(const FluxArgs &a, hipStream_t s)
 {
-    auto al = [](const void *p) { return ((uintptr_t)p % 16) == 0; };
-    return a.nx % vec == 0 && al(a.T) && al(a.T2) && al(a.Ci) && al(a.qy) && al(a.qz);
+    constexpr int NZ = 2;
+    const FaceGeom g{a.nx, a.ny, a.nz};
+    const int nbp = (int)(((int64_t)(a.nx - 2) * (a.ny - 2) + 255) / 256);
+    const int64_t blocks = (int64_t)nbp * ((a.nz - 2 + NZ - 1) / NZ);
+    hipLaunchKernelGGL((k_flux_small<C, NZ>), dim3((unsigned)blocks), dim3(256), 0, s, (C *)a.T2, (C *)a.qx,
+                       (C *)a.qy, (C *)a.qz, (const C *)a.T, (const C *)a.Ci, g, a.xh, nbp, (C)a.lam, (C)a.dt,
+                       (C)a.rdx, (C)a.rdy, (C)a.rdz);
+    IGG_HIP(hipGetLastError());
+    return IGG_OK;
+}
+
+int launch_flux_small(int dtype, const FluxArgs &a, hipStream_t s)
+{
+    return dtype == IGG_F64 ? run_small<double>(a, s) : run_small<float>(a, s);
 }
 
 int launch_flux_boxes(int dtype, const FluxArgs &a, const Box *b, int nb, hipStream_t s)
@@ -349,17 +426,21 @@ int launch_flux_boxes(int dtype, const FluxArgs &a, const Box *b, int nb, hipStr
     return dtype == IGG_F64 ? run_fused_boxes<double>(a, b, nb, s) : run_fused_boxes<float>(a, b, nb, s);
 }
 
-// The inner region: z-march tiles of 1 KB rows (128 FP64 or 256 FP32 cells)
-// where rows allow 16-byte vectors, else one cell per lane; regions below
-// zmarch_min_points() take the box kernel.
+// The inner region: z-march tiles of 1 KB rows (128 FP64 or 256 FP32 cells),
+// one row per thread: two rows per thread (FP32 180 registers against 133)
+// were 3-12% slower (768^3 FP32 2147 us against 2093, 452 x 360 x 440 FP64 772
+// against 724; FP64 in 8 rows, 4 rows 740).  FP32 takes 128-cell rows where
+// they leave a fifth fewer lanes past the rows' ends (384^3 334 -> 289 us,
+// 301 x 257 x 203 122 -> 97).  Rows of any length are read and written in
+// vectors (255 x 190 x 131 FP32 52 -> 44 with the rows per thread).  Regions
+// below zmarch_min_points() take the box kernel.
 int launch_flux_inner(int dtype, const FluxArgs &a, const Box &b, hipStream_t s)
 {
-    if (box_count(b) < zmarch_min_points()) return launch_flux_boxes(dtype, a, &b, 1, s);
-    if (dtype == IGG_F64)
-        return flux_vec_ok(a, 2) ? run_fused_zmarch<double, 2, 64, 4, 2>(a, b, s)
-                                  : run_fused_zmarch<double, 1, 64, 4, 2>(a, b, s);
-    return flux_vec_ok(a, 4) ? run_fused_zmarch<float, 4, 64, 4, 2>(a, b, s)
-                              : run_fused_zmarch<float, 1, 64, 4, 2>(a, b, s);
+    if (box_count(b) < zmarch_min_points() || a.nx < 4) return launch_flux_boxes(dtype, a, &b, 1, s);
+    if (dtype == IGG_F64) return run_fused_zmarch<double, 2, 64, 8, 1>(a, b, s);
+    const int n = b.i1 - b.i0 / 4 * 4, wide = (n + 255) / 256 * 256, half = (n + 127) / 128 * 128;
+    return half * 5 <= wide * 4 ? run_fused_zmarch<float, 2, 64, 4, 1>(a, b, s)
+                                : run_fused_zmarch<float, 4, 64, 4, 1>(a, b, s);
 }
 
 }  // namespace igg

@@ -264,6 +264,8 @@ struct FluxArgs {
 // one thread per cell, or z-march tiles for a large region.
 int launch_flux_boxes(int dtype, const FluxArgs &a, const Box *b, int nb, hipStream_t s);
 int launch_flux_inner(int dtype, const FluxArgs &a, const Box &b, hipStream_t s);
+// Every inner cell, for grids that sit in the caches.
+int launch_flux_small(int dtype, const FluxArgs &a, hipStream_t s);
 
 
 int launch_reduce(int op, const igg_field &a, const igg_field *b, double *out, hipStream_t s);
