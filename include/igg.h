@@ -212,9 +212,9 @@ int igg_finalize_global_grid(void);
  *               `stream`, whose first work-groups compute the slabs and
  *               store the y and z halo planes of T2 as they go (with
  *               IGG_SLAB_PACK=1 and every dimension periodic they fill send
- *               buffers that one copy then unpacks).  Fields of at most 96
- *               MiB in three arrays take one launch of a kernel that needs
- *               no slabs.
+ *               buffers that one copy then unpacks).  Fields of at most 88
+ *               MiB in three arrays (FP16: 24) take one launch of a kernel
+ *               that needs no slabs.
  *          Default: 3 where it applies; otherwise 1 for inner regions of
  *          2^21 points and more in FP64/FP32, 2 for smaller ones and for
  *          FP16.

@@ -389,15 +389,19 @@ static bool self_halo_ok()
 
 
 // Whether a step of `points` points takes the small-grid kernel: three arrays
-// of at most 96 MiB (160^3 FP64, 98 MB: 28.5 us with either kernel on inputs
-// that were not in the caches, 20.7 against 29.2 in a time loop; 155 x 333 x
-// 90 FP64, 111 MB: 33.5 against 30.8 and 24.3 against 32.7; 256^3 FP32, 201
-// MB: 61 against 41 and 38.8 against 46.7), or the points that
+// of at most 88 MiB (200 x 180 x 100 FP64, 82 MiB: 22.2 us against 24.5; 400 x
+// 100 x 100 FP64, 92 MiB: 27.1 against 25.6; 256^3 FP32, 201 MB: 61 against 41
+// on inputs that were not in the caches, 38.8 against 46.7 in a time loop); in
+// FP16, whose points cost as many instructions in half the bytes, 24 MiB (200
+// x 180 x 100, 21 MiB: 14.0 against 16.6 with stochastic rounding, 13.0
+// against 12.8 without; 180 x 160 x 200, 33 MiB: 18.2 against 19.8 and 14.7
+// against 14.0; 256^3: 45 against 28.7).  Or the points that
 // IGG_ZMARCH_MIN_POINTS asks for.
 static bool step_is_small(int dtype, int64_t points)
 {
     const int64_t zm = zmarch_min_points();
-    return zm == kZmarchMinPoints ? points * 3 * elem_bytes(dtype) <= ((int64_t)96 << 20) : points < zm;
+    if (zm != kZmarchMinPoints) return points < zm;
+    return points * 3 * elem_bytes(dtype) <= ((int64_t)(dtype == IGG_F16 ? 24 : 88) << 20);
 }
 
 // The same for the adjoint: five arrays of at most 96 MiB (128^3 FP64, 84 MB:

@@ -53,8 +53,8 @@ def test_one_launch_equals_the_chain(n, periods, zmin, monkeypatch):
 
 def test_small_and_marching_kernels_agree_at_the_rule():
     """The bytes at which the small-grid kernel hands over to the z-march
-    (96 MiB in three arrays): both sides of the line, both kernels."""
-    for n in ((160, 160, 160), (165, 160, 160)):
+    (88 MiB in three arrays): both sides of the line, both kernels."""
+    for n in ((150, 160, 160), (165, 160, 160)):
         say("rule", n)
         d = [1.0 / (m - 1) for m in n]
         T = torch.rand(n[::-1], device="cuda", dtype=torch.float64) + 1.0
