@@ -92,6 +92,14 @@ int check_field(const igg_field *f, const char *name, bool grid_sized)
     return IGG_OK;
 }
 
+// A field of rank r, named name[r] where there are several ranks (names are
+// only put together for a message).
+static int check_rank_field(const igg_field *f, const char *name, int r, bool grid_sized = true)
+{
+    if (grid().nranks == 1) return check_field(f, name, grid_sized);
+    return check_field(f, (std::string(name) + "[" + std::to_string(r) + "]").c_str(), grid_sized);
+}
+
 static int check_finite_pos(double v, const char *name, bool allow_zero)
 {
     if (!isfinite(v) || v < 0.0 || (!allow_zero && v == 0.0))
@@ -476,10 +484,9 @@ static int check_step(const igg_field *T2, const igg_field *T, const igg_field *
     int rc;
     const int P = g.nranks;
     for (int r = 0; r < P; ++r) {
-        const std::string sfx = P > 1 ? "[" + std::to_string(r) + "]" : "";
-        if ((rc = check_field(&T2[r], ("T2" + sfx).c_str(), true))) return rc;
-        if ((rc = check_field(&T[r], ("T" + sfx).c_str(), true))) return rc;
-        if ((rc = check_field(&Ci[r], ("Ci" + sfx).c_str(), true))) return rc;
+        if ((rc = check_rank_field(&T2[r], "T2", r))) return rc;
+        if ((rc = check_rank_field(&T[r], "T", r))) return rc;
+        if ((rc = check_rank_field(&Ci[r], "Ci", r))) return rc;
         if (T2[r].dtype != T[0].dtype || T[r].dtype != T[0].dtype || Ci[r].dtype != T[0].dtype)
             return fail(IGG_ERR_DTYPE, "T2, T and Ci must share one dtype");
     }
@@ -662,12 +669,11 @@ static int adjoint_step(int form, const igg_field *lam_n, const igg_field *lam_n
     if (!lam_n || !lam_np1 || !T_n || !Ci || !gCi) return fail(IGG_ERR_ARG, "null field");
     const int dt_ = lam_n[0].dtype;
     for (int r = 0; r < P; ++r) {
-        const std::string sfx = P > 1 ? "[" + std::to_string(r) + "]" : "";
-        if ((rc = check_field(&lam_n[r], ("lam_n" + sfx).c_str(), true))) return rc;
-        if ((rc = check_field(&lam_np1[r], ("lam_np1" + sfx).c_str(), true))) return rc;
-        if ((rc = check_field(&T_n[r], ("T_n" + sfx).c_str(), true))) return rc;
-        if ((rc = check_field(&Ci[r], ("Ci" + sfx).c_str(), true))) return rc;
-        if ((rc = check_field(&gCi[r], ("gCi" + sfx).c_str(), true))) return rc;
+        if ((rc = check_rank_field(&lam_n[r], "lam_n", r))) return rc;
+        if ((rc = check_rank_field(&lam_np1[r], "lam_np1", r))) return rc;
+        if ((rc = check_rank_field(&T_n[r], "T_n", r))) return rc;
+        if ((rc = check_rank_field(&Ci[r], "Ci", r))) return rc;
+        if ((rc = check_rank_field(&gCi[r], "gCi", r))) return rc;
         if (lam_n[r].dtype != dt_ || lam_np1[r].dtype != dt_ || T_n[r].dtype != dt_ || Ci[r].dtype != dt_ ||
             gCi[r].dtype != dt_)
             return fail(IGG_ERR_DTYPE, "adjoint fields must share one dtype");
@@ -746,14 +752,14 @@ static int adjoint_step(int form, const igg_field *lam_n, const igg_field *lam_n
         [&](int r, const Box &b, hipStream_t st) { return launch_adjoint_inner(dt_, args[r], b, st); }, s, false);
 }
 
-static int check_face(const igg_field *q, const char *name, int dim)
+static int check_face(const igg_field *q, const char *name, int dim, int r)
 {
     Grid &g = grid();
     int rc;
-    if ((rc = check_field(q, name, false))) return rc;
+    if ((rc = check_rank_field(q, name, r, false))) return rc;
     for (int d = 0; d < 3; ++d)
         if (q->size[d] != g.n[d] + (d == dim ? 1 : 0))
-            return fail(IGG_ERR_SIZE, std::string(name) + " must have n+1 points in its own dimension "
+            return fail(IGG_ERR_SIZE, std::string(name) + (g.nranks > 1 ? "[" + std::to_string(r) + "]" : "") + " must have n+1 points in its own dimension "
                                                           "and n in the others");
     return IGG_OK;
 }
@@ -771,13 +777,12 @@ static int flux_step_ranks(const igg_field *T2, const igg_field *T, const igg_fi
     if (!T2 || !T || !Ci || !qx || !qy || !qz) return fail(IGG_ERR_ARG, "null field");
     const int ty = T[0].dtype;
     for (int r = 0; r < P; ++r) {
-        const std::string sfx = P > 1 ? "[" + std::to_string(r) + "]" : "";
-        if ((rc = check_field(&T2[r], ("T2" + sfx).c_str(), true))) return rc;
-        if ((rc = check_field(&T[r], ("T" + sfx).c_str(), true))) return rc;
-        if ((rc = check_field(&Ci[r], ("Ci" + sfx).c_str(), true))) return rc;
-        if ((rc = check_face(&qx[r], ("qx" + sfx).c_str(), 0))) return rc;
-        if ((rc = check_face(&qy[r], ("qy" + sfx).c_str(), 1))) return rc;
-        if ((rc = check_face(&qz[r], ("qz" + sfx).c_str(), 2))) return rc;
+        if ((rc = check_rank_field(&T2[r], "T2", r))) return rc;
+        if ((rc = check_rank_field(&T[r], "T", r))) return rc;
+        if ((rc = check_rank_field(&Ci[r], "Ci", r))) return rc;
+        if ((rc = check_face(&qx[r], "qx", 0, r))) return rc;
+        if ((rc = check_face(&qy[r], "qy", 1, r))) return rc;
+        if ((rc = check_face(&qz[r], "qz", 2, r))) return rc;
         for (const igg_field *f : {&T2[r], &T[r], &Ci[r], &qx[r], &qy[r], &qz[r]})
             if (f->dtype != ty) return fail(IGG_ERR_DTYPE, "flux-form fields must share one dtype");
     }

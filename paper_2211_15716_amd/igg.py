@@ -10,6 +10,7 @@ The library is loaded on first use; if it is missing, every call raises
 binds to the HIP runtime torch has loaded.
 """
 import ctypes
+import functools
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -59,17 +60,21 @@ _INT3 = ctypes.c_int * 3
 _PI = ctypes.POINTER(ctypes.c_int)
 _PF = ctypes.POINTER(Field)
 _lib_handle = None
+_codes = {}  # torch dtype -> igg dtype
+_torch = None
 
 
 def load():
     """Load the HIP library (raises if it has not been built)."""
-    global _lib_handle
+    global _lib_handle, _torch
     if _lib_handle is not None:
         return _lib_handle
     if not os.path.exists(LIB_PATH):
         raise RuntimeError(f"HIP library not built: {LIB_PATH} is missing "
                            "(run __graft_entry__.build() or paper_2211_15716_amd/build.py)")
-    import torch  # noqa: F401  -- binds the library to torch's HIP runtime
+    import torch  # binds the library to torch's HIP runtime
+    _torch = torch
+    _codes.update({torch.float64: IGG_F64, torch.float32: IGG_F32, torch.float16: IGG_F16})
     lib = ctypes.CDLL(LIB_PATH)
     d, vp, i64p = ctypes.c_double, ctypes.c_void_p, ctypes.POINTER(ctypes.c_int64)
     lib.igg_init_global_grid.argtypes = [ctypes.c_int] * 3 + [_PI, _PI, _PI, _PI]
@@ -115,34 +120,48 @@ def _check(rc):
 
 
 # ------------------------------------------------------------------ marshalling
+# (a step of a small grid takes the GPU less time than its arguments took
+# here: nothing is looked up or built twice)
 def _dtype_code(t):
-    import torch
-    m = {torch.float64: IGG_F64, torch.float32: IGG_F32, torch.float16: IGG_F16}
-    if t.dtype not in m:
+    if not _codes:
+        load()
+    code = _codes.get(t.dtype)
+    if code is None:
         raise TypeError(f"unsupported dtype {t.dtype}")
-    return m[t.dtype]
+    return code
 
 
 def field(t):
     """igg_field of a contiguous (nz, ny, nx) device tensor."""
-    if t.dim() != 3:
+    shape = t.shape
+    if len(shape) != 3:
         raise ValueError("fields are 3-D tensors of shape (nz, ny, nx)")
     if not t.is_cuda:
         raise ValueError("fields must live on the HIP device")
     if not t.is_contiguous():
         raise ValueError("fields must be contiguous")
-    nz, ny, nx = t.shape
-    return Field(t.data_ptr(), _dtype_code(t), 0, (ctypes.c_int64 * 3)(nx, ny, nz))
+    return Field(t.data_ptr(), _codes.get(t.dtype) if _codes and t.dtype in _codes else _dtype_code(t), 0, shape[::-1])
 
 
 def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _torch is None:
+        load()
+    c = _torch._C
+    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+
+
+@functools.lru_cache(maxsize=64)
+def _int3_of(a, b, c):
+    return _INT3(a, b, c)
 
 
 def _int3(v):
-    return None if v is None else _INT3(*[int(x) for x in v])
+    if v is None:
+        return None
+    v = [int(x) for x in v]
+    return _int3_of(*v) if len(v) == 3 else _INT3(*v)
 
 
 # ------------------------------------------------------------------ grid
