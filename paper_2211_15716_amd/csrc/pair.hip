@@ -72,26 +72,31 @@ __device__ __forceinline__ int wrap(int c, int n, int per)
 // the block and one layer around it go to LDS, each from global loads of its
 // seven T points (the grid sits in the caches), then the block is computed
 // from LDS.  Bound by its instructions, the chain of its loads and the launch:
-// 32^3 FP64 3.4 us for two steps against 16 for two single steps of two
-// launches each, 96 x 80 x 64 9.2 against 27, 128^3 22 against 44.  Slower: a
-// T tile in LDS too (its own index arithmetic; 17 and 61 us at the last two
-// sizes with a rolled image loop), and the loads of three points at a time
-// issued together (56 registers instead of 30; 10.0 and 24.6).
+// 1024 threads for the fewest points in turn per thread, 32-bit byte offsets
+// (arrays below 2^31 bytes).  Per step in a time loop: 32^3 FP64 1.7 us
+// against 3.2 for a launch per step, 96 x 80 x 64 3.5 against 5.1, 128^3 9.8
+// against 12.1, FP32 6.9 against 7.5.  Slower: 256 threads and blocks of 16 x
+// 4 x 4 (96 x 80 x 64 4.4), a T tile in LDS too (its own index arithmetic),
+// and the loads of three points at a time issued together.
 template <typename S, int BX, int BY, int BZ, int SR, int MID>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
 k_step2_block(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T, const S *__restrict__ Ci, PairGeom g,
               int nbx, int nby, PairCoef<compute_t<S>> cf, uint32_t key1, uint32_t key2, SrOrigin so)
 {
     using C = compute_t<S>;
-    constexpr int UX = BX + 2, UY = BY + 2, UZ = BZ + 2, NU = UX * UY * UZ, NO = BX * BY * BZ;
+    constexpr int UX = BX + 2, UY = BY + 2, UZ = BZ + 2, NU = UX * UY * UZ, NO = BX * BY * BZ, NT = 1024;
+    constexpr uint32_t E = sizeof(S);
     __shared__ C u[UZ][UY][UX];
-    const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
-    const int x0 = 1 + (int)(b % nbx) * BX, y0 = 1 + (int)(b / nbx % nby) * BY, z0 = 1 + (int)(b / nbx / nby) * BZ;
+    const int b = (int)xcd_remap(blockIdx.x, gridDim.x);
+    const int x0 = 1 + b % nbx * BX, y0 = 1 + b / nbx % nby * BY, z0 = 1 + b / nbx / nby * BZ;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-    const int64_t sy = nx, sz = (int64_t)nx * ny;
+    const uint32_t ey = (uint32_t)nx * E, ez = ey * (uint32_t)ny;
+    auto ld = [](const S *A, uint32_t o) -> C {
+        return widen<C>(*reinterpret_cast<const S *>(reinterpret_cast<const char *>(A) + o));
+    };
 #pragma unroll
-    for (int t = 0; t < (NU + 255) / 256; ++t) {
-        const int q = t * 256 + threadIdx.x;
+    for (int t = 0; t < (NU + NT - 1) / NT; ++t) {
+        const int q = t * NT + threadIdx.x;
         const int ux = q % UX, uy = q / UX % UY, uz = q / (UX * UY);
         const int x = x0 - 1 + ux, y = y0 - 1 + uy, z = z0 - 1 + uz;
         // edges and corners of the layer are nobody's neighbours
@@ -100,13 +105,12 @@ k_step2_block(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T,
         const bool hx = x == 0 || x == nx - 1, hy = y == 0 || y == ny - 1, hz = z == 0 || z == nz - 1;
         C v;
         if ((hx && !g.per[0]) || (hy && !g.per[1]) || (hz && !g.per[2])) {
-            v = widen<C>(T[x + sy * y + sz * z]);
+            v = ld(T, (uint32_t)x * E + ey * (uint32_t)y + ez * (uint32_t)z);
         } else {
             const int xi = hx ? wrap(x, nx, 1) : x, yi = hy ? wrap(y, ny, 1) : y, zi = hz ? wrap(z, nz, 1) : z;
-            const int64_t p = xi + sy * yi + sz * zi;
-            const C o = diffuse<C>(widen<C>(T[p]), widen<C>(T[p - 1]), widen<C>(T[p + 1]), widen<C>(T[p - sy]),
-                                   widen<C>(T[p + sy]), widen<C>(T[p - sz]), widen<C>(T[p + sz]), widen<C>(Ci[p]),
-                                   cf.a, cf.rx, cf.ry, cf.rz);
+            const uint32_t p = (uint32_t)xi * E + ey * (uint32_t)yi + ez * (uint32_t)zi;
+            const C o = diffuse<C>(ld(T, p), ld(T, p - E), ld(T, p + E), ld(T, p - ey), ld(T, p + ey), ld(T, p - ez),
+                                   ld(T, p + ez), ld(Ci, p), cf.a, cf.rx, cf.ry, cf.rz);
             uint32_t r = 0;
             if (SR) r = sr_point_bits(sr_plane_key(key1, zi, so), xi, yi, so);
             const S s = Store<S>::put(o, r, SR);
@@ -118,15 +122,15 @@ k_step2_block(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T,
     }
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < NO / 256; ++t) {
-        const int q = t * 256 + threadIdx.x;
+    for (int t = 0; t < NO / NT; ++t) {
+        const int q = t * NT + threadIdx.x;
         const int ux = 1 + q % BX, uy = 1 + q / BX % BY, uz = 1 + q / (BX * BY);
         const int x = x0 - 1 + ux, y = y0 - 1 + uy, z = z0 - 1 + uz;
         if (x > nx - 2 || y > ny - 2 || z > nz - 2) continue;
-        const int64_t p = x + sy * y + sz * z;
         const C o = diffuse<C>(u[uz][uy][ux], u[uz][uy][ux - 1], u[uz][uy][ux + 1], u[uz][uy - 1][ux],
-                               u[uz][uy + 1][ux], u[uz - 1][uy][ux], u[uz + 1][uy][ux], widen<C>(Ci[p]), cf.a, cf.rx,
-                               cf.ry, cf.rz);
+                               u[uz][uy + 1][ux], u[uz - 1][uy][ux], u[uz + 1][uy][ux],
+                               ld(Ci, (uint32_t)x * E + ey * (uint32_t)y + ez * (uint32_t)z), cf.a, cf.rx, cf.ry,
+                               cf.rz);
         uint32_t r = 0;
         if (SR) r = sr_point_bits(sr_plane_key(key2, z, so), x, y, so);
         pair_store(g, x, y, z, out, Store<S>::put(o, r, SR));
@@ -394,7 +398,7 @@ int run_block(const StepPairArgs &a, hipStream_t s)
     const PairCoef<C> cf{(C)a.a, (C)a.rx, (C)a.ry, (C)a.rz};
     const dim3 grd((unsigned)((int64_t)nbx * nby * nbz));
     auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, grd, dim3(256), 0, s, (S *)a.T2, (S *)a.mid, (const S *)a.T, (const S *)a.Ci, g, nbx,
+        hipLaunchKernelGGL(kern, grd, dim3(1024), 0, s, (S *)a.T2, (S *)a.mid, (const S *)a.T, (const S *)a.Ci, g, nbx,
                            nby, cf, a.key1, a.key2, a.so);
     };
     if constexpr (sizeof(S) == 2) {
@@ -498,15 +502,15 @@ bool step_pair_pays(int dtype, const int n[3])
     return dtype != IGG_F16 && n[0] >= 16 && (int64_t)n[0] * n[1] * elem_bytes(dtype) < ((int64_t)1 << 31);
 }
 
-// Blocks of 16 x 4 x 4 points below 2^20 points, for more work-groups (32^3
-// FP64: 4 us a launch against 9 with 16 x 8 x 8; 300 x 70 x 50: 14.4 against
-// 16), 16 x 8 x 8 above, which recompute less of u (128^3: 22.9 against 25.4;
-// the four before the stores tested for halo images once).
+// Blocks of 16 x 8 x 8 points below 2^20 points, for more work-groups (32^3
+// FP64 1.7 us a step against 2.9 with 32 x 8 x 8; 300 x 70 x 50 6.1 against
+// 7.2), 32 x 8 x 8 above, which recompute less of u (128^3 9.8 against 10.4,
+// FP32 6.9 against 8.3).
 template <typename S>
 static int pair_blocks(const StepPairArgs &a, hipStream_t s)
 {
     const int64_t pts = (int64_t)(a.nx - 2) * (a.ny - 2) * (a.nz - 2);
-    return pts < ((int64_t)1 << 20) ? run_block<S, 16, 4, 4>(a, s) : run_block<S, 16, 8, 8>(a, s);
+    return pts < ((int64_t)1 << 20) ? run_block<S, 16, 8, 8>(a, s) : run_block<S, 32, 8, 8>(a, s);
 }
 
 int launch_step_pair(int dtype, const StepPairArgs &a, hipStream_t s)
