@@ -253,9 +253,11 @@ int diffusion_step_ranks(const igg_field *T2, const igg_field *T, const igg_fiel
  * schedule, steps between the first and the last run in pairs of one launch
  * (the same bits, about half the memory traffic; FP16 below 2^21 points
  * only); both buffers end up as single steps leave them.
- *   use_graph  0: every step is launched directly.  1: up to 16 launches of
- *          the loop are captured once into a HIP graph on a library stream
- *          and replayed on `stream`; the steps left over run directly.  The graph is kept for later calls with identical
+ *   use_graph  0: every step is launched directly.  1: from the second
+ *          call in a row with the same arguments on, up to 16 launches of the
+ *          loop are captured once into a HIP graph on a library stream and
+ *          replayed on `stream`; the steps left over, and a first call, run
+ *          directly.  The graph is kept for later calls with identical
  *          arguments (and pair count) and rebuilt when any differs.  For
  *          grids small enough that launch latency dominates.  Stochastic
  *          rounding needs a new counter every step, so it refuses
