@@ -109,6 +109,8 @@ struct AdjSmall {
     int nbp;  // work-groups per plane
     XHalo xh;
     YZImg yz;
+    int main;  // work-groups of the points; the rest copy lam_n's edges
+    EdgeLines ed;
 };
 template <typename C, int FORM, int NZ>
 __global__ void __launch_bounds__(256)
@@ -116,7 +118,12 @@ k_adj_small(C *__restrict__ lam_n, const C *__restrict__ lp, const C *__restrict
             C *__restrict__ gCi, AdjSmall g, C a, C rx, C ry, C rz, C lamf)
 {
     const int nx = g.nx, ny = g.ny, nz = g.nz;
-    const uint32_t b = (uint32_t)xcd_remap(blockIdx.x, gridDim.x);
+    if ((int)blockIdx.x >= g.main) {
+        const int e = ((int)blockIdx.x - g.main) * 256 + threadIdx.x;
+        if (e < g.ed.total) edge_point(lam_n, g.ed, e);
+        return;
+    }
+    const uint32_t b = (uint32_t)xcd_remap(blockIdx.x, g.main);
     const uint32_t bp = b % (uint32_t)g.nbp, bz = b / (uint32_t)g.nbp;
     const uint32_t q = bp * 256 + threadIdx.x, w = (uint32_t)(nx - 2);
     const int j = 1 + (int)(q / w), i = 1 + (int)(q % w), k0 = 1 + (int)bz * NZ;
@@ -174,6 +181,8 @@ struct AdjTile {
     int rblock;  // mode 2: x-rows of tiles per block dealt to one XCD
     XHalo xh;
     YZImg yz;
+    int main;  // work-groups of the tiles; the rest copy lam_n's edges
+    EdgeLines ed;
 };
 
 template <typename C, int VEC> struct AVec {
@@ -227,9 +236,14 @@ k_adj_zmarch(C *__restrict__ lam_n, const C *__restrict__ lp, const C *__restric
     __shared__ C smu[2][LH][LW];
     __shared__ C sT[2][LH][LW];
     const int tx = threadIdx.x % BX, ty = threadIdx.x / BX;
+    if ((int)blockIdx.x >= z.main) {
+        const int e = ((int)blockIdx.x - z.main) * (BX * TY) + threadIdx.x;
+        if (e < z.ed.total) edge_point(lam_n, z.ed, e);
+        return;
+    }
     int64_t g = blockIdx.x;
     if (z.remap == 2) {  // blocks of rblock x-rows of tiles dealt to the XCDs in turn
-        const int64_t ntx0 = z.ntx, B = z.rblock, P = gridDim.x / ntx0, P8 = P / (8 * B) * (8 * B);
+        const int64_t ntx0 = z.ntx, B = z.rblock, P = z.main / ntx0, P8 = P / (8 * B) * (8 * B);
         if (g < ntx0 * P8) {
             const int64_t x = g % 8, slot = g / 8, q = slot / ntx0;
             g = slot % ntx0 + ntx0 * (((q / B) * 8 + x) * B + q % B);
@@ -490,6 +504,9 @@ static int run_zmarch(const AdjArgs &a, const Box &b, hipStream_t s)
     z.yz = a.yz;
     int64_t blocks = (int64_t)z.ntx * z.nty * ((depth + zc - 1) / zc);
     if (blocks == 0) return IGG_OK;
+    z.main = (int)blocks;
+    z.ed = a.ed;
+    blocks += (a.ed.total + BX * TY - 1) / (BX * TY);
     hipLaunchKernelGGL((k_adj_zmarch<C, VEC, BX, TY, RY, FORM, WAVES>), dim3((unsigned)blocks), dim3(BX * TY), 0, s,
                        (C *)a.lam_n, (const C *)a.lp, (const C *)a.Tn, (const C *)a.Ci, (C *)a.gCi, z,
                        (C)a.a, (C)a.rx, (C)a.ry, (C)a.rz, (C)a.lamf);
@@ -535,8 +552,9 @@ template <typename C, int FORM>
 static int run_small(const AdjArgs &a, hipStream_t s)
 {
     constexpr int NZ = 2;
-    const AdjSmall g{a.nx, a.ny, a.nz, (int)(((int64_t)(a.nx - 2) * (a.ny - 2) + 255) / 256), a.xh, a.yz};
-    const int64_t blocks = (int64_t)g.nbp * ((a.nz - 2 + NZ - 1) / NZ);
+    AdjSmall g{a.nx, a.ny, a.nz, (int)(((int64_t)(a.nx - 2) * (a.ny - 2) + 255) / 256), a.xh, a.yz, 0, a.ed};
+    g.main = g.nbp * ((a.nz - 2 + NZ - 1) / NZ);
+    const int64_t blocks = (int64_t)g.main + (a.ed.total + 255) / 256;
     hipLaunchKernelGGL((k_adj_small<C, FORM, NZ>), dim3((unsigned)blocks), dim3(256), 0, s, (C *)a.lam_n,
                        (const C *)a.lp, (const C *)a.Tn, (const C *)a.Ci, (C *)a.gCi, g, (C)a.a, (C)a.rx, (C)a.ry,
                        (C)a.rz, (C)a.lamf);
@@ -550,12 +568,34 @@ int launch_adjoint_small(int dtype, const AdjArgs &a, hipStream_t s)
     return dtype == IGG_F64 ? run_small<double, 0>(a, s) : run_small<float, 0>(a, s);
 }
 
+// The edges alone, after launches whose kernel does not copy them.
+template <typename S>
+__global__ void __launch_bounds__(256) k_edges(S *A, EdgeLines g)
+{
+    const int e = (int)blockIdx.x * 256 + (int)threadIdx.x;
+    if (e < g.total) edge_point(A, g, e);
+}
+
+static int launch_edges(int dtype, void *A, const EdgeLines &ed, hipStream_t s)
+{
+    const dim3 blocks((ed.total + 255) / 256);
+    if (dtype == IGG_F64)
+        hipLaunchKernelGGL(k_edges<double>, blocks, dim3(256), 0, s, (double *)A, ed);
+    else
+        hipLaunchKernelGGL(k_edges<float>, blocks, dim3(256), 0, s, (float *)A, ed);
+    IGG_HIP(hipGetLastError());
+    return IGG_OK;
+}
+
 int launch_adjoint_inner(int dtype, const AdjArgs &a, const Box &b, hipStream_t s)
 {
     // the z-march kernel addresses a plane with 32-bit offsets (2 GiB at most)
     const int64_t plane = (int64_t)a.nx * a.ny * (dtype == IGG_F64 ? 8 : 4);
     if (box_count(b) < zmarch_min_points() || plane + 16 >= ((int64_t)1 << 31) || a.nx < 4)
-        return launch_adjoint_boxes(dtype, a, &b, 1, s);
+    {
+        const int rc = launch_adjoint_boxes(dtype, a, &b, 1, s);
+        return rc || !a.ed.total ? rc : launch_edges(dtype, a.lam_n, a.ed, s);
+    }
     return a.form == 1 ? adjoint_inner<1>(dtype, a, b, s) : adjoint_inner<0>(dtype, a, b, s);
 }
 

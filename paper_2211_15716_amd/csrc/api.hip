@@ -532,11 +532,12 @@ static int step_ranks(const igg_field *T2, const igg_field *T, const igg_field *
     // One rank, x exchange in the stores, no schedule asked for: one launch.
     // Small grids take a kernel of their own; on larger ones the slab waves
     // store the y and z halo planes as they compute the points those planes
-    // copy (an unsplit step takes slabs of the least width).  Where only some
-    // dimensions have a period, the edges follow.  Against slabs, halo update
-    // and inner region in launches of their own: 256^3 FP64 without periods
-    // 83.5 -> 74.7 us, with two 84.6 -> 76.3, unsplit 80.0 -> 73.5.
+    // copy (an unsplit step takes slabs of the least width).  Against slabs,
+    // halo update and inner region in launches of their own: 256^3 FP64
+    // without periods 83.5 -> 74.7 us, with two 84.6 -> 76.3, unsplit 80.0 ->
+    // 73.5.
     if (self_halo_ok() && (g.schedule < 0 || g.schedule == 3)) {
+        args[0].ed = edge_lines();
         const Box all{1, g.n[0] - 1, 1, g.n[1] - 1, 1, g.n[2] - 1};
         const int *widths = split ? split : g.ol;
         Split sp;
@@ -558,7 +559,7 @@ static int step_ranks(const igg_field *T2, const igg_field *T, const igg_field *
         pk.direct = 1;
         FusedStep ctx{dtype, args.data(), &pk};
         return run_split(
-            widths, dtype, [&](hipStream_t st) { return launch_step_edges(dtype, T2[0].data, g.n, st); },
+            widths, dtype, [&](hipStream_t) { return IGG_OK; },
             [&](int r, const Split &b, hipStream_t st) { return launch_step_slabs(dtype, args[r], b, &pk, st); },
             [&](int r, const Box &b, hipStream_t st) { return launch_step_inner(dtype, args[r], b, st); }, s, true,
             fused_step, &ctx);
@@ -721,6 +722,7 @@ static int adjoint_step(int form, const igg_field *lam_n, const igg_field *lam_n
         // halo points, those points (the adjoint runs its chain serially
         // anyway, so the boundary has nothing to overlap)
         AdjArgs a0 = args[0];
+        a0.ed = edge_lines();
         a0.yz = YZImg{1, -1, -1, -1, -1, g.n[1], g.n[2]};
         if (g.periods[1]) {
             a0.yz.jl = g.ol[1] - 1;
@@ -735,7 +737,7 @@ static int adjoint_step(int form, const igg_field *lam_n, const igg_field *lam_n
         if ((rc = small ? launch_adjoint_small(dt_, a0, s) : launch_adjoint_inner(dt_, a0, all, s))) return rc;
         if ((rc = timing_mark(s, 0))) return rc;
         if (g.timing) { g.t_launches++; g.t_points += box_points(all); }
-        return launch_step_edges(dt_, lam_n[0].data, g.n, s);
+        return IGG_OK;
     }
     if (!split) {
         for (int r = 0; r < P; ++r) {

@@ -293,6 +293,53 @@ __device__ __forceinline__ bool boxset_point(const BoxSet &bs, int64_t t, int &i
     return i < bx.i1;
 }
 
+// ------------------------------------------------------------------ edges
+// The points of a field's y and z halo planes (of periodic y and z) that lie
+// in a plane of a dimension without a period: no step computes them, and the
+// halo update copies them from their images in y and z, which lie in the same
+// fixed plane, so nothing else in a step's launch writes the sources.  They
+// lie on the 12 edges of the block: 4 lines along x, 4 along y, 4 along z,
+// total points in all (0 where every dimension has a period, or y and z have
+// none: nothing to copy).
+struct EdgeLines {
+    int n[3];
+    int per[3];
+    int ylo, yhi, zlo, zhi;  // images of y = ny-1, 0 and z = nz-1, 0
+    int total;
+};
+
+template <typename S>
+__device__ __forceinline__ void edge_point(S *A, const EdgeLines &g, int e)
+{
+    const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    int x, y, z;
+    if (e < 4 * nx) {
+        const int s = e / nx;
+        x = e - s * nx;
+        y = s & 1 ? ny - 1 : 0;
+        z = s & 2 ? nz - 1 : 0;
+    } else if (e < 4 * (nx + ny)) {
+        e -= 4 * nx;
+        const int s = e / ny;
+        y = e - s * ny;
+        x = s & 1 ? nx - 1 : 0;
+        z = s & 2 ? nz - 1 : 0;
+    } else {
+        e -= 4 * (nx + ny);
+        const int s = e / nz;
+        z = e - s * nz;
+        x = s & 1 ? nx - 1 : 0;
+        y = s & 2 ? ny - 1 : 0;
+    }
+    const bool ex = x == 0 || x == nx - 1, ey = y == 0 || y == ny - 1, ez = z == 0 || z == nz - 1;
+    const bool fixed = (ex && !g.per[0]) || (ey && !g.per[1]) || (ez && !g.per[2]);
+    const bool my = ey && g.per[1], mz = ez && g.per[2];
+    if (!fixed || !(my || mz)) return;
+    const int ys = my ? (y == 0 ? g.yhi : g.ylo) : y, zs = mz ? (z == 0 ? g.zhi : g.zlo) : z;
+    const int64_t sy = nx, sz = (int64_t)nx * ny;
+    A[x + sy * y + sz * z] = A[x + sy * ys + sz * zs];
+}
+
 // ------------------------------------------------------------ XCD mapping
 // Work-groups of one launch are handed to the 8 XCDs (each with its own L2)
 // in turn: group g runs on XCD g % 8.  Renumber them so each XCD receives

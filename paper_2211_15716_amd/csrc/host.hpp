@@ -145,6 +145,7 @@ struct StepArgs {
     int stochastic;
     XHalo xh;
     SrOrigin so;
+    EdgeLines ed{};  // edges of T2 copied by the launch (total > 0)
 };
 int launch_step_boxes(int dtype, const StepArgs &a, const Box *b, int nb, hipStream_t s);
 struct SlabPack;
@@ -157,10 +158,9 @@ int launch_step_boundary(int dtype, const StepArgs &a, const Split &sp, hipStrea
 // The step on one rank in one launch, halo update of T2 included, for grids
 // too small for z-march tiles.
 int launch_step_small(int dtype, const StepArgs &a, hipStream_t s);
-// The points of a field's y and z halo planes in the planes of dimensions without
-// a period, which the halo update copies but no step computes (nothing to do
-// unless some dimensions have a period and others none).
-int launch_step_edges(int dtype, void *A, const int n[3], hipStream_t s);
+// The edges of a grid-sized field of one rank, for a launch that fills its
+// halo.
+EdgeLines edge_lines();
 
 // Two steps in one launch, on one rank whose periodic dimensions overlap by
 // 2: T2 = T_{n+2} from T = T_n (valid halo), halo of T2 included; with mid,
@@ -231,6 +231,7 @@ struct AdjArgs {
     int form = 0;          // 0: Laplacian step, 1: staggered flux form
     double lamf = 0.0;     // lam, for the flux form's face fluxes
     YZImg yz{};            // y/z halo of lam_n stored with its images (on: set)
+    EdgeLines ed{};        // edges of lam_n copied by the launch (total > 0)
 };
 int launch_adjoint_boxes(int dtype, const AdjArgs &a, const Box *b, int nb, hipStream_t s);
 int launch_adjoint_inner(int dtype, const AdjArgs &a, const Box &b, hipStream_t s);

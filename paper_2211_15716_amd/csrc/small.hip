@@ -7,9 +7,7 @@
 // (plane ol-1 for plane n-1, plane n-ol for plane 0) is stored there too by
 // the thread that computes it.  Where some dimensions have a period and
 // others none, the points in which the latter's planes meet the former's halo
-// are copied by the launch's last work-groups (k_step_edges after the z-march
-// kernel), as the halo update copies them: their sources are points that no
-// step writes.
+// are copied by the launch's last work-groups (EdgeLines).
 #include "host.hpp"
 
 namespace igg {
@@ -25,50 +23,6 @@ struct OneGeom {
     int per[3];
     int lo[3], hi[3];  // per dimension: the plane copied to plane n-1, and to plane 0
 };
-
-// ------------------------------------------------------------------- edges
-// y and z halo planes of periodic y and z at the points where another
-// dimension has no period: point (i, j, k) takes the value at the images of j
-// and k.  Line by line, e = 0..: count in one_edges().
-struct OneEdges {
-    int64_t first;   // first work-group of the edges
-    int line[3];     // points per dimension whose lines exist (0: none): along x, y, z
-    int total;
-};
-
-template <typename S>
-__device__ __forceinline__ void one_edge_point(S *A, const OneGeom &g, const OneEdges &ed, int e)
-{
-    // lines along x (y and z at a boundary), along y (x and z), along z (x and y)
-    int c[3], d = 0;
-    while (d < 2 && e >= 4 * ed.line[d]) e -= 4 * ed.line[d++];
-    const int l = ed.line[d];
-    const int s = e / l, a = d == 0 ? 1 : 0, b = d == 2 ? 1 : 2;
-    c[d] = e - s * l;
-    c[a] = s & 1 ? g.n[a] - 1 : 0;
-    c[b] = s & 2 ? g.n[b] - 1 : 0;
-    bool fixed = false, moved = false;
-    int m[3] = {c[0], c[1], c[2]};
-    for (int q = 0; q < 3; ++q) {
-        const bool end = c[q] == 0 || c[q] == g.n[q] - 1;
-        if (!end) continue;
-        if (!g.per[q]) fixed = true;
-        else if (q > 0) {
-            m[q] = c[q] == 0 ? g.hi[q] : g.lo[q];
-            moved = true;
-        }
-    }
-    if (!fixed || !moved) return;
-    const int64_t sy = g.n[0], sz = (int64_t)g.n[0] * g.n[1];
-    A[c[0] + sy * c[1] + sz * c[2]] = A[m[0] + sy * m[1] + sz * m[2]];
-}
-
-template <typename S>
-__global__ void __launch_bounds__(256) k_step_edges(S *__restrict__ T2, OneGeom g, OneEdges ed)
-{
-    const int e = (int)blockIdx.x * 256 + threadIdx.x;
-    if (e < ed.total) one_edge_point(T2, g, ed, e);
-}
 
 // Stores v at (i, j, k) and at the halo points that copy it.
 template <typename S>
@@ -106,17 +60,17 @@ __device__ __forceinline__ void one_store(const OneGeom &g, int i, int j, int k,
 // 69 x 300 x 301 FP32 17.4 against 34.8.
 template <typename S, int NZ, int SR>
 __global__ void __launch_bounds__(256)
-k_step_small(S *__restrict__ T2, const S *__restrict__ T, const S *__restrict__ Ci, OneGeom g, OneEdges ed, int nbp,
+k_step_small(S *__restrict__ T2, const S *__restrict__ T, const S *__restrict__ Ci, OneGeom g, EdgeLines ed, int first_edge, int nbp,
              OneCoef<compute_t<S>> cf, uint32_t key, SrOrigin so)
 {
     using C = compute_t<S>;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-    if (blockIdx.x >= ed.first) {
-        const int e = (int)(blockIdx.x - ed.first) * 256 + threadIdx.x;
-        if (e < ed.total) one_edge_point(T2, g, ed, e);
+    if ((int)blockIdx.x >= first_edge) {
+        const int e = ((int)blockIdx.x - first_edge) * 256 + threadIdx.x;
+        if (e < ed.total) edge_point(T2, ed, e);
         return;
     }
-    const uint32_t b = (uint32_t)xcd_remap(blockIdx.x, ed.first);
+    const uint32_t b = (uint32_t)xcd_remap(blockIdx.x, first_edge);
     const uint32_t bp = b % (uint32_t)nbp, bz = b / (uint32_t)nbp;
     const uint32_t q = bp * 256 + threadIdx.x, w = (uint32_t)(nx - 2);
     const int j = 1 + (int)(q / w), i = 1 + (int)(q % w), k0 = 1 + (int)bz * NZ;
@@ -161,20 +115,6 @@ OneGeom geom(const int n[3])
     return g;
 }
 
-// The edge lines of a grid of mixed periods (none otherwise), after `first`
-// work-groups; returns the number of work-groups they add.
-int64_t one_edges(const OneGeom &g, int64_t first, int threads, OneEdges &ed)
-{
-    ed = OneEdges{first, {0, 0, 0}, 0};
-    const int np = g.per[0] + g.per[1] + g.per[2];
-    if (np == 0 || np == 3 || (!g.per[1] && !g.per[2])) return 0;
-    for (int d = 0; d < 3; ++d) {
-        ed.line[d] = g.n[d];
-        ed.total += 4 * g.n[d];
-    }
-    return (ed.total + threads - 1) / threads;
-}
-
 template <typename S, int NZ>
 int run_small(const StepArgs &a, hipStream_t s)
 {
@@ -182,13 +122,12 @@ int run_small(const StepArgs &a, hipStream_t s)
     const int n[3] = {a.nx, a.ny, a.nz};
     const OneGeom g = geom(n);
     const int nbp = (int)(((int64_t)(a.nx - 2) * (a.ny - 2) + 255) / 256);
-    int64_t blocks = (int64_t)nbp * ((a.nz - 2 + NZ - 1) / NZ);
-    OneEdges ed;
-    blocks += one_edges(g, blocks, 256, ed);
+    const int main = (int)((int64_t)nbp * ((a.nz - 2 + NZ - 1) / NZ));
+    const int64_t blocks = (int64_t)main + (a.ed.total + 255) / 256;
     const OneCoef<C> cf{(C)a.a, (C)a.rx, (C)a.ry, (C)a.rz};
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, s, (S *)a.T2, (const S *)a.T, (const S *)a.Ci, g,
-                           ed, nbp, cf, a.key, a.so);
+                           a.ed, main, nbp, cf, a.key, a.so);
     };
     if constexpr (sizeof(S) == 2) {
         if (a.stochastic) {
@@ -198,18 +137,6 @@ int run_small(const StepArgs &a, hipStream_t s)
         }
     }
     go(k_step_small<S, NZ, 0>);
-    IGG_HIP(hipGetLastError());
-    return IGG_OK;
-}
-
-template <typename S>
-int run_edges(void *A, const int n[3], hipStream_t s)
-{
-    OneEdges ed;
-    const OneGeom g = geom(n);
-    const int64_t blocks = one_edges(g, 0, 256, ed);
-    if (blocks == 0) return IGG_OK;
-    hipLaunchKernelGGL(k_step_edges<S>, dim3((unsigned)blocks), dim3(256), 0, s, (S *)A, g, ed);
     IGG_HIP(hipGetLastError());
     return IGG_OK;
 }
@@ -231,11 +158,21 @@ int launch_step_small(int dtype, const StepArgs &a, hipStream_t s)
     return small_typed<_Float16>(a, s);
 }
 
-int launch_step_edges(int dtype, void *A, const int n[3], hipStream_t s)
+EdgeLines edge_lines()
 {
-    if (dtype == IGG_F64) return run_edges<double>(A, n, s);
-    if (dtype == IGG_F32) return run_edges<float>(A, n, s);
-    return run_edges<_Float16>(A, n, s);
+    const Grid &g = grid();
+    EdgeLines ed{};
+    for (int d = 0; d < 3; ++d) {
+        ed.n[d] = g.n[d];
+        ed.per[d] = g.periods[d];
+    }
+    ed.ylo = g.ol[1] - 1;
+    ed.yhi = g.n[1] - g.ol[1];
+    ed.zlo = g.ol[2] - 1;
+    ed.zhi = g.n[2] - g.ol[2];
+    const bool all = g.periods[0] && g.periods[1] && g.periods[2];
+    if (!all && (g.periods[1] || g.periods[2])) ed.total = 4 * (g.n[0] + g.n[1] + g.n[2]);
+    return ed;
 }
 
 }  // namespace igg

@@ -345,9 +345,11 @@ struct ZTile {
     XHalo xh;
     SrOrigin so;
     // boundary slabs in the same launch: work-groups [0, slab_blocks) run
-    // the slab waves of ss (dispatched first), the rest tile the boxes
+    // the slab waves of ss (dispatched first) and after them the waves that
+    // copy T2's edges, the rest tile the boxes
     int64_t slab_blocks;
     SlabSet ss;
+    EdgeLines ed;
 };
 
 // BX x TY threads; thread (tx, ty) owns RY consecutive rows of VEC points.
@@ -376,8 +378,10 @@ k_step_zmarch(S *__restrict__ T2, const S *__restrict__ T, const S *__restrict__
     int64_t g = blockIdx.x;
     if constexpr (!WRAP) {
         if (g < z.slab_blocks) {
-            slab_body<S, VEC, (SR > 0)>(T2, T, Ci, z.ss, a, rx, ry, rz, key,
-                                        g * (BX * TY / 64) + (int64_t)(threadIdx.x / 64), threadIdx.x & 63);
+            const int64_t w = g * (BX * TY / 64) + (int64_t)(threadIdx.x / 64);
+            const int64_t e = (w - z.ss.waves) * 64 + (threadIdx.x & 63);
+            if (e >= 0 && e < z.ed.total) edge_point(T2, z.ed, (int)e);
+            slab_body<S, VEC, (SR > 0)>(T2, T, Ci, z.ss, a, rx, ry, rz, key, w, threadIdx.x & 63);
             return;
         }
     }
@@ -868,7 +872,8 @@ static int run_zmarch(const StepArgs &a, const Box *b, int nbox, hipStream_t s, 
     if (nbox == 1) z.box[1] = z.box[0];
     if (slabs && slabs->waves > 0) {
         z.ss = *slabs;
-        z.slab_blocks = (slabs->waves + (BX * TY / 64) - 1) / (BX * TY / 64);
+        z.ed = a.ed;
+        z.slab_blocks = (slabs->waves + (a.ed.total + 63) / 64 + (BX * TY / 64) - 1) / (BX * TY / 64);
         blocks += z.slab_blocks;
     }
     if (blocks == 0) return IGG_OK;
