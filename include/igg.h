@@ -316,6 +316,25 @@ int diffusion_step_adjoint(const igg_field *lam_n, const igg_field *lam_np1,
                            double lam, double dt, double dx, double dy, double dz,
                            const int split[3], void *stream);
 
+/* Adjoint steps that one launch can take on this grid for fields of element
+ * type dtype: 2 where diffusion_step_adjoint_pair applies and pays (FP64 and
+ * FP32, on one rank with overlaps of 2 in the periodic dimensions, the default
+ * schedule and no kernel timing; not on grids of middle size, which two single
+ * steps take as fast), else 1; 0 without a grid or for an unknown dtype. */
+int igg_adjoints_per_launch(int dtype);
+
+/* Two adjoint steps in one launch: lam_n from lam_np2 through lambda_{n+1},
+ * which stays on chip, with the terms of T_np1 and T_n added to gCi: the bits
+ * and the halo planes two calls of diffusion_step_adjoint give, for lam_np2
+ * and Ci with valid halos (in dimensions without a period, lambda_{n+1} has
+ * lam_np2's planes, which are zero).
+ * Errors: as diffusion_step_adjoint; IGG_ERR_STATE where
+ * igg_adjoints_per_launch is 1. */
+int diffusion_step_adjoint_pair(const igg_field *lam_n, const igg_field *lam_np2, const igg_field *T_np1,
+                                const igg_field *T_n, const igg_field *Ci, const igg_field *gCi,
+                                double lam, double dt, double dx, double dy, double dz,
+                                const int split[3], void *stream);
+
 /* diffusion_step_adjoint for every rank of the grid: each argument is an
  * array of nranks fields, rank r's blocks (no output block sharing memory
  * with another block).  The x exchange of lam_n stores into the x

@@ -17,13 +17,6 @@
 
 namespace igg {
 
-template <typename C>
-__device__ __forceinline__ void adjoint_point(C l, C lapmu, C lapT, C a, C &lam_n, C &g)
-{
-    lam_n = fma_(a, lapmu, l);
-    g = fma_(a * l, lapT, g);
-}
-
 // One cell of the adjoint from mu = Ci.*lp and T_n at the cell and its six
 // neighbours.  FORM 0, the Laplacian step (a = dt*lam, r = 1/dd^2):
 //   lam_n = lp + a*L(mu),  gCi += a*lp*L(T_n).
@@ -38,7 +31,8 @@ __device__ __forceinline__ void adj_cell(C l, C m0, C mxm, C mxp, C mym, C myp, 
     if constexpr (FORM == 0) {
         const C lapmu = laplace<C>(m0, mxm, mxp, mym, myp, mzm, mzp, rx, ry, rz);
         const C lapT = laplace<C>(t0, txm, txp, tym, typ, tzm, tzp, rx, ry, rz);
-        adjoint_point<C>(l, lapmu, lapT, a, ln, g);
+        ln = adjoint_lam<C>(l, lapmu, a);
+        g = adjoint_grad<C>(l, lapT, a, g);
     } else {
         const C divp = flux_div<C>(face_flux<C>(m0, mxm, lamf, rx), face_flux<C>(mxp, m0, lamf, rx),
                                    face_flux<C>(m0, mym, lamf, ry), face_flux<C>(myp, m0, lamf, ry),

@@ -600,17 +600,19 @@ static int step_ranks(const igg_field *T2, const igg_field *T, const igg_field *
         [&](int r, const Box &b, hipStream_t st) { return launch_step_inner(dtype, args[r], b, st); }, s);
 }
 
-// Whether two steps may run as one launch (launch_step_pair): one rank, the
-// default schedule, overlaps of 2 in the periodic dimensions.  Timing counts
-// single steps, so it keeps them.
-static bool pair_ok(int dtype)
+// Whether two steps may run as one launch (launch_step_pair,
+// launch_adjoint_pair): one rank, the default schedule, overlaps of 2 in the
+// periodic dimensions.  Timing counts single steps, so it keeps them.
+static bool pairs_allowed()
 {
     const Grid &g = grid();
     for (int d = 0; d < 3; ++d)
         if (g.periods[d] && g.ol[d] != 2) return false;
     return g.nranks == 1 && g.fuse_x && g.slab_pack == 2 && (g.schedule < 0 || g.schedule == 3) && !g.timing &&
-           g.delay_where == 0 && step_pair_pays(dtype, g.n);
+           g.delay_where == 0;
 }
+static bool pair_ok(int dtype) { return pairs_allowed() && step_pair_pays(dtype, grid().n); }
+static bool adjoint_pair_ok(int dtype) { return pairs_allowed() && adjoint_pair_pays(dtype, grid().n); }
 
 // Two checked steps T -> T2 in one launch, the state between them stored in
 // mid when given.
@@ -657,12 +659,11 @@ static int update_halo_ranks(const igg_field *fields, int nfields, void *stream)
     return launch_halo(fields, nfields, (hipStream_t)stream);
 }
 
-// The adjoint step of either form (0: Laplacian, 1: staggered flux form)
-// for the grid's nranks ranks: each argument is an array of one field per
-// rank (a single field on a one-rank grid).
-static int adjoint_step(int form, const igg_field *lam_n, const igg_field *lam_np1, const igg_field *T_n,
-                        const igg_field *Ci, const igg_field *gCi, double lam, double dt, double dx, double dy,
-                        double dz, const int split[3], void *stream)
+// The argument checks of an adjoint step for the grid's nranks ranks (host
+// only).
+static int check_adjoint(const igg_field *lam_n, const igg_field *lam_np1, const igg_field *T_n, const igg_field *Ci,
+                         const igg_field *gCi, double lam, double dt, double dx, double dy, double dz,
+                         const int split[3])
 {
     Grid &g = grid();
     int rc;
@@ -691,6 +692,21 @@ static int adjoint_step(int form, const igg_field *lam_n, const igg_field *lam_n
         }
     if ((rc = check_spacings(lam, dt, dx, dy, dz))) return rc;
     if ((rc = check_split(split, g.ol))) return rc;
+    return IGG_OK;
+}
+
+// The adjoint step of either form (0: Laplacian, 1: staggered flux form)
+// for the grid's nranks ranks: each argument is an array of one field per
+// rank (a single field on a one-rank grid).
+static int adjoint_step(int form, const igg_field *lam_n, const igg_field *lam_np1, const igg_field *T_n,
+                        const igg_field *Ci, const igg_field *gCi, double lam, double dt, double dx, double dy,
+                        double dz, const int split[3], void *stream)
+{
+    Grid &g = grid();
+    int rc;
+    const int P = g.nranks;
+    if ((rc = check_adjoint(lam_n, lam_np1, T_n, Ci, gCi, lam, dt, dx, dy, dz, split))) return rc;
+    const int dt_ = lam_n[0].dtype;
     // per rank: the x exchange of lam_n stored by the adjoint kernels into
     // the x neighbours' lam_n, as in the step
     std::vector<AdjArgs> args(P);
@@ -1246,6 +1262,32 @@ int diffusion_step_adjoint(const igg_field *lam_n, const igg_field *lam_np1,
     if (g.nranks > 1)
         return fail(IGG_ERR_STATE, "the grid holds several virtual ranks: use diffusion_step_adjoint_ranks");
     return adjoint_step(0, lam_n, lam_np1, T_n, Ci, gCi, lam, dt, dx, dy, dz, split, stream);
+}
+
+int igg_adjoints_per_launch(int dtype)
+{
+    if (!grid().init || dtype < IGG_F64 || dtype > IGG_F16) return 0;
+    return adjoint_pair_ok(dtype) ? 2 : 1;
+}
+
+int diffusion_step_adjoint_pair(const igg_field *lam_n, const igg_field *lam_np2, const igg_field *T_np1,
+                                const igg_field *T_n, const igg_field *Ci, const igg_field *gCi, double lam, double dt,
+                                double dx, double dy, double dz, const int split[3], void *stream)
+{
+    Grid &g = grid();
+    if (!g.init) return fail(IGG_ERR_STATE, "the global grid is not initialised");
+    if (g.nranks > 1)
+        return fail(IGG_ERR_STATE, "the grid holds several virtual ranks: use diffusion_step_adjoint_ranks");
+    int rc;
+    if ((rc = check_adjoint(lam_n, lam_np2, T_np1, Ci, gCi, lam, dt, dx, dy, dz, split))) return rc;
+    if ((rc = check_adjoint(lam_n, lam_np2, T_n, Ci, gCi, lam, dt, dx, dy, dz, split))) return rc;
+    if (!adjoint_pair_ok(lam_n->dtype))
+        return fail(IGG_ERR_STATE, "two adjoint steps in one launch do not apply on this grid");
+    if ((rc = ensure_device())) return rc;
+    const AdjPairArgs a{lam_n->data, lam_np2->data, T_np1->data, T_n->data, Ci->data, gCi->data,
+                        g.n[0], g.n[1], g.n[2], {g.periods[0], g.periods[1], g.periods[2]},
+                        dt * lam, 1.0 / (dx * dx), 1.0 / (dy * dy), 1.0 / (dz * dz)};
+    return launch_adjoint_pair(lam_n->dtype, a, (hipStream_t)stream);
 }
 
 int diffusion_step_adjoint_ranks(const igg_field *lam_n, const igg_field *lam_np1, const igg_field *T_n,

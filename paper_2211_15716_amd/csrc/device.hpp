@@ -254,6 +254,19 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void *p, int64_
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
 }
 
+// One cell of the adjoint of the Laplacian step from lp and the Laplacians of
+// mu = Ci.*lp and of T_n there: lam_n, and gCi with the step's term added.
+template <typename C>
+__device__ __forceinline__ C adjoint_lam(C l, C lapmu, C a)
+{
+    return fma_(a, lapmu, l);
+}
+template <typename C>
+__device__ __forceinline__ C adjoint_grad(C l, C lapT, C a, C g)
+{
+    return fma_(a * l, lapT, g);
+}
+
 // ------------------------------------------------------------------ boxes
 // Half-open index box [i0,i1) x [j0,j1) x [k0,k1).
 struct Box {

@@ -183,6 +183,23 @@ int launch_step_pair(int dtype, const StepPairArgs &a, hipStream_t s);
 // there at all).
 bool step_pair_pays(int dtype, const int n[3]);
 
+// Two adjoint steps of the Laplacian form in one launch, on the grids where
+// adjoint_pair_pays: lam = lambda_n from l2 = lambda_{n+2}, T1 = T_{n+1} and T0 =
+// T_n, both steps' terms added to gCi.
+struct AdjPairArgs {
+    void *lam;
+    const void *l2;
+    const void *T1;
+    const void *T0;
+    const void *Ci;
+    void *gCi;
+    int nx, ny, nz;
+    int per[3];
+    double a, rx, ry, rz;  // as AdjArgs
+};
+int launch_adjoint_pair(int dtype, const AdjPairArgs &a, hipStream_t s);
+bool adjoint_pair_pays(int dtype, const int n[3]);
+
 // The y and z halo planes of one rank that is its own neighbour in every
 // periodic dimension, packed by the boundary-slab kernel as it computes them.
 // send[d][s] holds the plane of dimension d+1 (y, then z) sent to the lower

@@ -12,7 +12,7 @@
 // 0 is the point of plane n-2 and that of plane n-1 the point of plane 1; in
 // a dimension without a period it keeps T_n's value.  The halo of T_{n+2} is
 // stored with the points it copies.
-#include "host.hpp"
+#include "pair.hpp"
 
 namespace igg {
 
@@ -21,51 +21,6 @@ namespace {
 template <typename C> struct PairCoef {
     C a, rx, ry, rz;
 };
-
-struct PairGeom {
-    int n[3];
-    int per[3];
-};
-
-// Stores v at (i, j, k) and at the halo points whose image it is in periodic
-// dimensions of overlap 2.
-template <typename S>
-__device__ __forceinline__ void pair_store(const PairGeom &g, int i, int j, int k, S *A, S v)
-{
-    const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-    const int64_t sy = nx, sz = (int64_t)nx * ny;
-    S *P = A + (i + sy * j + sz * k);
-    *P = v;
-    const bool xe = g.per[0] && (i == 1 || i == nx - 2), ye = g.per[1] && (j == 1 || j == ny - 2);
-    const bool ze = g.per[2] && (k == 1 || k == nz - 2);
-    if (!xe && !ye && !ze) return;
-    // the distance to the image in each dimension, twice where both halo
-    // planes copy the point (n = 3)
-    const int64_t dx[3] = {0, xe && i == 1 ? nx - 2 : 0, xe && i == nx - 2 ? -(nx - 2) : 0};
-    const int64_t dy[3] = {0, ye && j == 1 ? sy * (ny - 2) : 0, ye && j == ny - 2 ? -sy * (ny - 2) : 0};
-    const int64_t dz[3] = {0, ze && k == 1 ? sz * (nz - 2) : 0, ze && k == nz - 2 ? -sz * (nz - 2) : 0};
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        if (c && !dz[c]) continue;
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            if (b && !dy[b]) continue;
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-                if (!a ? (b || c) : dx[a] != 0) P[dx[a] + dy[b] + dz[c]] = v;
-        }
-    }
-}
-
-// The plane, row or column read for index c in -1..n (others: clamped): in a
-// periodic dimension the one the halo update copies it from.  Ci's own halo is
-// never read, nor are T's edges, where a plane of a dimension without a period
-// meets a halo plane (a step leaves them as they are).
-__device__ __forceinline__ int wrap(int c, int n, int per)
-{
-    if (per) c = c <= 0 ? c + n - 2 : (c >= n - 1 ? c - (n - 2) : c);
-    return c < 0 ? 0 : (c > n - 1 ? n - 1 : c);
-}
 
 // ------------------------------------------------------------ small grids
 // One block of BX x BY x BZ points of T_{n+2} per work-group: the u points of
@@ -151,15 +106,6 @@ k_step2_block(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T,
 // 64 KB of loads in flight.  Time per step in a time loop, against single
 // steps: 512^3 FP64 319 us against 527, FP32 172 against 285; 256^3 FP64 44
 // against 73, FP32 23 against 47; 301 x 257 x 203 FP32 25 against 48.
-struct PairTile {
-    PairGeom g;
-    int W, HG;       // vectors and row groups of the work-group
-    int ntx, nty;    // tiles
-    int zc;          // planes per work-group
-    int nt;          // 1: non-temporal stores
-    int deal;        // 1: tile rows dealt to the XCDs in turn, 0: in ranges
-};
-
 template <typename S, int VEC, int RY, int CROSS, int MID>
 __global__ void __launch_bounds__(1024)
 k_step2_zmarch(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T, const S *__restrict__ Ci, PairTile z,
@@ -227,8 +173,6 @@ k_step2_zmarch(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T
                 fixed |= 1u << (r * VEC + q);
     }
     const uint32_t vo = (uint32_t)iv * E;
-    const bool full = i >= 1 && i + VEC <= nx - 1;
-    const bool xedge = g.per[0] && (i <= 1 || i + VEC >= nx - 1);
 
     const int64_t pb = sxy * (int64_t)E;
     auto rs = [&](const S *A, int k) { return buf_rsrc(A + (int64_t)k * sxy, pb); };
@@ -253,43 +197,10 @@ k_step2_zmarch(S *__restrict__ out, S *__restrict__ mid, const S *__restrict__ T
             if (q == hq) v[q] = x;
         return v;
     };
-    // one row of a result: the tile's points, and the halo points they fill
-    auto put_row = [&](S *A, int kk, int jj, const V &v) {
-        __amdgpu_buffer_rsrc_t d = rs(A, kk);
-        const uint32_t row = (uint32_t)(jj * nx) * E;
-        if (full) {
-            if (z.nt) buf_store<V, 2>(v, d, row + (uint32_t)i * E);
-            else buf_store<V, 0>(v, d, row + (uint32_t)i * E);
-        } else {
-#pragma unroll
-            for (int q = 0; q < VEC; ++q)
-                if (i + q >= 1 && i + q <= nx - 2) buf_store<S, 0>(v[q], d, row + (uint32_t)(i + q) * E);
-        }
-        if (xedge) {
-#pragma unroll
-            for (int q = 0; q < VEC; ++q) {
-                if (i + q == 1) buf_store<S, 0>(v[q], d, row + (uint32_t)(nx - 1) * E);
-                if (i + q == nx - 2) buf_store<S, 0>(v[q], d, row);
-            }
-        }
-    };
     auto put = [&](S *A, int k, const V (&v)[RY]) {
-        const bool zimg = g.per[2] && (k == 1 || k == nz - 2);
 #pragma unroll
-        for (int r = 0; r < RY; ++r) {
-            if (!(st >> r & 1)) continue;
-            const int j = jr[r];
-            put_row(A, k, j, v[r]);
-            if (zimg || (g.per[1] && (j == 1 || j == ny - 2))) {
-#pragma unroll 1
-                for (int m = 1; m < 9; ++m) {
-                    const int a = m % 3, c = m / 3;
-                    const int jj = a == 0 ? j : (!g.per[1] ? -1 : a == 1 ? (j == 1 ? ny - 1 : -1) : (j == ny - 2 ? 0 : -1));
-                    const int kk = c == 0 ? k : (!g.per[2] ? -1 : c == 1 ? (k == 1 ? nz - 1 : -1) : (k == nz - 2 ? 0 : -1));
-                    if (kk >= 0 && jj >= 0) put_row(A, kk, jj, v[r]);
-                }
-            }
-        }
+        for (int r = 0; r < RY; ++r)
+            if (st >> r & 1) pair_put<S, VEC>(g, A, i, jr[r], k, v[r], z.nt);
     };
 
     const int lbase = tg * RY * W + tv;
@@ -420,39 +331,7 @@ int run_zmarch2(const StepPairArgs &a, hipStream_t s)
 {
     PairTile z{};
     z.g = PairGeom{{a.nx, a.ny, a.nz}, {a.per[0], a.per[1], a.per[2]}};
-    // The tile and the planes per work-group for which the launch ends
-    // soonest: rounds of 256 work-groups (one of 700 to 1024 threads per CU;
-    // two of half the size read more rows around their tiles), each of zc
-    // planes and about one more to fill the pipeline, a plane costing a fixed
-    // time, one for its points and a little for its width.  Tiles start at
-    // whole 128-byte lines of a row (512^3 FP64: 650 us a launch against 661
-    // with the vectors beside the tile in the same waves as the tile's).
-    // Over 13 grids from 160^3 to 512^3 the choice is 4% slower than the
-    // fastest of about 200 shapes on average and 11% at worst; a launch of
-    // just over 256 work-groups instead costs up to twice the time.
-    const int nv = (a.nx - 2) / VEC + 1;  // vectors up to that of the last inner point
-    double best = 0;
-    for (int target = 128; target >= 32; target /= 2) {
-        const int ntx = (nv + target - 1) / target, W = ((nv + ntx - 1) / ntx + 7) / 8 * 8 + 2;
-        if (best > 0 && W < 42) continue;
-        for (int hg = 1024 / W; hg * RY >= 6 && hg * W > 700 - W; --hg) {
-            const int th = hg * RY - 4;
-            const int64_t cols = (int64_t)ntx * ((a.ny - 2 + th - 1) / th);
-            for (int zc = 6; zc <= 64; ++zc) {
-                const int64_t wg = cols * ((a.nz - 2 + zc - 1) / zc);
-                const double cost = (double)((wg + 255) / 256) * (zc + 1) * (400 + th * (W - 2) + 2 * W);
-                if (best == 0 || cost < best) {
-                    best = cost;
-                    z.ntx = ntx;
-                    z.W = W;
-                    z.HG = hg;
-                    z.zc = zc;
-                }
-            }
-        }
-    }
-    const int TH = z.HG * RY - 4;
-    z.nty = (a.ny - 2 + TH - 1) / TH;
+    pair_tiles<VEC, RY>(a.nx, a.ny, a.nz, z);
     const int64_t blocks = (int64_t)z.ntx * z.nty * ((a.nz - 2 + z.zc - 1) / z.zc);
     // Stores that stay in the caches where T, T2 and Ci fit the 256 MB
     // last-level cache together (256^3 FP32 47 us a launch against 52, 320 x

@@ -80,6 +80,11 @@ class Problem:
         igg.diffusion_step_adjoint(lam_n, lam_np1, Tn, Ci, gCi, self.lam, self.dt, self.dx, self.dy, self.dz,
                                    split=self.split, stream=stream)
 
+    def adjoint_pair(self, lam_n, lam_np2, Tnp1, Tn, Ci, gCi, stream=None):
+        """Two adjoint steps in one launch, lambda_{n+1} not kept."""
+        igg.diffusion_step_adjoint_pair(lam_n, lam_np2, Tnp1, Tn, Ci, gCi, self.lam, self.dt, self.dx, self.dy,
+                                        self.dz, split=self.split, stream=stream)
+
 
 class FluxProblem:
     """The staggered flux form of the same time loop (Sec. 2 staggered grid)
@@ -221,6 +226,31 @@ def _pairs(prob, T0):
             and "step" not in vars(prob) and igg.steps_per_launch(T0) == 2)
 
 
+def _adjoint_pairs(prob, T0):
+    """Whether the sweep may take two of prob's adjoint steps in one launch."""
+    return (isinstance(T0, torch.Tensor) and isinstance(prob, Problem) and type(prob).adjoint is Problem.adjoint
+            and "adjoint" not in vars(prob) and igg.adjoints_per_launch(T0) == 2)
+
+
+def _pair_adjoints(ops):
+    """Merge ("adjoint", n), nothing but a restore of state n-1 and frees, and
+    ("adjoint", n-1) into the restore, ("adjoint2", n) and the frees: the
+    adjoint steps of n and n-1 in one launch, both states being stored."""
+    out, q = [], 0
+    while q < len(ops):
+        n, e = ops[q][1], q + 1
+        while ops[q][0] == "adjoint" and e < len(ops) and (ops[e][0] == "free" or ops[e] == ("restore", n - 1)):
+            e += 1
+        if ops[q][0] == "adjoint" and e < len(ops) and ops[e] == ("adjoint", n - 1) and ("restore", n - 1) in ops[q:e]:
+            out.append(("adjoint2", n))
+            out.extend(op for op in ops[q + 1:e] if op[0] == "free")
+            q = e + 1
+        else:
+            out.append(ops[q])
+            q += 1
+    return out
+
+
 def _pair_stores(ops):
     """Merge ("advance_store", a, b) followed by ("advance_store", b, b+1)
     into ("advance_store2", a, b+1), whose last two steps are one launch that
@@ -244,7 +274,8 @@ class Sweep:
     buffer directly, which is a freed snapshot's buffer when one is free (its
     halo planes in non-periodic dimensions hold T0's, which no step writes).
     Where the library takes two steps in one launch, states that nobody needs
-    are skipped and neighbouring snapshots are written by one launch; the
+    are skipped, neighbouring snapshots are written by one launch and two
+    adjoint steps whose states are both stored are taken by one; the
     step from T0 is a single one, which gives every later state the halo such
     launches rely on.  Counts forward and adjoint steps."""
 
@@ -260,6 +291,8 @@ class Sweep:
         self.pairs = _pairs(prob, T0)
         ops = _fuse_stores(ops)
         self.fwd, self.rev = [_pair_stores(p) if self.pairs else p for p in _split_ops(ops)]
+        if _adjoint_pairs(prob, T0):
+            self.rev = _pair_adjoints(self.rev)
 
     def _advance(self, a, b, fresh=False):
         """From state a to state b; with fresh, b is written to a new
@@ -345,6 +378,13 @@ class Sweep:
                 self.p.adjoint(ln, lp, self.cur, self.Ci, gCi)
                 lp, ln = ln, lp
                 self.adjoints += 1
+            elif op[0] == "adjoint2":
+                n, T1 = op[1], self.cur
+                assert self.cur_n == n, (op, self.cur_n)
+                self.cur, self.cur_n = self.store[n - 1], n - 1
+                self.p.adjoint_pair(ln, lp, T1, self.cur, self.Ci, gCi)
+                lp, ln = ln, lp
+                self.adjoints += 2
             else:
                 self._do(op)
         return lp, gCi

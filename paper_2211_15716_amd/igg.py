@@ -37,7 +37,8 @@ EXPORTS = ["igg_init_global_grid", "igg_global_size", "igg_topology", "igg_updat
            "igg_timing_enable", "igg_timing_read", "igg_last_error", "igg_version",
            "igg_nranks", "igg_rank_coords", "igg_neighbors", "igg_update_halo_ranks", "diffusion_step_ranks",
            "diffusion_step_adjoint_ranks", "diffusion_flux_step_ranks", "diffusion_flux_step_adjoint_ranks",
-           "diffusion_run", "igg_steps_per_launch", "diffusion_step_pair", "igg_stream_probe", "igg_reduce_noalloc", "igg_adjoint_seed"]
+           "diffusion_run", "igg_steps_per_launch", "diffusion_step_pair", "igg_adjoints_per_launch",
+           "diffusion_step_adjoint_pair", "igg_stream_probe", "igg_reduce_noalloc", "igg_adjoint_seed"]
 
 
 class IggError(RuntimeError):
@@ -92,6 +93,8 @@ def load():
                                                         _PI, vp]
     lib.igg_steps_per_launch.argtypes = [ctypes.c_int]
     lib.diffusion_step_pair.argtypes = [_PF] * 4 + [d] * 5 + [_PI, ctypes.POINTER(Rounding), vp]
+    lib.igg_adjoints_per_launch.argtypes = [ctypes.c_int]
+    lib.diffusion_step_adjoint_pair.argtypes = [_PF] * 6 + [d] * 5 + [_PI, vp]
     lib.diffusion_dt.argtypes = [_PF, d, d, d, d, ctypes.POINTER(d), vp]
     lib.diffusion_step_adjoint.argtypes = [_PF] * 5 + [d] * 5 + [_PI, vp]
     lib.diffusion_step_adjoint_ranks.argtypes = [_PF] * 5 + [d] * 5 + [_PI, vp]
@@ -327,6 +330,20 @@ def diffusion_step_adjoint(lam_n, lam_np1, T_n, Ci, gCi, lam, dt, dx, dy, dz, sp
     fs = [field(t) for t in (lam_n, lam_np1, T_n, Ci, gCi)]
     _check(load().diffusion_step_adjoint(*[ctypes.byref(f) for f in fs], float(lam), float(dt), float(dx),
                                          float(dy), float(dz), _int3(split), _stream(stream)))
+
+
+def adjoints_per_launch(T):
+    """Adjoint steps one launch can take on fields like T (1 or 2)."""
+    return load().igg_adjoints_per_launch(_dtype_code(T))
+
+
+def diffusion_step_adjoint_pair(lam_n, lam_np2, T_np1, T_n, Ci, gCi, lam, dt, dx, dy, dz, split=(16, 2, 2),
+                                stream=None):
+    """Two adjoint steps in one launch: lam_n from lam_np2, the terms of T_np1
+    and T_n added to gCi; needs adjoints_per_launch(lam_n) == 2."""
+    fs = [field(t) for t in (lam_n, lam_np2, T_np1, T_n, Ci, gCi)]
+    _check(load().diffusion_step_adjoint_pair(*[ctypes.byref(f) for f in fs], float(lam), float(dt), float(dx),
+                                              float(dy), float(dz), _int3(split), _stream(stream)))
 
 
 def diffusion_flux_step(T2, T, Ci, qx, qy, qz, lam, dt, dx, dy, dz, split=None, stream=None):

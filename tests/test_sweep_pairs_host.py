@@ -81,3 +81,42 @@ def test_only_problems_own_step_is_paired(monkeypatch):
     own = diffusion.Problem(*args)
     own.step = lambda out, T, Ci, stream=None: None
     assert not diffusion._pairs(own, T)
+
+
+@pytest.mark.parametrize("sched", [("store_all",), ("periodic", 1), ("periodic", 5), ("sqrt",), ("binomial", 1),
+                                   ("binomial", 4)])
+@pytest.mark.parametrize("nt", [1, 2, 3, 8, 21])
+def test_sweep_with_adjoint_pairs_sees_every_state(sched, nt, monkeypatch):
+    """The states the adjoint steps see, one or two a launch, as with single
+    steps; no launch writes the adjoint state it reads."""
+    T0, Ci, seen = torch.full((3, 3, 3), 0.5, dtype=torch.float64), torch.rand(3, 3, 3, dtype=torch.float64), []
+
+    def f(T):
+        return 0.5 * T + Ci
+
+    def adjoint(ln, lp, Tn, *a, **k):
+        assert ln is not lp
+        seen.append(Tn.clone())
+
+    def adjoint_pair(ln, lp, T1, T, *a, **k):
+        assert ln is not lp and T1 is not T
+        seen.extend((T1.clone(), T.clone()))
+
+    monkeypatch.setattr(igg, "steps_per_launch", lambda T: 1)
+    monkeypatch.setattr(igg, "adjoints_per_launch", lambda T: 2)
+    monkeypatch.setattr(igg, "diffusion_step", lambda T2, T, *a, **k: T2.copy_(f(T)))
+    monkeypatch.setattr(igg, "diffusion_step_adjoint", adjoint)
+    monkeypatch.setattr(igg, "diffusion_step_adjoint_pair", adjoint_pair)
+    for name in ("_clone", "_fresh_like"):
+        monkeypatch.setattr(diffusion, name, lambda x: x.clone())
+    monkeypatch.setattr(diffusion, "_zeros_like", lambda x: torch.zeros_like(x))
+    states = [T0.clone()]
+    for _ in range(nt):
+        states.append(f(states[-1]))
+    ops = ck.make(sched[0], nt, sched[1] if len(sched) > 1 else None)
+    sw = diffusion.Sweep(diffusion.Problem(1.0, 0.1, 1.0, 1.0, 1.0), Ci, T0, ops)
+    sw.forward(nt)
+    sw.reverse(torch.zeros_like(T0))
+    assert sw.adjoints == nt and len(seen) == nt
+    assert all(torch.equal(s, states[nt - 1 - q]) for q, s in enumerate(seen))
+    assert any(op[0] == "adjoint2" for op in sw.rev) or nt < 2 or sched[0] in ("periodic", "binomial")
