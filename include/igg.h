@@ -324,16 +324,16 @@ int diffusion_step_adjoint(const igg_field *lam_n, const igg_field *lam_np1,
 int igg_adjoints_per_launch(int dtype);
 
 /* Two adjoint steps in one launch: lam_n from lam_np2 through lambda_{n+1},
- * which stays on chip, with the terms of T_np1 and T_n added to gCi: the bits
- * and the halo planes two calls of diffusion_step_adjoint give, for lam_np2
- * and Ci with valid halos (in dimensions without a period, lambda_{n+1} has
- * lam_np2's planes, which are zero).
+ * the terms of T_{n+1} and T_n added to gCi, where T_{n+1} is diffusion_step's
+ * of T_n with the same arguments.  lambda_{n+1} and T_{n+1} stay on chip.  The
+ * bits and the halo planes of two calls of diffusion_step_adjoint, for
+ * lam_np2, T_n and Ci with valid halos (in dimensions without a period
+ * lambda_{n+1} and T_{n+1} have lam_np2's and T_n's planes, the former zero).
  * Errors: as diffusion_step_adjoint; IGG_ERR_STATE where
  * igg_adjoints_per_launch is 1. */
-int diffusion_step_adjoint_pair(const igg_field *lam_n, const igg_field *lam_np2, const igg_field *T_np1,
-                                const igg_field *T_n, const igg_field *Ci, const igg_field *gCi,
-                                double lam, double dt, double dx, double dy, double dz,
-                                const int split[3], void *stream);
+int diffusion_step_adjoint_pair(const igg_field *lam_n, const igg_field *lam_np2, const igg_field *T_n,
+                                const igg_field *Ci, const igg_field *gCi, double lam, double dt, double dx,
+                                double dy, double dz, const int split[3], void *stream);
 
 /* diffusion_step_adjoint for every rank of the grid: each argument is an
  * array of nranks fields, rank r's blocks (no output block sharing memory

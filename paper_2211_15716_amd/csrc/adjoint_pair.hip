@@ -1,18 +1,19 @@
 // adjoint_pair.hip -- two adjoint steps of the Laplacian form in one launch.
 //
-// lambda_{n+1} is computed from lambda_{n+2} tile by tile, kept on chip, and
-// lambda_n is computed from it; gCi takes the terms of both steps, the later
-// one's first.  lambda_{n+2}, Ci and gCi are read and lambda_n and gCi are
-// written once for two steps.  Every point goes through adjoint_lam and
-// adjoint_grad with the operands the one-step kernels give it, so the bits are those of two single
-// steps.  A work-group recomputes the lambda_{n+1} points its tile shares with
-// its neighbours (one layer on every side).
+// From lambda_{n+2} and T_n: T_{n+1} (the forward step's own arithmetic) and
+// lambda_{n+1} are computed tile by tile and kept on chip, then lambda_n is
+// computed from lambda_{n+1}, and gCi takes the terms of both steps, the later
+// one's first.  lambda_{n+2}, T_n, Ci and gCi are read and lambda_n and gCi
+// are written once for two steps, and T_{n+1} need not be stored at all.
+// Every point goes through the arithmetic of the one-step kernels with the
+// operands they give it, so the bits are those of two single steps.  A
+// work-group recomputes the lambda_{n+1} and T_{n+1} points its tile shares
+// with its neighbours (one layer on every side).
 //
 // One rank, overlaps of 2 in the periodic dimensions.  The halo of
-// lambda_{n+1} is formed as the halo update would (a periodic dimension's from
-// its images; one without a period keeps lambda_{n+2}'s, which is zero); the
-// halo of lambda_n is stored with the points it copies.  T_n and T_{n+1} are
-// read where they stand.
+// lambda_{n+1} and T_{n+1} is formed as the halo update would: a periodic
+// dimension's from its images; one without a period keeps lambda_{n+2}'s
+// (zero) and T_n's.  The halo of lambda_n is stored with the points it copies.
 #include "pair.hpp"
 
 namespace igg {
@@ -25,17 +26,18 @@ template <typename C> struct AdjPairCoef {
 
 // ------------------------------------------------------------ small grids
 // One block of BX x BY x BZ points of lambda_n per work-group, as
-// k_step2_block: lambda_{n+1} and mu = Ci.*lambda_{n+1} of the block and one
-// layer around it go to LDS.  Bound by the loads' instructions and latency.
+// k_step2_block: lambda_{n+1}, mu = Ci.*lambda_{n+1} and T_{n+1} of the block
+// and one layer around it go to LDS.  Bound by the loads' instructions and latency.
 template <typename C, int BX, int BY, int BZ>
 __global__ void __launch_bounds__(1024)
-k_adj2_block(C *__restrict__ lam, const C *__restrict__ l2, const C *__restrict__ T1, const C *__restrict__ T0,
-             const C *__restrict__ Ci, C *__restrict__ gCi, PairGeom g, int nbx, int nby, AdjPairCoef<C> cf)
+k_adj2_block(C *__restrict__ lam, const C *__restrict__ l2, const C *__restrict__ T, const C *__restrict__ Ci,
+             C *__restrict__ gCi, PairGeom g, int nbx, int nby, AdjPairCoef<C> cf)
 {
     constexpr int UX = BX + 2, UY = BY + 2, UZ = BZ + 2, NU = UX * UY * UZ, NO = BX * BY * BZ, NT = 1024;
     constexpr uint32_t E = sizeof(C);
     __shared__ C u[UZ][UY][UX];  // lambda_{n+1}
     __shared__ C m[UZ][UY][UX];  // Ci.*lambda_{n+1}
+    __shared__ C w[UZ][UY][UX];  // T_{n+1}
     const int b = (int)xcd_remap(blockIdx.x, gridDim.x);
     const int x0 = 1 + b % nbx * BX, y0 = 1 + b / nbx % nby * BY, z0 = 1 + b / nbx / nby * BZ;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
@@ -44,6 +46,14 @@ k_adj2_block(C *__restrict__ lam, const C *__restrict__ l2, const C *__restrict_
         return *reinterpret_cast<const C *>(reinterpret_cast<const char *>(A) + o);
     };
     auto mu = [&](uint32_t o) -> C { return ld(Ci, o) * ld(l2, o); };
+    auto lapT = [&](uint32_t p) -> C {
+        return laplace<C>(ld(T, p), ld(T, p - E), ld(T, p + E), ld(T, p - ey), ld(T, p + ey), ld(T, p - ez),
+                          ld(T, p + ez), cf.rx, cf.ry, cf.rz);
+    };
+    auto lapS = [&](const C (&s)[UZ][UY][UX], int x, int y, int z) -> C {
+        return laplace<C>(s[z][y][x], s[z][y][x - 1], s[z][y][x + 1], s[z][y - 1][x], s[z][y + 1][x], s[z - 1][y][x],
+                          s[z + 1][y][x], cf.rx, cf.ry, cf.rz);
+    };
 #pragma unroll
     for (int t = 0; t < (NU + NT - 1) / NT; ++t) {
         const int q = t * NT + threadIdx.x;
@@ -53,11 +63,12 @@ k_adj2_block(C *__restrict__ lam, const C *__restrict__ l2, const C *__restrict_
         const int sides = (ux == 0 || ux == UX - 1) + (uy == 0 || uy == UY - 1) + (uz == 0 || uz == UZ - 1);
         if (q >= NU || x >= nx || y >= ny || z >= nz || sides > 1) continue;
         const bool hx = x == 0 || x == nx - 1, hy = y == 0 || y == ny - 1, hz = z == 0 || z == nz - 1;
-        C v, c;
+        C v, c, tn;
         if ((hx && !g.per[0]) || (hy && !g.per[1]) || (hz && !g.per[2])) {
             const uint32_t p = (uint32_t)x * E + ey * (uint32_t)y + ez * (uint32_t)z;
             c = ld(Ci, p);
             v = ld(l2, p);
+            tn = ld(T, p);
         } else {
             const int xi = hx ? wrap(x, nx, 1) : x, yi = hy ? wrap(y, ny, 1) : y, zi = hz ? wrap(z, nz, 1) : z;
             const uint32_t p = (uint32_t)xi * E + ey * (uint32_t)yi + ez * (uint32_t)zi;
@@ -66,8 +77,10 @@ k_adj2_block(C *__restrict__ lam, const C *__restrict__ l2, const C *__restrict_
             const C lap = laplace<C>(c * l, mu(p - E), mu(p + E), mu(p - ey), mu(p + ey), mu(p - ez), mu(p + ez),
                                      cf.rx, cf.ry, cf.rz);
             v = adjoint_lam<C>(l, lap, cf.a);
+            tn = fma_(cf.a * c, lapT(p), ld(T, p));
         }
         u[uz][uy][ux] = v;
+        w[uz][uy][ux] = tn;
         m[uz][uy][ux] = c * v;
     }
     __syncthreads();
@@ -78,16 +91,10 @@ k_adj2_block(C *__restrict__ lam, const C *__restrict__ l2, const C *__restrict_
         const int x = x0 - 1 + ux, y = y0 - 1 + uy, z = z0 - 1 + uz;
         if (x > nx - 2 || y > ny - 2 || z > nz - 2) continue;
         const uint32_t p = (uint32_t)x * E + ey * (uint32_t)y + ez * (uint32_t)z;
-        auto lap = [&](const C *A) -> C {
-            return laplace<C>(ld(A, p), ld(A, p - E), ld(A, p + E), ld(A, p - ey), ld(A, p + ey), ld(A, p - ez),
-                              ld(A, p + ez), cf.rx, cf.ry, cf.rz);
-        };
         const C l1 = u[uz][uy][ux];
-        const C ga = adjoint_grad<C>(ld(l2, p), lap(T1), cf.a, ld(gCi, p));
-        const C gg = adjoint_grad<C>(l1, lap(T0), cf.a, ga);
-        const C lm = laplace<C>(m[uz][uy][ux], m[uz][uy][ux - 1], m[uz][uy][ux + 1], m[uz][uy - 1][ux],
-                                m[uz][uy + 1][ux], m[uz - 1][uy][ux], m[uz + 1][uy][ux], cf.rx, cf.ry, cf.rz);
-        pair_store(g, x, y, z, lam, adjoint_lam<C>(l1, lm, cf.a));
+        const C ga = adjoint_grad<C>(ld(l2, p), lapS(w, ux, uy, uz), cf.a, ld(gCi, p));
+        const C gg = adjoint_grad<C>(l1, lapT(p), cf.a, ga);
+        pair_store(g, x, y, z, lam, adjoint_lam<C>(l1, lapS(m, ux, uy, uz), cf.a));
         *reinterpret_cast<C *>(reinterpret_cast<char *>(gCi) + p) = gg;
     }
 }
@@ -98,22 +105,24 @@ k_adj2_block(C *__restrict__ lam, const C *__restrict__ l2, const C *__restrict_
 constexpr int kAdjPlane = 1024;
 
 // The tiling of k_step2_zmarch with one row per thread.  At plane k a work-group
-// has four LDS tiles (mu_{n+2} and T_{n+1} of plane k, mu_{n+1} and T_n of
+// has four LDS tiles (mu_{n+2} and T_n of plane k, mu_{n+1} and T_{n+1} of
 // plane k-1) in one of two buffers, the tiles of the plane before in the other,
-// and in registers Ci and lambda_{n+2} of planes k and k+1, T_{n+1} of plane
-// k+1 and T_n of plane k, with the next planes in flight: one barrier a plane.
-// It computes lambda_{n+1} and the first term of gCi at plane k, then lambda_n
-// and the second term at plane k-1.  Bound by HBM bytes (7 arrays for two
-// steps, 4.7 TB/s at 256^3 FP64) and the rows re-read around the tiles; about
-// 100 registers, so that 1024 threads fit a CU (kept through the loop: the
-// state above only, the Laplacians' operands for one of the four at a time;
-// with all four at once and the addresses kept, 44 registers spilled).
-// pair_tiles chooses within 2% of the fastest of about 60 shapes at 256^3 and
-// at 160^3, 200 x 180 x 150 and 301 x 257 x 203.
+// and in registers Ci and lambda_{n+2} of planes k and k+1 and T_n of plane
+// k+1, with the next planes in flight: one barrier a plane.  It computes
+// T_{n+1} and lambda_{n+1} at plane k, then lambda_n and both terms of gCi at
+// plane k-1.
+// Bound by HBM bytes (6 arrays for two steps: 4.5 TB/s at 256^3 FP64, 4.6 at
+// 400^3) and the rows re-read around the tiles; about 100 registers, so that
+// 1024 threads fit a CU (kept through the loop: the state above only, the
+// Laplacians' operands for one of the four at a time; with all four at once
+// and the store addresses kept, 44 registers spilled).  Reading T_{n+1} from
+// memory instead of forming it: 200 us at 256^3 FP64 against 179.  pair_tiles
+// chose within 2% of the fastest of about 60 shapes at 256^3, 160^3, 200 x 180
+// x 150 and 301 x 257 x 203.
 template <typename S, int VEC, int GEN>
 __global__ void __launch_bounds__(1024)
-k_adj2_zmarch(S *__restrict__ lam, const S *__restrict__ l2, const S *__restrict__ T1, const S *__restrict__ T0,
-              const S *__restrict__ Ci, S *__restrict__ gCi, PairTile z, AdjPairCoef<S> cf)
+k_adj2_zmarch(S *__restrict__ lam, const S *__restrict__ l2, const S *__restrict__ T, const S *__restrict__ Ci,
+              S *__restrict__ gCi, PairTile z, AdjPairCoef<S> cf)
 {
     typedef S V __attribute__((ext_vector_type(VEC)));
     constexpr uint32_t E = sizeof(S);
@@ -145,7 +154,7 @@ k_adj2_zmarch(S *__restrict__ lam, const S *__restrict__ l2, const S *__restrict
     const int kb = 1 + bz * z.zc;
     const int ke = kb + z.zc < nz - 1 ? kb + z.zc : nz - 1;
 
-    // lambda_{n+2} and Ci: where a vector is read (as in k_step2_zmarch)
+    // lambda_{n+2}, T_n and Ci: where a vector is read (as in k_step2_zmarch)
     int iv = i;
     if (i < 0) iv = g.per[0] ? i + nx - 2 : 0;
     if (i >= nx) iv = g.per[0] ? i - (nx - 2) : 0;
@@ -155,15 +164,13 @@ k_adj2_zmarch(S *__restrict__ lam, const S *__restrict__ l2, const S *__restrict
     if (g.per[0] && i < nx && i + VEC >= nx) { hq = nx - 1 - i; hx = 1; }
     const bool edges = GEN && g.per[0] && !(g.per[1] && g.per[2]);
     const uint32_t row = (uint32_t)(wrap(j, ny, g.per[1]) * nx) * E, vo = row + (uint32_t)iv * E;
-    // T_n, T_{n+1} and gCi: at their own place; the rows and vectors that only
-    // lambda_{n+1} needs read none (an offset past every plane: the load gives
-    // zero and touches no memory)
+    // gCi is read where it is written (elsewhere an offset past every plane:
+    // the load gives zero and touches no memory)
     constexpr uint32_t none = 0xffffff00u;
-    const bool needT = live && lr >= 1 && lr < H - 1 && i >= 0 && i < nx && j < ny;
     const bool st = live && lr >= 2 && lr < H - 2 && j <= ny - 2 && tv >= 1 && tv < W - 1 && i < nx;
-    const uint32_t to = needT ? (uint32_t)(j * nx + i) * E : none, go_ = st ? to : none;
+    const uint32_t go_ = st ? (uint32_t)(j * nx + i) * E : none;
     const uint32_t h1 = edges && hq >= 0 ? row + (uint32_t)hx * E : none;
-    uint32_t fixed = 0;  // points of lambda_{n+1} that keep lambda_{n+2}'s value
+    uint32_t fixed = 0;  // points that keep lambda_{n+2}'s and T_n's values
 #pragma unroll
     for (int q = 0; q < VEC; ++q)
         if ((!g.per[0] && (i + q <= 0 || i + q >= nx - 1)) || (!g.per[1] && (j <= 0 || j >= ny - 1))) fixed |= 1u << q;
@@ -195,9 +202,7 @@ k_adj2_zmarch(S *__restrict__ lam, const S *__restrict__ l2, const S *__restrict
         }
         return v;
     };
-    auto ldT = [&](const S *A, int k) -> V {
-        return buf_load<V, 0>(rs(A, k < 0 ? 0 : (k > nz - 1 ? nz - 1 : k)), to);
-    };
+    auto ldp = [&](const S *A, int k) -> V { return patch(ldw(A, k), ld1(A, k)); };
 
     // (threads beyond the work-group's vectors have places of their own)
     const int lb = live ? lr * W + tv : t, up = live && lr > 0 ? lb - W : lb, dn = live && lr < H - 1 ? lb + W : lb;
@@ -216,40 +221,51 @@ k_adj2_zmarch(S *__restrict__ lam, const S *__restrict__ l2, const S *__restrict
         return o;
     };
 
-    V lc = patch(ldw(l2, kb - 1), ld1(l2, kb - 1)), lp = patch(ldw(l2, kb), ld1(l2, kb));
-    V cc = patch(ldw(Ci, kb - 1), ld1(Ci, kb - 1)), cp = patch(ldw(Ci, kb), ld1(Ci, kb));
-    V tp = ldT(T1, kb), sp = ldT(T0, kb - 1), l1{}, gk{}, ga{};
+    V lc = ldp(l2, kb - 1), lp = ldp(l2, kb), cc = ldp(Ci, kb - 1), cp = ldp(Ci, kb), tp = ldp(T, kb);
+    V gk{}, l1{}, l2p{}, ltp{};  // of plane k-1: gCi, lambda_{n+1}, lambda_{n+2}, the Laplacian of T_n
     {
         V *o = lds + lb;
         o[0] = cc * lc;
-        o[plane] = ldT(T1, kb - 1);
+        o[plane] = ldp(T, kb - 1);
         o[2 * plane] = o[3 * plane] = V{};
         o += 4 * plane;
-        o[0] = patch(ldw(Ci, kb - 2), ld1(Ci, kb - 2)) * patch(ldw(l2, kb - 2), ld1(l2, kb - 2));
-        o[plane] = o[2 * plane] = o[3 * plane] = V{};
+        o[0] = ldp(Ci, kb - 2) * ldp(l2, kb - 2);
+        o[plane] = ldp(T, kb - 2);
+        o[2 * plane] = o[3 * plane] = V{};
     }
     for (int k = kb - 1; k <= ke; ++k) {
         const int buf = (k - kb + 1) & 1;
-        V *sM2 = lds + buf * 4 * plane, *sT1 = sM2 + plane, *sM1 = sT1 + plane, *sT0 = sM1 + plane;
-        V *oM2 = lds + (buf ^ 1) * 4 * plane + lb, *oT1 = oM2 + plane, *oM1 = oT1 + plane, *oT0 = oM1 + plane;
+        V *sM2 = lds + buf * 4 * plane, *sT0 = sM2 + plane, *sM1 = sT0 + plane, *sT1 = sM1 + plane;
+        V *oM2 = lds + (buf ^ 1) * 4 * plane + lb, *oT0 = oM2 + plane, *oM1 = oT0 + plane, *oT1 = oM1 + plane;
         // (the last plane's loads are read again and not used)
         const int kn = k < ke ? k + 2 : k;
-        V ln = ldw(l2, kn), cn = ldw(Ci, kn);
-        S ln1 = ld1(l2, kn), cn1 = ld1(Ci, kn);
-        V tn = ldT(T1, kn), sn = ldT(T0, k + 1);
-        V gn = buf_load<V, 2>(rs(gCi, min(k + 1, nz - 2)), go_);
+        V ln = ldw(l2, kn), cn = ldw(Ci, kn), tn = ldw(T, kn);
+        S ln1 = ld1(l2, kn), cn1 = ld1(Ci, kn), tn1 = ld1(T, kn);
+        V gn = buf_load<V, 2>(rs(gCi, min(k, nz - 2)), go_);
         __syncthreads();
         const uint32_t fx = !g.per[2] && (k <= 0 || k >= nz - 1) ? ~0u : fixed;
         // (one Laplacian's operands in registers at a time; the next plane's
         // vectors go to the other buffer as soon as this one's are used)
-        V gu, un, go, o;
+        V lt, un, tu, go, o;
         {
-            const V lt = lap(sT1, *oT1, tp);
-            *oT1 = tp;
+            const V c = sT0[lb];
+            lt = lap(sT0, *oT0, tp);
+            *oT0 = tp;
 #pragma unroll
-            for (int q = 0; q < VEC; ++q) gu[q] = adjoint_grad<S>(lc[q], lt[q], cf.a, gk[q]);
+            for (int q = 0; q < VEC; ++q) tu[q] = fx >> q & 1 ? c[q] : fma_(cf.a * cc[q], lt[q], c[q]);
         }
-        __asm__ volatile("" : "+v"(gu));
+        __asm__ volatile("" : "+v"(lt), "+v"(tu));
+        __builtin_amdgcn_sched_barrier(0);
+        {
+            const V lu = lap(sT1, *oT1, tu);
+            *oT1 = tu;
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) {
+                const S ga = adjoint_grad<S>(l2p[q], lu[q], cf.a, gk[q]);
+                go[q] = adjoint_grad<S>(l1[q], ltp[q], cf.a, ga);
+            }
+        }
+        __asm__ volatile("" : "+v"(go));
         __builtin_amdgcn_sched_barrier(0);
         {
             const V mp = cp * lp, lm = lap(sM2, *oM2, mp);
@@ -260,14 +276,6 @@ k_adj2_zmarch(S *__restrict__ lam, const S *__restrict__ l2, const S *__restrict
         __asm__ volatile("" : "+v"(un));
         __builtin_amdgcn_sched_barrier(0);
         {
-            const V lt = lap(sT0, *oT0, sp);
-            *oT0 = sp;
-#pragma unroll
-            for (int q = 0; q < VEC; ++q) go[q] = adjoint_grad<S>(l1[q], lt[q], cf.a, ga[q]);
-        }
-        __asm__ volatile("" : "+v"(go));
-        __builtin_amdgcn_sched_barrier(0);
-        {
             const V mp = cc * un, lm = lap(sM1, *oM1, mp);
             *oM1 = mp;
 #pragma unroll
@@ -276,8 +284,8 @@ k_adj2_zmarch(S *__restrict__ lam, const S *__restrict__ l2, const S *__restrict
         __asm__ volatile("" : "+v"(o));
         // the loads are waited for here, before the stores: a wait after them
         // would wait for the stores too
-        __asm__ volatile("" : "+v"(ln), "+v"(cn), "+v"(tn), "+v"(sn), "+v"(gn));
-        if constexpr (GEN) __asm__ volatile("" : "+v"(ln1), "+v"(cn1));
+        __asm__ volatile("" : "+v"(ln), "+v"(cn), "+v"(tn), "+v"(gn));
+        if constexpr (GEN) __asm__ volatile("" : "+v"(ln1), "+v"(cn1), "+v"(tn1));
         if (k > kb && st) {
             // (addresses formed here, not kept through the loop: registers)
             int is = i, js = j;
@@ -285,22 +293,22 @@ k_adj2_zmarch(S *__restrict__ lam, const S *__restrict__ l2, const S *__restrict
             pair_put<S, VEC>(g, lam, is, js, k - 1, o, 1);
             const __amdgpu_buffer_rsrc_t d = buf_rsrc(gCi + (int64_t)(k - 1) * sxy, pb);
             if (is >= 1 && is + VEC <= nx - 1) {
-                buf_store<V, 2>(go, d, to);
+                buf_store<V, 2>(go, d, go_);
             } else {
 #pragma unroll
                 for (int q = 0; q < VEC; ++q)
                     if (is + q >= 1 && is + q <= nx - 2) buf_store<S, 0>(go[q], d, (uint32_t)(js * nx + is + q) * E);
             }
         }
+        l2p = lc;
         lc = lp;
         cc = cp;
         lp = patch(ln, ln1);
         cp = patch(cn, cn1);
-        tp = tn;
-        sp = sn;
+        tp = patch(tn, tn1);
         gk = gn;
-        ga = gu;
         l1 = un;
+        ltp = lt;
     }
 }
 
@@ -311,8 +319,7 @@ int run_block(const AdjPairArgs &a, hipStream_t s)
     const int nbx = (a.nx - 2 + BX - 1) / BX, nby = (a.ny - 2 + BY - 1) / BY, nbz = (a.nz - 2 + BZ - 1) / BZ;
     const AdjPairCoef<C> cf{(C)a.a, (C)a.rx, (C)a.ry, (C)a.rz};
     hipLaunchKernelGGL((k_adj2_block<C, BX, BY, BZ>), dim3((unsigned)((int64_t)nbx * nby * nbz)), dim3(1024), 0, s,
-                       (C *)a.lam, (const C *)a.l2, (const C *)a.T1, (const C *)a.T0, (const C *)a.Ci, (C *)a.gCi, g,
-                       nbx, nby, cf);
+                       (C *)a.lam, (const C *)a.l2, (const C *)a.T, (const C *)a.Ci, (C *)a.gCi, g, nbx, nby, cf);
     IGG_HIP(hipGetLastError());
     return IGG_OK;
 }
@@ -330,7 +337,7 @@ int run_march(const AdjPairArgs &a, hipStream_t s)
     const AdjPairCoef<S> cf{(S)a.a, (S)a.rx, (S)a.ry, (S)a.rz};
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(tpb), lds, s, (S *)a.lam, (const S *)a.l2,
-                           (const S *)a.T1, (const S *)a.T0, (const S *)a.Ci, (S *)a.gCi, z, cf);
+                           (const S *)a.T, (const S *)a.Ci, (S *)a.gCi, z, cf);
     };
     // GEN: rows that end inside a vector, or a halo of x that meets planes of a
     // dimension without a period
@@ -343,25 +350,28 @@ int run_march(const AdjPairArgs &a, hipStream_t s)
 }  // namespace
 
 // Which kernel takes a pair on this grid (0: none, two single steps are as
-// fast).  Marching from 2^20 points in FP64 and 5 * 2^19 in FP32 on (us a
-// pair against two single steps: 110^3 FP64 24.6 against 31.6, 96^3 23.9
-// against 24.3; FP32 144^3 27.9 against 29.5, 128^3 26.6 against 23.0; 256^3
-// FP64 200 against 323, FP32 102 against 161); blocks below 2^19 points, where
-// the launches count (48^3 FP64 8.4 against 8.0 on the GPU, 11.5 against 21.1
-// as called in turn from Python; 96^3 25.3 against 24.3).  Or marching from
-// the points that IGG_ZMARCH_MIN_POINTS asks for on.
+// fast).  A pair saves the store of T_{n+1} in the forward steps too; us for
+// the adjoint pair and a forward pair without that store against two adjoint
+// steps and a forward pair with it.  Marching in FP64 from 3 * 2^18 points on
+// (96^3 35 against 42, 128^3 52 against 78), in FP32 from 7 * 2^18 (128^3 41
+// against 47, 110^3 49 against 36); blocks below that in FP64 and below 2^19
+// points in FP32 (80^3 24 against 27, FP32 19 against 19, 96^3 30 against 27,
+// but one launch less to make: 48^3 FP64 11.5 against 21 for the adjoint steps
+// called in turn from Python).  256^3 FP64: 179 against 323 for the adjoint
+// steps, FP32 93 against 161.  Or marching from the points that
+// IGG_ZMARCH_MIN_POINTS asks for on.
 enum { kNoPair, kPairBlocks, kPairMarch };
 static int adjoint_pair_kernel(int dtype, const int n[3])
 {
     if (dtype == IGG_F16) return kNoPair;
     const int64_t pts = (int64_t)(n[0] - 2) * (n[1] - 2) * (n[2] - 2), zm = zmarch_min_points();
     const bool def = zm == kZmarchMinPoints;
-    const int64_t m = 1 << 19, esz = elem_bytes(dtype);
+    const int64_t esz = elem_bytes(dtype);
     // 32-bit offsets in a plane (marching) or an array (blocks); rows that
     // can be read a period away
-    if (pts >= (def ? (dtype == IGG_F64 ? 2 * m : 5 * m) : zm))
+    if (pts >= (def ? (dtype == IGG_F64 ? 3 << 18 : 7 << 18) : zm))
         return n[0] >= 16 && (int64_t)n[0] * n[1] * esz + 16 < ((int64_t)1 << 31) ? kPairMarch : kNoPair;
-    if (pts >= (def ? m : zm)) return kNoPair;
+    if (def && dtype == IGG_F32 && pts >= 1 << 19) return kNoPair;
     return (int64_t)n[0] * n[1] * n[2] * esz < ((int64_t)1 << 31) ? kPairBlocks : kNoPair;
 }
 

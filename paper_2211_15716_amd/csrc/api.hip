@@ -1270,21 +1270,20 @@ int igg_adjoints_per_launch(int dtype)
     return adjoint_pair_ok(dtype) ? 2 : 1;
 }
 
-int diffusion_step_adjoint_pair(const igg_field *lam_n, const igg_field *lam_np2, const igg_field *T_np1,
-                                const igg_field *T_n, const igg_field *Ci, const igg_field *gCi, double lam, double dt,
-                                double dx, double dy, double dz, const int split[3], void *stream)
+int diffusion_step_adjoint_pair(const igg_field *lam_n, const igg_field *lam_np2, const igg_field *T_n,
+                                const igg_field *Ci, const igg_field *gCi, double lam, double dt, double dx, double dy,
+                                double dz, const int split[3], void *stream)
 {
     Grid &g = grid();
     if (!g.init) return fail(IGG_ERR_STATE, "the global grid is not initialised");
     if (g.nranks > 1)
         return fail(IGG_ERR_STATE, "the grid holds several virtual ranks: use diffusion_step_adjoint_ranks");
     int rc;
-    if ((rc = check_adjoint(lam_n, lam_np2, T_np1, Ci, gCi, lam, dt, dx, dy, dz, split))) return rc;
     if ((rc = check_adjoint(lam_n, lam_np2, T_n, Ci, gCi, lam, dt, dx, dy, dz, split))) return rc;
     if (!adjoint_pair_ok(lam_n->dtype))
         return fail(IGG_ERR_STATE, "two adjoint steps in one launch do not apply on this grid");
     if ((rc = ensure_device())) return rc;
-    const AdjPairArgs a{lam_n->data, lam_np2->data, T_np1->data, T_n->data, Ci->data, gCi->data,
+    const AdjPairArgs a{lam_n->data, lam_np2->data, T_n->data, Ci->data, gCi->data,
                         g.n[0], g.n[1], g.n[2], {g.periods[0], g.periods[1], g.periods[2]},
                         dt * lam, 1.0 / (dx * dx), 1.0 / (dy * dy), 1.0 / (dz * dz)};
     return launch_adjoint_pair(lam_n->dtype, a, (hipStream_t)stream);

@@ -184,13 +184,12 @@ int launch_step_pair(int dtype, const StepPairArgs &a, hipStream_t s);
 bool step_pair_pays(int dtype, const int n[3]);
 
 // Two adjoint steps of the Laplacian form in one launch, on the grids where
-// adjoint_pair_pays: lam = lambda_n from l2 = lambda_{n+2}, T1 = T_{n+1} and T0 =
-// T_n, both steps' terms added to gCi.
+// adjoint_pair_pays: lam = lambda_n from l2 = lambda_{n+2} and T = T_n, both
+// steps' terms added to gCi.
 struct AdjPairArgs {
     void *lam;
     const void *l2;
-    const void *T1;
-    const void *T0;
+    const void *T;
     const void *Ci;
     void *gCi;
     int nx, ny, nz;

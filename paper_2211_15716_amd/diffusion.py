@@ -80,10 +80,10 @@ class Problem:
         igg.diffusion_step_adjoint(lam_n, lam_np1, Tn, Ci, gCi, self.lam, self.dt, self.dx, self.dy, self.dz,
                                    split=self.split, stream=stream)
 
-    def adjoint_pair(self, lam_n, lam_np2, Tnp1, Tn, Ci, gCi, stream=None):
-        """Two adjoint steps in one launch, lambda_{n+1} not kept."""
-        igg.diffusion_step_adjoint_pair(lam_n, lam_np2, Tnp1, Tn, Ci, gCi, self.lam, self.dt, self.dx, self.dy,
-                                        self.dz, split=self.split, stream=stream)
+    def adjoint_pair(self, lam_n, lam_np2, Tn, Ci, gCi, stream=None):
+        """Two adjoint steps in one launch, T_{n+1} and lambda_{n+1} not kept."""
+        igg.diffusion_step_adjoint_pair(lam_n, lam_np2, Tn, Ci, gCi, self.lam, self.dt, self.dx, self.dy, self.dz,
+                                        split=self.split, stream=stream)
 
 
 class FluxProblem:
@@ -227,28 +227,66 @@ def _pairs(prob, T0):
 
 
 def _adjoint_pairs(prob, T0):
-    """Whether the sweep may take two of prob's adjoint steps in one launch."""
-    return (isinstance(T0, torch.Tensor) and isinstance(prob, Problem) and type(prob).adjoint is Problem.adjoint
-            and "adjoint" not in vars(prob) and igg.adjoints_per_launch(T0) == 2)
+    """Whether the sweep may take two of prob's adjoint steps in one launch
+    (which forms the state between them by Problem's own step)."""
+    return (isinstance(T0, torch.Tensor) and isinstance(prob, Problem) and type(prob).step is Problem.step
+            and type(prob).adjoint is Problem.adjoint and not {"step", "adjoint"} & set(vars(prob))
+            and igg.adjoints_per_launch(T0) == 2)
 
 
 def _pair_adjoints(ops):
     """Merge ("adjoint", n), nothing but a restore of state n-1 and frees, and
-    ("adjoint", n-1) into the restore, ("adjoint2", n) and the frees: the
-    adjoint steps of n and n-1 in one launch, both states being stored."""
+    ("adjoint", n-1) into ("adjoint2", n) and the frees: the adjoint steps of n
+    and n-1 in one launch, from the stored state n-1 (not state 0, whose halo
+    no step has formed).  State n is then neither restored nor, where nothing
+    else needs it, stored or computed."""
     out, q = [], 0
     while q < len(ops):
-        n, e = ops[q][1], q + 1
-        while ops[q][0] == "adjoint" and e < len(ops) and (ops[e][0] == "free" or ops[e] == ("restore", n - 1)):
-            e += 1
-        if ops[q][0] == "adjoint" and e < len(ops) and ops[e] == ("adjoint", n - 1) and ("restore", n - 1) in ops[q:e]:
-            out.append(("adjoint2", n))
-            out.extend(op for op in ops[q + 1:e] if op[0] == "free")
-            q = e + 1
-        else:
-            out.append(ops[q])
-            q += 1
-    return out
+        op, e = ops[q], q + 1
+        if op[0] == "adjoint":
+            while e < len(ops) and (ops[e][0] == "free" or ops[e] == ("restore", op[1] - 1)):
+                e += 1
+            if op[1] > 1 and e < len(ops) and ops[e] == ("adjoint", op[1] - 1) and ("restore", op[1] - 1) in ops[q:e]:
+                if out and out[-1] == ("restore", op[1]):
+                    out.pop()
+                out.append(("adjoint2", op[1]))
+                out.extend(o for o in ops[q + 1:e] if o[0] == "free")
+                q = e + 1
+                continue
+        out.append(op)
+        q += 1
+    # snapshots that are never restored
+    live = {}  # state -> [position of its store, restores]
+    drop = set()
+    for q, op in enumerate(out):
+        n = op[-1]
+        if op[0] in ("advance_store", "store"):
+            live[n] = [q, 0]
+        elif op[0] == "restore" and n in live:
+            live[n][1] += 1
+        elif op[0] == "adjoint2" and n - 1 in live:
+            live[n - 1][1] += 1
+        elif op[0] == "free" and n in live:
+            p, used = live.pop(n)
+            if not used:
+                drop.add(q)
+                if out[p][0] == "store":
+                    drop.add(p)
+                else:
+                    out[p] = ("advance",) + out[p][1:]
+    out = [op for q, op in enumerate(out) if q not in drop]
+    # advances run together; one whose state nothing uses goes (but for the
+    # forward sweep's last, from which T_nt is computed)
+    ops, first = [], True
+    for q, op in enumerate(out):
+        if op[0] in ("advance", "advance_store") and ops and ops[-1][0] == "advance" and ops[-1][2] == op[1]:
+            ops[-1] = (op[0], ops[-1][1], op[2])
+            continue
+        if ops and ops[-1][0] == "advance" and not first and op[0] in ("restore", "adjoint2"):
+            ops.pop()
+        first = first and op[0] not in ("adjoint", "adjoint2")
+        ops.append(op)
+    return ops
 
 
 def _pair_stores(ops):
@@ -274,8 +312,9 @@ class Sweep:
     buffer directly, which is a freed snapshot's buffer when one is free (its
     halo planes in non-periodic dimensions hold T0's, which no step writes).
     Where the library takes two steps in one launch, states that nobody needs
-    are skipped, neighbouring snapshots are written by one launch and two
-    adjoint steps whose states are both stored are taken by one; the
+    are skipped and neighbouring snapshots are written by one launch; where it
+    takes two adjoint steps in one, the state between is neither stored nor
+    computed for them.  The
     step from T0 is a single one, which gives every later state the halo such
     launches rely on.  Counts forward and adjoint steps."""
 
@@ -290,9 +329,9 @@ class Sweep:
         self.peak = 1
         self.pairs = _pairs(prob, T0)
         ops = _fuse_stores(ops)
-        self.fwd, self.rev = [_pair_stores(p) if self.pairs else p for p in _split_ops(ops)]
         if _adjoint_pairs(prob, T0):
-            self.rev = _pair_adjoints(self.rev)
+            ops = _pair_adjoints(ops)
+        self.fwd, self.rev = [_pair_stores(p) if self.pairs else p for p in _split_ops(ops)]
 
     def _advance(self, a, b, fresh=False):
         """From state a to state b; with fresh, b is written to a new
@@ -379,10 +418,8 @@ class Sweep:
                 lp, ln = ln, lp
                 self.adjoints += 1
             elif op[0] == "adjoint2":
-                n, T1 = op[1], self.cur
-                assert self.cur_n == n, (op, self.cur_n)
-                self.cur, self.cur_n = self.store[n - 1], n - 1
-                self.p.adjoint_pair(ln, lp, T1, self.cur, self.Ci, gCi)
+                self.cur, self.cur_n = self.store[op[1] - 1], op[1] - 1
+                self.p.adjoint_pair(ln, lp, self.cur, self.Ci, gCi)
                 lp, ln = ln, lp
                 self.adjoints += 2
             else:
@@ -398,7 +435,7 @@ def checkpoint_ops(kind, nt, arg=None):
 
 def _split_ops(ops):
     for q, op in enumerate(ops):
-        if op[0] == "adjoint":
+        if op[0] in ("adjoint", "adjoint2"):
             return ops[:q], ops[q:]
     return ops, []
 

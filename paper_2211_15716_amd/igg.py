@@ -94,7 +94,7 @@ def load():
     lib.igg_steps_per_launch.argtypes = [ctypes.c_int]
     lib.diffusion_step_pair.argtypes = [_PF] * 4 + [d] * 5 + [_PI, ctypes.POINTER(Rounding), vp]
     lib.igg_adjoints_per_launch.argtypes = [ctypes.c_int]
-    lib.diffusion_step_adjoint_pair.argtypes = [_PF] * 6 + [d] * 5 + [_PI, vp]
+    lib.diffusion_step_adjoint_pair.argtypes = [_PF] * 5 + [d] * 5 + [_PI, vp]
     lib.diffusion_dt.argtypes = [_PF, d, d, d, d, ctypes.POINTER(d), vp]
     lib.diffusion_step_adjoint.argtypes = [_PF] * 5 + [d] * 5 + [_PI, vp]
     lib.diffusion_step_adjoint_ranks.argtypes = [_PF] * 5 + [d] * 5 + [_PI, vp]
@@ -337,11 +337,11 @@ def adjoints_per_launch(T):
     return load().igg_adjoints_per_launch(_dtype_code(T))
 
 
-def diffusion_step_adjoint_pair(lam_n, lam_np2, T_np1, T_n, Ci, gCi, lam, dt, dx, dy, dz, split=(16, 2, 2),
-                                stream=None):
-    """Two adjoint steps in one launch: lam_n from lam_np2, the terms of T_np1
-    and T_n added to gCi; needs adjoints_per_launch(lam_n) == 2."""
-    fs = [field(t) for t in (lam_n, lam_np2, T_np1, T_n, Ci, gCi)]
+def diffusion_step_adjoint_pair(lam_n, lam_np2, T_n, Ci, gCi, lam, dt, dx, dy, dz, split=(16, 2, 2), stream=None):
+    """Two adjoint steps in one launch: lam_n from lam_np2, the terms of
+    T_{n+1} (the step of T_n) and T_n added to gCi; needs
+    adjoints_per_launch(lam_n) == 2."""
+    fs = [field(t) for t in (lam_n, lam_np2, T_n, Ci, gCi)]
     _check(load().diffusion_step_adjoint_pair(*[ctypes.byref(f) for f in fs], float(lam), float(dt), float(dx),
                                               float(dy), float(dz), _int3(split), _stream(stream)))
 

@@ -17,27 +17,29 @@ def _fields(n, periods, dtype):
         igg.update_halo(t)
         return t
 
-    lam, T1, T0, Ci, gCi = rand(-1, 1), rand(1, 2), rand(1, 2), rand(0.25, 0.75), rand(-1, 1)
+    lam, T0, Tobs, Ci, gCi = rand(-1, 1), rand(1, 2), rand(1, 2), rand(0.25, 0.75), rand(-1, 1)
     for d, per in enumerate(periods):
         if not per:
             for k in (0, n[d] - 1):
                 lam.select(2 - d, k).zero_()
-    return lam, T1, T0, Ci, gCi
+    return lam, T0, Tobs, Ci, gCi
 
 
 def _compare(n, periods, dtype):
-    lam, T1, T0, Ci, gCi = _fields(n, periods, dtype)
+    lam, T0, _, Ci, gCi = _fields(n, periods, dtype)
     d = [1.0 / (m - 1) for m in n]
     c = (1.0, min(v * v for v in d) / 6.1 / 0.75, *d)
+    T1 = T0.clone()
+    igg.diffusion_step(T1, T0, Ci, *c, split=None)
     g1, g2 = gCi.clone(), gCi.clone()
     mid, one, two = torch.zeros_like(lam), torch.zeros_like(lam), torch.zeros_like(lam)
     igg.diffusion_step_adjoint(mid, lam, T1, Ci, g1, *c, split=None)
     igg.diffusion_step_adjoint(one, mid, T0, Ci, g1, *c, split=None)
     if igg.adjoints_per_launch(lam) == 1:
         with pytest.raises(igg.IggError):
-            igg.diffusion_step_adjoint_pair(two, lam, T1, T0, Ci, g2, *c, split=None)
+            igg.diffusion_step_adjoint_pair(two, lam, T0, Ci, g2, *c, split=None)
         return False
-    igg.diffusion_step_adjoint_pair(two, lam, T1, T0, Ci, g2, *c, split=None)
+    igg.diffusion_step_adjoint_pair(two, lam, T0, Ci, g2, *c, split=None)
     assert torch.equal(two, one)
     assert torch.equal(g2, g1)
     return True
