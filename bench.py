@@ -629,9 +629,9 @@ def main():
 def adjoint_variant(igg, torch, synth):
     """Loss and gradient of the 256^3 FP64 inverse problem: nt = 200 steps,
     T_obs from Ci_true (sine), guess Ci = 0.5, snapshots every 16 steps.
-    Algorithmic bytes: 24 per point per forward step (forward sweep and
-    recomputation) and 48 per point per adjoint step (lam', Ci, T_n read,
-    gCi read and written, lam written)."""
+    Algorithmic bytes: 24 per point per launch of forward steps (forward sweep
+    and recomputation; one step or two) and 48 per point per launch of adjoint
+    steps (lam', Ci, T_n read, gCi read and written, lam written)."""
     from paper_2211_15716_amd import diffusion
     w = synth.workload("c4_256_inverse", seed=0)
     n = w["nx"]
@@ -646,14 +646,11 @@ def adjoint_variant(igg, torch, synth):
     sched = ("periodic", 16)
     diffusion.loss_and_grad(T, C, O, prob, nt, sched)  # warm-up
     torch.cuda.synchronize()
-    igg.timing_enable(True)
     t0 = time.perf_counter()
     L, gT, gC, sw = diffusion.loss_and_grad(T, C, O, prob, nt, sched)
     torch.cuda.synchronize()
     el = time.perf_counter() - t0
-    igg.timing_enable(False)
-    k_ms, k_launches, k_pts, b_ms = igg.timing_read()
-    nbytes = (24.0 * sw.advances + 48.0 * sw.adjoints) * pts
+    nbytes = (24.0 * sw.advance_launches + 48.0 * sw.adjoint_launches) * pts
     # the same gradient with events between the sweeps: the reverse sweep's
     # own time (adjoint steps plus the recomputation inside each segment)
     sw2 = diffusion.Sweep(prob, C, T, diffusion.checkpoint_ops(*sched[:1], nt, *sched[1:]))
@@ -662,7 +659,7 @@ def adjoint_variant(igg, torch, synth):
     ev[0].record()
     Tnt = sw2.forward(nt)
     ev[1].record()
-    fwd_adv = sw2.advances
+    fwd_adv, fwd_launches = sw2.advances, sw2.advance_launches
     lam_nt = diffusion._inner_only(Tnt - O)
     igg.update_halo(lam_nt)
     sw2.reverse(lam_nt)
@@ -670,7 +667,7 @@ def adjoint_variant(igg, torch, synth):
     torch.cuda.synchronize()
     rev_ms = ev[1].elapsed_time(ev[2])
     recompute = sw2.advances - fwd_adv
-    rev_bytes = (48.0 * sw2.adjoints + 24.0 * recompute) * pts
+    rev_bytes = (48.0 * sw2.adjoint_launches + 24.0 * (sw2.advance_launches - fwd_launches)) * pts
     out = {"grid": [n, n, n], "nt": nt, "schedule": "periodic every 16", "ms_total": round(el * 1e3, 3),
            "forward_steps": sw.advances, "adjoint_steps": sw.adjoints, "peak_snapshots": sw.peak,
            "T_eff_GBs": round(nbytes / el / 1e9, 1), "hbm_frac": round(nbytes / el / 1e9 / HBM_PEAK_GBS, 4),

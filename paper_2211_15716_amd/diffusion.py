@@ -316,7 +316,8 @@ class Sweep:
     takes two adjoint steps in one, the state between is neither stored nor
     computed for them.  The
     step from T0 is a single one, which gives every later state the halo such
-    launches rely on.  Counts forward and adjoint steps."""
+    launches rely on.  Counts forward and adjoint steps,
+    and the launches that took them."""
 
     def __init__(self, prob, Ci, T0, ops):
         self.p, self.Ci, self.ops = prob, Ci, ops
@@ -324,8 +325,8 @@ class Sweep:
         self.work = [_clone(T0), _clone(T0)]  # halo planes of non-periodic dimensions
         self.pool = []  # buffers of freed snapshots
         self.cur, self.cur_n = T0, 0
-        self.advances = 0
-        self.adjoints = 0
+        self.advances = self.advance_launches = 0
+        self.adjoints = self.adjoint_launches = 0
         self.peak = 1
         self.pairs = _pairs(prob, T0)
         ops = _fuse_stores(ops)
@@ -350,6 +351,7 @@ class Sweep:
                 self.p.step(dst, self.cur, self.Ci)
             self.cur = dst
             self.advances += 1 + two
+            self.advance_launches += 1
             a += 1 + two
         self.cur_n = b
 
@@ -379,6 +381,7 @@ class Sweep:
             mid, dst = self._snapshot(), self._snapshot()
             self.p.step_pair(dst, mid, self.cur, self.Ci)
             self.advances += 2
+            self.advance_launches += 1
             self._keep(b - 1, mid)
             self._keep(b, dst)
             self.cur, self.cur_n = dst, b
@@ -401,6 +404,7 @@ class Sweep:
         out = _fresh_like(self.cur)  # carries the non-periodic halo planes
         self.p.step(out, self.cur, self.Ci)
         self.advances += 1
+        self.advance_launches += 1
         return out
 
     def reverse(self, lam_nt):
@@ -417,11 +421,13 @@ class Sweep:
                 self.p.adjoint(ln, lp, self.cur, self.Ci, gCi)
                 lp, ln = ln, lp
                 self.adjoints += 1
+                self.adjoint_launches += 1
             elif op[0] == "adjoint2":
                 self.cur, self.cur_n = self.store[op[1] - 1], op[1] - 1
                 self.p.adjoint_pair(ln, lp, self.cur, self.Ci, gCi)
                 lp, ln = ln, lp
                 self.adjoints += 2
+                self.adjoint_launches += 1
             else:
                 self._do(op)
         return lp, gCi
