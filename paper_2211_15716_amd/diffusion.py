@@ -37,12 +37,13 @@ def forward(T, Ci, nt, lam, dt, dx, dy, dz, split=(16, 2, 2), work=None, sr_seed
     hold T's halo planes in non-periodic dimensions).  FP16 fields round
     their stores stochastically when sr_seed is given, with counter
     counter0 + step."""
-    # Fig. 1 starts the second buffer as a copy of the first: halo planes of
-    # non-periodic dimensions are never written by the step, so both buffers
-    # must carry them from the start
-    T2 = T.clone() if work is None else work
     if nt < 1:
         return T
+    # Fig. 1 starts the second buffer as a copy of the first: halo planes of
+    # non-periodic dimensions are never written by the step, so both buffers
+    # must carry them from the start (without such dimensions there is nothing
+    # to carry: 256^3 FP64, 20 steps, 990 us with the copy, 946 without)
+    T2 = _fresh_like(T) if work is None else work
     rnd = None
     if T.dtype == torch.float16 and sr_seed is not None:
         rnd = igg.rounding("stochastic", sr_seed, counter0)
@@ -322,7 +323,7 @@ class Sweep:
     def __init__(self, prob, Ci, T0, ops):
         self.p, self.Ci, self.ops = prob, Ci, ops
         self.store = {0: T0}
-        self.work = [_clone(T0), _clone(T0)]  # halo planes of non-periodic dimensions
+        self.work = [_fresh_like(T0), _fresh_like(T0)]
         self.pool = []  # buffers of freed snapshots
         self.cur, self.cur_n = T0, 0
         self.advances = self.advance_launches = 0
