@@ -73,9 +73,9 @@ __device__ __forceinline__ void red_walk(const RedRegion &g, Load &&load, Use &&
 {
     const int lane = threadIdx.x & 63;
     const int64_t waves = (int64_t)gridDim.x * (RED_THREADS / 64);
-    int64_t r = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (RED_THREADS / 64) + (threadIdx.x >> 6)));
-    int j = (int)(r % g.h), k = (int)(r / g.h);
-    for (; r < g.rows; r += ROWS * waves) {
+    const int first = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (RED_THREADS / 64) + (threadIdx.x >> 6)));
+    int j = first % g.h, k = first / g.h;
+    for (int64_t r = first; r < g.rows; r += ROWS * waves) {
         int64_t base[ROWS];
 #pragma unroll
         for (int q = 0; q < ROWS; ++q) {
@@ -87,23 +87,24 @@ __device__ __forceinline__ void red_walk(const RedRegion &g, Load &&load, Use &&
                 ++k;
             }
         }
+        // the rows past the last are read as the first again and not used: a
+        // branch around each load made the compiler wait for the one before
         const int nr = r + (ROWS - 1) * waves < g.rows ? ROWS : (int)((g.rows - r + waves - 1) / waves);
+#pragma unroll
+        for (int q = 1; q < ROWS; ++q)
+            if (q >= nr) base[q] = base[0];
+        auto points = [&](int64_t i, auto n) {
+#pragma unroll
+            for (int q = 0; q < ROWS; ++q) load(q, base[q] + i, n);
+#pragma unroll
+            for (int q = 0; q < ROWS; ++q)
+                if (q < nr) use(q, base[q] + i, n);
+        };
         for (int i = g.i0 + lane * VEC; i < g.i1; i += 64 * VEC) {
             if (i + VEC <= g.i1) {
-#pragma unroll
-                for (int q = 0; q < ROWS; ++q)
-                    if (q < nr) load(q, base[q] + i, std::integral_constant<int, VEC>());
-#pragma unroll
-                for (int q = 0; q < ROWS; ++q)
-                    if (q < nr) use(q, base[q] + i, std::integral_constant<int, VEC>());
+                points(i, std::integral_constant<int, VEC>());
             } else {
-                for (int e = i; e < g.i1; ++e)
-#pragma unroll
-                    for (int q = 0; q < ROWS; ++q)
-                        if (q < nr) {
-                            load(q, base[q] + e, std::integral_constant<int, 1>());
-                            use(q, base[q] + e, std::integral_constant<int, 1>());
-                        }
+                for (int e = i; e < g.i1; ++e) points(e, std::integral_constant<int, 1>());
             }
         }
     }
@@ -132,8 +133,9 @@ __device__ __forceinline__ double red_lanes(int op, const double (&acc)[N])
 // and the ramp of a launch; the operation is a template argument because a
 // branch per point cost as much as the loads.  256 x 250 x 241 FP64: maximum
 // 56 -> 31 us, sum 53 -> 29 (123 MB), dot product 59 -> 43 (247 MB); 512^3:
-// maximum 363 -> 219 us (4.9 TB/s), dot product 423 -> 367 (5.9 TB/s), against
-// one row per work-group and one point per lane.
+// maximum 363 -> 202 us (5.3 TB/s), dot product 423 -> 367 (5.9 TB/s), against
+// one row per work-group and one point per lane.  Loads without a branch: 301 x
+// 257 x 203 FP64 maximum 39 -> 31 us, 512^3 218 -> 202.
 template <typename S, int OP>
 __global__ void __launch_bounds__(RED_THREADS)
 k_reduce(const S *__restrict__ a, const S *__restrict__ b, RedRegion g, double *__restrict__ part)
