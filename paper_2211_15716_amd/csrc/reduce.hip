@@ -60,9 +60,13 @@ __device__ __forceinline__ double block_combine(int op, double v, double *sh)
 // The rows (j, k) of a region of h x depth rows and nx points per row, i0 to
 // i1 of each, dealt to the waves of the launch in turn (ROWS at a time, so
 // that their loads are in flight together) and walked in vectors of 16 bytes:
-// load(q, p, n) reads the n points at offset p into slot q, use(q, p, n)
-// takes them, in an order that depends on the region and the launch only.
-// n is VEC, or 1 at the end of a row.
+// load(q, p, n) reads the n points at offset p into slot q, use(q, p, n, skip)
+// takes them but for the first `skip`, in an order that depends on the region
+// and the launch only.  n is VEC (the vector at the end of a row begins before
+// it would, and skips what the one before it took), or 1 in rows shorter than
+// that.  (Points read one by one at the end of a row cost a load's latency each:
+// 61 x 152 x 288 FP32 sum 15.0 us against 12.1, 301 x 257 x 203 20.7 against
+// 17.1.)
 struct RedRegion {
     int nx, ny, i0, i1, j0, k0, h;
     int64_t rows;
@@ -93,19 +97,26 @@ __device__ __forceinline__ void red_walk(const RedRegion &g, Load &&load, Use &&
 #pragma unroll
         for (int q = 1; q < ROWS; ++q)
             if (q >= nr) base[q] = base[0];
-        auto points = [&](int64_t i, auto n) {
+        auto points = [&](int64_t i, auto n, int skip) {
 #pragma unroll
             for (int q = 0; q < ROWS; ++q) load(q, base[q] + i, n);
+            if (skip == 0) {
 #pragma unroll
-            for (int q = 0; q < ROWS; ++q)
-                if (q < nr) use(q, base[q] + i, n);
-        };
-        for (int i = g.i0 + lane * VEC; i < g.i1; i += 64 * VEC) {
-            if (i + VEC <= g.i1) {
-                points(i, std::integral_constant<int, VEC>());
+                for (int q = 0; q < ROWS; ++q)
+                    if (q < nr) use(q, base[q] + i, n, 0);
             } else {
-                for (int e = i; e < g.i1; ++e) points(e, std::integral_constant<int, 1>());
+#pragma unroll
+                for (int q = 0; q < ROWS; ++q)
+                    if (q < nr) use(q, base[q] + i, n, skip);
             }
+        };
+        if (g.i1 - g.i0 >= VEC) {
+            for (int i = g.i0 + lane * VEC; i < g.i1; i += 64 * VEC) {
+                const int at = min(i, g.i1 - VEC);
+                points(at, std::integral_constant<int, VEC>(), i - at);
+            }
+        } else if (lane < g.i1 - g.i0) {
+            points(g.i0 + lane, std::integral_constant<int, 1>(), 0);
         }
     }
 }
@@ -160,10 +171,10 @@ k_reduce(const S *__restrict__ a, const S *__restrict__ b, RedRegion g, double *
                 if (TWO) vb[q][0] = b[p];
             }
         },
-        [&](int q, int64_t, auto n) {
+        [&](int q, int64_t, auto n, int skip) {
 #pragma unroll
             for (int e = 0; e < n.value; ++e)
-                acc[e] = combine(OP, acc[e], term<S>(OP, va[q][e], TWO ? vb[q][e] : S(0)));
+                if (e >= skip) acc[e] = combine(OP, acc[e], term<S>(OP, va[q][e], TWO ? vb[q][e] : S(0)));
         });
     double v = block_combine(OP, red_lanes<R::N>(OP, acc), sh);
     // (the host may be waiting for it)
@@ -315,14 +326,14 @@ k_seed(const S *__restrict__ a, const S *__restrict__ b, S *__restrict__ lam, in
                 if (b) vb[q][0] = b[p];
             }
         },
-        [&](int q, int64_t p, auto n) {
+        [&](int q, int64_t p, auto n, int skip) {
             typename R::type v{};
 #pragma unroll
             for (int e = 0; e < n.value; ++e) {
                 if (a && b) {
                     v[e] = (S)((C)va[q][e] - (C)vb[q][e]);
                     const double d = (double)(C)va[q][e] - (double)(C)vb[q][e];
-                    acc[e] += 0.5 * (d * d);
+                    if (e >= skip) acc[e] += 0.5 * (d * d);
                 } else if (a) {
                     v[e] = va[q][e];
                 }
