@@ -259,8 +259,10 @@ int diffusion_step_ranks(const igg_field *T2, const igg_field *T, const igg_fiel
  *          replayed on `stream`; the steps left over, and a first call, run
  *          directly.  The graph is kept for later calls with identical
  *          arguments (and pair count) and rebuilt when any differs.  For grids
- *          small enough that launch latency dominates.  Stochastic rounding
- *          needs a new counter every step, so it refuses use_graph = 1.
+ *          small enough that launch latency dominates.  On a stream that is
+ *          being captured the steps run (and are captured) directly.
+ *          Stochastic rounding needs a new counter every step, so it refuses
+ *          use_graph = 1.
  * Results are bit-identical for both values of use_graph.
  * Errors: as diffusion_step; IGG_ERR_ARG for nt < 0, a null final_buf, or
  * use_graph with stochastic rounding. */

@@ -1146,6 +1146,14 @@ int diffusion_run(const igg_field *T, const igg_field *T2, const igg_field *Ci, 
         return IGG_OK;
     };
     if (!use_graph || nrec < 2) return direct();
+    // A stream that is being captured records the launches themselves: a graph
+    // launched on it would not become part of what the caller captures.
+    if (s) {
+        if ((rc = check_step(T2, T, Ci, lam, dt, dx, dy, dz, split, rnd))) return rc;
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        IGG_HIP(hipStreamIsCapturing(s, &st));
+        if (st != hipStreamCaptureStatusNone) return direct();
+    }
     std::vector<unsigned char> key;
     auto put = [&](const void *p, size_t n) {
         const unsigned char *c = (const unsigned char *)p;
