@@ -283,7 +283,9 @@ int igg_steps_per_launch(int dtype);
  * counter + 1).  T's halo planes must hold the points they copy (any step's
  * result does); the planes of dimensions without a period are read from T,
  * and T2 and mid must hold the same.
- * Errors: as diffusion_step; IGG_ERR_STATE where igg_steps_per_launch is 1. */
+ * Errors: as diffusion_step; IGG_ERR_STATE where igg_steps_per_launch is 1
+ * for another reason than kernel timing (a caller that planned pairs before
+ * timing was switched on may launch them). */
 int diffusion_step_pair(const igg_field *T2, const igg_field *mid, const igg_field *T, const igg_field *Ci,
                         double lam, double dt, double dx, double dy, double dz, const int split[3],
                         const igg_rounding *rnd, void *stream);
@@ -331,7 +333,7 @@ int igg_adjoints_per_launch(int dtype);
  * lam_np2, T_n and Ci with valid halos (in dimensions without a period
  * lambda_{n+1} and T_{n+1} have lam_np2's and T_n's planes, the former zero).
  * Errors: as diffusion_step_adjoint; IGG_ERR_STATE where
- * igg_adjoints_per_launch is 1. */
+ * igg_adjoints_per_launch is 1 for another reason than kernel timing. */
 int diffusion_step_adjoint_pair(const igg_field *lam_n, const igg_field *lam_np2, const igg_field *T_n,
                                 const igg_field *Ci, const igg_field *gCi, double lam, double dt, double dx,
                                 double dy, double dz, const int split[3], void *stream);
@@ -463,7 +465,9 @@ int igg_plan_split(const int n[3], const int split[3], int boxes[7][6], int *nbo
  * on, and so are the boundary-slab kernels of a split step.  The events
  * carry no system-scope fence; enabling creates a pool of them for 1024
  * launches on the current device, so timed work does not pay for their
- * creation.
+ * creation.  Launches that take two steps (diffusion_step_pair,
+ * diffusion_step_adjoint_pair) are timed as one launch with every inner point
+ * computed twice; diffusion_run takes single steps while timing is on.
  * igg_timing_read synchronises those events and returns the summed
  * inner-kernel duration in milliseconds, its launch count, the inner points
  * those launches computed, and the summed boundary-kernel duration (any

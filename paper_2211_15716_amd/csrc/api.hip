@@ -602,17 +602,35 @@ static int step_ranks(const igg_field *T2, const igg_field *T, const igg_field *
 
 // Whether two steps may run as one launch (launch_step_pair,
 // launch_adjoint_pair): one rank, the default schedule, overlaps of 2 in the
-// periodic dimensions.  Timing counts single steps, so it keeps them.
+// periodic dimensions.  Nothing here changes while the grid lives: a caller
+// that planned pairs can launch them.  Timing is about single steps, so where
+// it is on none are planned (pairs_planned), but those launched are timed too.
 static bool pairs_allowed()
 {
     const Grid &g = grid();
     for (int d = 0; d < 3; ++d)
         if (g.periods[d] && g.ol[d] != 2) return false;
-    return g.nranks == 1 && g.fuse_x && g.slab_pack == 2 && (g.schedule < 0 || g.schedule == 3) && !g.timing &&
-           g.delay_where == 0;
+    return g.nranks == 1 && g.fuse_x && g.slab_pack == 2 && (g.schedule < 0 || g.schedule == 3) && g.delay_where == 0;
 }
 static bool pair_ok(int dtype) { return pairs_allowed() && step_pair_pays(dtype, grid().n); }
 static bool adjoint_pair_ok(int dtype) { return pairs_allowed() && adjoint_pair_pays(dtype, grid().n); }
+static bool pairs_planned() { return !grid().timing; }
+
+// A pair's launch, timed as one launch that computes every inner point twice.
+template <typename Launch>
+static int timed_pair(hipStream_t s, Launch launch)
+{
+    Grid &g = grid();
+    int rc;
+    if ((rc = timing_mark(s, 0))) return rc;
+    if ((rc = launch())) return rc;
+    if ((rc = timing_mark(s, 0))) return rc;
+    if (g.timing) {
+        g.t_launches++;
+        g.t_points += 2 * box_points(Box{1, g.n[0] - 1, 1, g.n[1] - 1, 1, g.n[2] - 1});
+    }
+    return IGG_OK;
+}
 
 // Two checked steps T -> T2 in one launch, the state between them stored in
 // mid when given.
@@ -629,7 +647,7 @@ static int step_pair(const igg_field *T2, const igg_field *mid, const igg_field 
                          {g.periods[0], g.periods[1], g.periods[2]}, a.a, a.rx, a.ry, a.rz,
                          rnd ? sr_key(rnd->seed, rnd->counter) : 0, rnd ? sr_key(rnd->seed, rnd->counter + 1) : 0,
                          stochastic, a.so};
-    return launch_step_pair(T->dtype, p, s);
+    return timed_pair(s, [&] { return launch_step_pair(T->dtype, p, s); });
 }
 
 // update_halo over the grid's ranks: fields[r * nfields + f] is field f of
@@ -1112,7 +1130,7 @@ int diffusion_run(const igg_field *T, const igg_field *T2, const igg_field *Ci, 
     // leaves T_nt and T_{nt-1} where single steps would; the first step is a
     // single one, which gives the state the halo the pairs rely on, and the
     // last one too, which leaves T_{nt-1} in the other buffer.
-    const int npair = nt >= 6 && pair_ok(T->dtype) ? (nt - 2) / 4 * 2 : 0;
+    const int npair = nt >= 6 && pairs_planned() && pair_ok(T->dtype) ? (nt - 2) / 4 * 2 : 0;
     int cur = 0, it = 0;
     auto single = [&](hipStream_t st) {
         igg_rounding r;
@@ -1221,7 +1239,7 @@ int diffusion_run(const igg_field *T, const igg_field *T2, const igg_field *Ci, 
 int igg_steps_per_launch(int dtype)
 {
     if (!grid().init || dtype < IGG_F64 || dtype > IGG_F16) return 0;
-    return pair_ok(dtype) ? 2 : 1;
+    return pairs_planned() && pair_ok(dtype) ? 2 : 1;
 }
 
 int diffusion_step_pair(const igg_field *T2, const igg_field *mid, const igg_field *T, const igg_field *Ci, double lam,
@@ -1275,7 +1293,7 @@ int diffusion_step_adjoint(const igg_field *lam_n, const igg_field *lam_np1,
 int igg_adjoints_per_launch(int dtype)
 {
     if (!grid().init || dtype < IGG_F64 || dtype > IGG_F16) return 0;
-    return adjoint_pair_ok(dtype) ? 2 : 1;
+    return pairs_planned() && adjoint_pair_ok(dtype) ? 2 : 1;
 }
 
 int diffusion_step_adjoint_pair(const igg_field *lam_n, const igg_field *lam_np2, const igg_field *T_n,
@@ -1294,7 +1312,8 @@ int diffusion_step_adjoint_pair(const igg_field *lam_n, const igg_field *lam_np2
     const AdjPairArgs a{lam_n->data, lam_np2->data, T_n->data, Ci->data, gCi->data,
                         g.n[0], g.n[1], g.n[2], {g.periods[0], g.periods[1], g.periods[2]},
                         dt * lam, 1.0 / (dx * dx), 1.0 / (dy * dy), 1.0 / (dz * dz)};
-    return launch_adjoint_pair(lam_n->dtype, a, (hipStream_t)stream);
+    return timed_pair((hipStream_t)stream,
+                      [&] { return launch_adjoint_pair(lam_n->dtype, a, (hipStream_t)stream); });
 }
 
 int diffusion_step_adjoint_ranks(const igg_field *lam_n, const igg_field *lam_np1, const igg_field *T_n,
