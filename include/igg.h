@@ -29,7 +29,8 @@
  *     are created on the current HIP device at the first call that needs the
  *     GPU, and released by igg_finalize_global_grid.  Calls that overlap in
  *     time (from several host threads, or on unordered streams) race on the
- *     shared halo buffers and are not supported.
+ *     shared halo buffers and are not supported, except igg_reduce and
+ *     diffusion_dt, whose calls have result buffers of their own.
  *   - Environment variables choose schedules and launch shapes only; no
  *     setting changes a result bit.  Read by igg_init_global_grid:
  *     IGG_SCHEDULE (0, 1, 2 or 3: see diffusion_step; unset = by size and

@@ -182,7 +182,11 @@ int ensure_device()
     int64_t cap = std::max(m0, std::max(m1, m2)) * 8;
     g.halo_cap = (size_t)((cap + 255) / 256 * 256);
     IGG_HIP(hipMalloc((void **)&g.halo_buf, g.halo_cap * 2 * 2 * IGG_MAX_FIELDS * g.nranks));
-    IGG_HIP(hipHostMalloc((void **)&g.red_host, 1024 * sizeof(double), hipHostMallocDefault));
+    {
+        RedSlots first;  // allocated here, so that a reduction allocates nothing
+        int rc;
+        if ((rc = first.acquire())) return rc;
+    }
     g.device = dev;
     g.dev_ready = true;
     return IGG_OK;
@@ -198,7 +202,8 @@ static int release_device()
     };
     chk(hipStreamSynchronize(g.side), "hipStreamSynchronize(side)");
     chk(hipFree(g.halo_buf), "hipFree(halo_buf)");
-    chk(hipHostFree(g.red_host), "hipHostFree(red_host)");
+    for (double *p : g.red_free) chk(hipHostFree(p), "hipHostFree(red_free)");
+    g.red_free.clear();
     chk(hipEventDestroy(g.ev_fork), "hipEventDestroy");
     chk(hipEventDestroy(g.ev_join), "hipEventDestroy");
     for (hipEvent_t e : g.tev) chk(hipEventDestroy(e), "hipEventDestroy(timing)");
@@ -1415,10 +1420,10 @@ int igg_adjoint_seed(const igg_field *T, const igg_field *T_obs, const igg_field
     }
     if ((rc = ensure_device())) return rc;
     hipStream_t s = (hipStream_t)stream;
-    int parts = 0;
-    if ((rc = launch_seed(T, T_obs, *lam, loss ? &parts : nullptr, s))) return rc;
+    RedSlots slots;
+    if ((rc = launch_seed(T, T_obs, *lam, loss ? &slots : nullptr, s))) return rc;
     if (halo && (rc = launch_halo(lam, 1, s))) return rc;
-    return loss ? read_seed_loss(parts, loss, s) : IGG_OK;
+    return loss ? read_seed_loss(slots, loss, s) : IGG_OK;
 }
 
 int igg_reduce_noalloc(int op, const igg_field *a, const igg_field *b, double *out_dev, void *stream)

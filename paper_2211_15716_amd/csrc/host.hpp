@@ -68,7 +68,7 @@ struct Grid {
     unsigned char *halo_buf = nullptr;  // send and receive planes of every rank
     size_t halo_cap = 0;                // bytes of one side of one field (one plane)
 
-    double *red_host = nullptr;  // pinned host memory: per-block partial results
+    std::vector<double *> red_free;  // pinned host memory for partial results, not in use (RedSlots)
 
     int schedule = -1;  // 1: slabs + update on the helper stream, 0: slabs first on the caller
                         // stream, 2: one chain on the caller stream, -1: 1 or 2 by size
@@ -286,12 +286,23 @@ int launch_flux_small(int dtype, const FluxArgs &a, hipStream_t s);
 
 
 int launch_reduce(int op, const igg_field &a, const igg_field *b, double *out, hipStream_t s);
+// Pinned host memory of a call that returns a reduction's value: taken from the
+// grid's list (or allocated) by acquire, given back when the call ends.
+struct RedSlots {
+    double *part = nullptr;
+    int n = 0;  // partial results in it
+    RedSlots() = default;
+    RedSlots(const RedSlots &) = delete;
+    RedSlots &operator=(const RedSlots &) = delete;
+    ~RedSlots();
+    int acquire();
+};
 // lam = a - b (or a, or 0) on the inner points of lam, zero on its halo; with
-// parts, *parts partial sums of the FP64 loss 0.5*sum (a-b)^2 are left for
+// loss, the partial sums of the FP64 loss 0.5*sum (a-b)^2 are left there for
 // read_seed_loss.
-int launch_seed(const igg_field *a, const igg_field *b, const igg_field &lam, int *parts, hipStream_t s);
-// The loss from the last seed's partial sums, after synchronising s.
-int read_seed_loss(int parts, double *out, hipStream_t s);
+int launch_seed(const igg_field *a, const igg_field *b, const igg_field &lam, RedSlots *loss, hipStream_t s);
+// The loss from a seed's partial sums, after synchronising s.
+int read_seed_loss(const RedSlots &loss, double *out, hipStream_t s);
 // The same reduction into *out_dev (device memory), with the partial results
 // in the library's static device array instead of the grid's buffers: no
 // allocation, no synchronisation.

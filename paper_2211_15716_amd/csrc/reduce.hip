@@ -260,6 +260,33 @@ static double combine_host(int op, int n, const double *part)
     return acc[0];
 }
 
+// Pinned memory for the partial results of one call that returns them to the
+// host.  Calls that overlap in time (from several host threads) each have
+// their own; those not in use wait in the grid's list, which so holds as many
+// as there were such calls at once.
+static std::mutex g_red_mu;
+
+int RedSlots::acquire()
+{
+    Grid &g = grid();
+    {
+        std::lock_guard<std::mutex> lock(g_red_mu);
+        if (!g.red_free.empty()) {
+            part = g.red_free.back();
+            g.red_free.pop_back();
+            return IGG_OK;
+        }
+    }
+    IGG_HIP(hipHostMalloc((void **)&part, RED_BLOCKS * sizeof(double), hipHostMallocDefault));
+    return IGG_OK;
+}
+RedSlots::~RedSlots()
+{
+    if (!part) return;
+    std::lock_guard<std::mutex> lock(g_red_mu);
+    grid().red_free.push_back(part);
+}
+
 // The work-groups write their partial results straight to pinned host memory
 // (8 KB) and the host combines them: no second launch and no copy.  The host
 // watches for them itself for up to 2 ms: the stream's work before them has
@@ -288,12 +315,13 @@ static void mark_parts(double *part)
 
 int launch_reduce(int op, const igg_field &a, const igg_field *b, double *out, hipStream_t s)
 {
-    Grid &g = grid();
+    RedSlots slots;
     int rc, blocks = 0;
-    mark_parts(g.red_host);
-    if ((rc = launch_typed(op, a, b, g.red_host, RED_BLOCKS, &blocks, s))) return rc;
-    if ((rc = wait_parts(g.red_host, blocks, s))) return rc;
-    *out = combine_host(op, blocks, g.red_host);
+    if ((rc = slots.acquire())) return rc;
+    mark_parts(slots.part);
+    if ((rc = launch_typed(op, a, b, slots.part, RED_BLOCKS, &blocks, s))) return rc;
+    if ((rc = wait_parts(slots.part, blocks, s))) return rc;
+    *out = combine_host(op, blocks, slots.part);
     return IGG_OK;
 }
 
@@ -380,21 +408,22 @@ static int seed_typed(const igg_field *a, const igg_field *b, const igg_field &l
     return IGG_OK;
 }
 
-int launch_seed(const igg_field *a, const igg_field *b, const igg_field &lam, int *parts, hipStream_t s)
+int launch_seed(const igg_field *a, const igg_field *b, const igg_field &lam, RedSlots *loss, hipStream_t s)
 {
-    double *part = parts ? grid().red_host : nullptr;
-    int blocks = 0;
-    const int rc = lam.dtype == IGG_F64   ? seed_typed<double>(a, b, lam, part, &blocks, s)
+    int rc, blocks = 0;
+    if (loss && (rc = loss->acquire())) return rc;
+    double *part = loss ? loss->part : nullptr;
+    rc = lam.dtype == IGG_F64   ? seed_typed<double>(a, b, lam, part, &blocks, s)
                    : lam.dtype == IGG_F32 ? seed_typed<float>(a, b, lam, part, &blocks, s)
                                           : seed_typed<_Float16>(a, b, lam, part, &blocks, s);
-    if (parts) *parts = blocks;
+    if (loss) loss->n = blocks;
     return rc;
 }
 
-int read_seed_loss(int parts, double *out, hipStream_t s)
+int read_seed_loss(const RedSlots &loss, double *out, hipStream_t s)
 {
     IGG_HIP(hipStreamSynchronize(s));
-    *out = combine_host(IGG_RED_HALF_SQDIFF, parts, grid().red_host);
+    *out = combine_host(IGG_RED_HALF_SQDIFF, loss.n, loss.part);
     return IGG_OK;
 }
 
