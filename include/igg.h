@@ -211,17 +211,21 @@ int igg_finalize_global_grid(void);
  *            2  slabs, update and inner region as one chain on `stream`;
  *            3  on one rank: slabs and inner region in one launch on
  *               `stream`, whose first work-groups compute the slabs and
- *               store the y and z halo planes of T2 as they go (with
- *               IGG_SLAB_PACK=1 and every dimension periodic they fill send
- *               buffers that one copy then unpacks).  Fields of at most 88
- *               MiB in three arrays (FP16: 24) take one launch of a kernel
- *               that needs no slabs.
+ *               store the y and z halo planes of T2 as they go.  Nothing
+ *               waits for the slabs, so whatever `split` says they have the
+ *               least width, and there are none in dimensions without a
+ *               period (with IGG_SLAB_PACK=1 and every dimension periodic
+ *               they have the widths of `split` and fill send buffers that
+ *               one copy then unpacks).  Grids of at most 90 MiB of inner
+ *               points in three arrays (FP16: 25), and of at most 4 inner
+ *               rows in y, take one launch of a kernel without slabs; where
+ *               the slabs leave no inner region they are the launch.
  *          Default: 3 where it applies; otherwise 1 for inner regions of
  *          2^21 points and more in FP64/FP32, 2 for smaller ones and for
  *          FP16.
- *          NULL = no overlap asked for: on one rank the same launch with
- *          slabs of the least width, otherwise (and with a schedule set) the
- *          whole step, then the halo update, on `stream`.
+ *          NULL = no overlap asked for: on one rank the same launch,
+ *          otherwise (and with a schedule set) the whole step, then the halo
+ *          update, on `stream`.
  *   rnd    FP16 store rounding, NULL = round to nearest even (ignored for
  *          FP64/FP32).
  * Arithmetic: FP64 for IGG_F64; FP32 for IGG_F32 and IGG_F16 with dt*lam and

@@ -401,20 +401,25 @@ static bool self_halo_ok()
 }
 
 
-// Whether a step of `points` points takes the small-grid kernel: three arrays
-// of at most 88 MiB (200 x 180 x 100 FP64, 82 MiB: 22.2 us against 24.5; 400 x
-// 100 x 100 FP64, 92 MiB: 27.1 against 25.6; 256^3 FP32, 201 MB: 61 against 41
-// on inputs that were not in the caches, 38.8 against 46.7 in a time loop); in
-// FP16, whose points cost as many instructions in half the bytes, 24 MiB (200
-// x 180 x 100, 21 MiB: 14.0 against 16.6 with stochastic rounding, 13.0
-// against 12.8 without; 180 x 160 x 200, 33 MiB: 18.2 against 19.8 and 14.7
-// against 14.0; 256^3: 45 against 28.7).  Or the points that
-// IGG_ZMARCH_MIN_POINTS asks for.
-static bool step_is_small(int dtype, int64_t points)
+// Whether a step takes the small-grid kernel: its inner points in three arrays
+// of at most 90 MiB (200 x 180 x 100 FP64, 79 MiB: 22.2 us against 24.5; 400 x
+// 100 x 100 FP64, 87 MiB: 27.1 against 25.6 on inputs that were not in the
+// caches, 19.3 against 26.5 in a time loop; 256^3 FP32, 188 MiB: 61 against 41
+// and 38.8 against 46.7); in FP16, whose points cost as many instructions in
+// half the bytes, 25 MiB (200 x 180 x 100, 20 MiB: 14.0 against 16.6 with
+// stochastic rounding, 13.0 against 12.8 without; 180 x 160 x 200, 32 MiB: 18.2
+// against 19.8 and 14.7 against 14.0; 256^3: 45 against 28.7).  Planes of at
+// most four inner rows leave most of a z-march tile's threads idle and have
+// their rows side by side for the small-grid kernel, which takes them at any
+// size (4000 x 6 x 2000 FP64 227 against 327, without periods 186 against 212;
+// 4000 x 8 x 2000 322 against 354, 287 against 244).  Or the inner points that
+// IGG_ZMARCH_MIN_POINTS asks for.  The split does not come into it: the kernel
+// has no slabs.
+static bool step_is_small(int dtype, const int n[3])
 {
-    const int64_t zm = zmarch_min_points();
+    const int64_t zm = zmarch_min_points(), points = (int64_t)(n[0] - 2) * (n[1] - 2) * (n[2] - 2);
     if (zm != kZmarchMinPoints) return points < zm;
-    return points * 3 * elem_bytes(dtype) <= ((int64_t)(dtype == IGG_F16 ? 24 : 88) << 20);
+    return n[1] <= 6 || points * 3 * elem_bytes(dtype) <= ((int64_t)(dtype == IGG_F16 ? 25 : 90) << 20);
 }
 
 // The same for the adjoint: five arrays of at most 96 MiB (128^3 FP64, 84 MB:
@@ -537,29 +542,31 @@ static int step_ranks(const igg_field *T2, const igg_field *T, const igg_field *
     // One rank, x exchange in the stores, no schedule asked for: one launch.
     // Small grids take a kernel of their own; on larger ones the slab waves
     // store the y and z halo planes as they compute the points those planes
-    // copy (an unsplit step takes slabs of the least width).  Against slabs,
-    // halo update and inner region in launches of their own: 256^3 FP64
-    // without periods 83.5 -> 74.7 us, with two 84.6 -> 76.3, unsplit 80.0 ->
-    // 73.5.
+    // copy.  Against slabs, halo update and inner region in launches of their
+    // own: 256^3 FP64 without periods 83.5 -> 74.7 us, with two 84.6 -> 76.3,
+    // unsplit 80.0 -> 73.5.  Whatever the split, there are slabs in periodic
+    // dimensions only, of the least width: nothing waits for them, and a slab
+    // wave takes longer for a point than a tile (512^3 FP64 with slabs of 100
+    // planes 673 us, of 2 533; without periods and slabs 529, with slabs of 2
+    // 535; 4000 x 2000 x 4 89 and 105).
     if (self_halo_ok() && (g.schedule < 0 || g.schedule == 3)) {
         args[0].ed = edge_lines();
-        const Box all{1, g.n[0] - 1, 1, g.n[1] - 1, 1, g.n[2] - 1};
-        const int *widths = split ? split : g.ol;
-        Split sp;
-        plan_split(g.n, widths, sp);
-        sp.inner.i0 = all.i0;
-        sp.inner.i1 = all.i1;
-        if (step_is_small(dtype, box_points(sp.inner))) {
+        if (step_is_small(dtype, g.n)) {
             if ((rc = timing_mark(s, 0))) return rc;
             if ((rc = launch_step_small(dtype, args[0], s))) return rc;
             if ((rc = timing_mark(s, 0))) return rc;
-            if (g.timing) { g.t_launches++; g.t_points += box_points(all); }
+            if (g.timing) {
+                g.t_launches++;
+                g.t_points += box_points(Box{1, g.n[0] - 1, 1, g.n[1] - 1, 1, g.n[2] - 1});
+            }
             return test_delay(3, s);
         }
         SlabPack pk{};
+        int widths[3];
         for (int d = 0; d < 3; ++d) {
             pk.ol[d] = g.ol[d];
             pk.per[d] = g.periods[d];
+            widths[d] = g.periods[d] ? g.ol[d] : 1;
         }
         pk.direct = 1;
         FusedStep ctx{dtype, args.data(), &pk};
