@@ -1,7 +1,7 @@
 // reduce.hip -- FP64 reductions over a field (maximum(Ci) of Fig. 1, loss,
 // conservation and dot-product sums).  Values are widened to FP64 before
-// they are combined; rows are dealt to a fixed number of waves and combined
-// in a fixed tree, so a call's bits do not vary between runs.
+// they are combined; the field's vectors are dealt to a fixed number of threads
+// and combined in a fixed tree, so a call's bits do not vary between runs.
 #include <string.h>
 
 #include <atomic>
@@ -57,78 +57,114 @@ __device__ __forceinline__ double block_combine(int op, double v, double *sh)
     return sh[0];
 }
 
-// The rows (j, k) of a region of h x depth rows and nx points per row, i0 to
-// i1 of each, dealt to the waves of the launch in turn (ROWS at a time, so
-// that their loads are in flight together) and walked in vectors of 16 bytes:
-// load(q, p, n) reads the n points at offset p into slot q, use(q, p, n, skip)
-// takes them but for the first `skip`, in an order that depends on the region
-// and the launch only.  n is VEC (the vector at the end of a row begins before
-// it would, and skips what the one before it took), or 1 in rows shorter than
-// that.  (Points read one by one at the end of a row cost a load's latency each:
-// 61 x 152 x 288 FP32 sum 15.0 us against 12.1, 301 x 257 x 203 20.7 against
-// 17.1.)
+// A field is walked in vectors of 16 bytes from its first point to its last,
+// whatever its rows: a work-group takes chunks of U * RED_THREADS vectors, each
+// thread one in U turns whose loads are in flight together.  load(u, p) reads
+// the vector at offset p into slot u, use(u, p, m) takes it, where bit e of m
+// says that point e is one of the region's (IN: the inner points; else every
+// point); vectors without such a point are not read.  point(p) takes the points
+// after the last whole vector, which lie in a halo plane.  The order in which
+// points meet depends on the field's size and the launch only.
+//
+// Whole rows for each wave instead left waves idle where rows are few, lanes
+// where they are short, and stored to as many places as there were waves: 20000
+// x 20 x 20 FP64 maximum 69 us against 15, 13 x 500 x 700 42 against 10, seed
+// without a loss 512^3 FP64 767 against 590, 256^3 80 against 74.
 struct RedRegion {
-    int nx, ny, i0, i1, j0, k0, h;
-    int64_t rows;
-    int dj, dk;  // rows and planes from one of a wave's rows to its next
+    int nx, ny, nz;
+    int64_t nv;      // whole vectors
+    int tail;        // points after them
+    int ui, uj, uk;  // points, rows and planes from a thread's vector to its next in the turn
+    int di, dj, dk;  // and from its last in a turn to the first in the next
 };
-template <int VEC, int ROWS, typename Load, typename Use>
-__device__ __forceinline__ void red_walk(const RedRegion &g, Load &&load, Use &&use)
+// The inner points of the vector at (i, j, k), without a branch: lo of them in
+// its own row, hi in the next (a vector ends no later than the row after its
+// own, which is never a row of the next plane's inside).
+template <int VEC>
+__device__ __forceinline__ uint32_t red_inner(const RedRegion &g, int i, int j, int k)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t waves = (int64_t)gridDim.x * (RED_THREADS / 64);
-    const int first = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (RED_THREADS / 64) + (threadIdx.x >> 6)));
-    int j = first % g.h, k = first / g.h;
-    for (int64_t r = first; r < g.rows; r += ROWS * waves) {
-        int64_t base[ROWS];
+    constexpr uint32_t all = (1u << VEC) - 1;
+    const bool ks = k > 0 && k < g.nz - 1;
+    if (g.nx < VEC) {  // several rows
+        uint32_t m = 0;
 #pragma unroll
-        for (int q = 0; q < ROWS; ++q) {
-            base[q] = ((int64_t)(g.k0 + k) * g.ny + g.j0 + j) * g.nx;
-            j += g.dj;
-            k += g.dk;
-            if (j >= g.h) {
-                j -= g.h;
-                ++k;
+        for (int e = 0; e < VEC; ++e) {
+            if (i > 0 && i < g.nx - 1 && j > 0 && j < g.ny - 1 && k > 0 && k < g.nz - 1) m |= 1u << e;
+            if (++i == g.nx) {
+                i = 0;
+                if (++j == g.ny) {
+                    j = 0;
+                    ++k;
+                }
             }
         }
-        // the rows past the last are read as the first again and not used: a
-        // branch around each load made the compiler wait for the one before
-        const int nr = r + (ROWS - 1) * waves < g.rows ? ROWS : (int)((g.rows - r + waves - 1) / waves);
-#pragma unroll
-        for (int q = 1; q < ROWS; ++q)
-            if (q >= nr) base[q] = base[0];
-        auto points = [&](int64_t i, auto n, int skip) {
-#pragma unroll
-            for (int q = 0; q < ROWS; ++q) load(q, base[q] + i, n);
-            if (skip == 0) {
-#pragma unroll
-                for (int q = 0; q < ROWS; ++q)
-                    if (q < nr) use(q, base[q] + i, n, 0);
-            } else {
-#pragma unroll
-                for (int q = 0; q < ROWS; ++q)
-                    if (q < nr) use(q, base[q] + i, n, skip);
-            }
-        };
-        if (g.i1 - g.i0 >= VEC) {
-            for (int i = g.i0 + lane * VEC; i < g.i1; i += 64 * VEC) {
-                const int at = min(i, g.i1 - VEC);
-                points(at, std::integral_constant<int, VEC>(), i - at);
-            }
-        } else if (lane < g.i1 - g.i0) {
-            points(g.i0 + lane, std::integral_constant<int, 1>(), 0);
-        }
+        return m;
     }
+    const int left = min(g.nx - i, VEC + 1);  // points to the row's end
+    const uint32_t lo = ((1u << (left - 1)) - 1) & ~(i == 0 ? 1u : 0u), hi = all & ~((2u << left) - 1);
+    return (ks && j > 0 && j < g.ny - 1 ? lo : 0) | (ks && j < g.ny - 2 ? hi : 0);
+}
+template <int VEC, int U, int IN, typename Load, typename Use, typename Point>
+__device__ __forceinline__ void red_walk(const RedRegion &g, Load &&load, Use &&use, Point &&point)
+{
+    // a work-group takes U * RED_THREADS vectors in a row, its threads one each
+    // in turn
+    int64_t v = (int64_t)blockIdx.x * (U * RED_THREADS) + threadIdx.x;
+    int i = 0, j = 0, k = 0;
+    if (IN) {
+        const int64_t row = v * VEC / g.nx;
+        i = (int)(v * VEC - row * g.nx);
+        k = (int)(row / g.ny);
+        j = (int)(row - (int64_t)k * g.ny);
+    }
+    auto on = [&](int di, int dj, int dk) {
+        i += di;
+        j += dj;
+        k += dk;
+        if (i >= g.nx) {
+            i -= g.nx;
+            ++j;
+        }
+        if (j >= g.ny) {
+            j -= g.ny;
+            ++k;
+        }
+    };
+    for (; v < g.nv; v += (int64_t)gridDim.x * (U * RED_THREADS)) {
+        uint32_t m[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            m[u] = IN ? red_inner<VEC>(g, i, j, k) : (1u << VEC) - 1;
+            if (v + u * RED_THREADS >= g.nv) m[u] = 0;
+            if (IN) on(g.ui, g.uj, g.uk);
+        }
+        if (IN) on(g.di, g.dj, g.dk);
+        // vectors without a point of the region are read as the first again and
+        // not used: a branch around each load made the compiler wait for the
+        // one before
+#pragma unroll
+        for (int u = 0; u < U; ++u) load(u, (m[u] ? v + u * RED_THREADS : v) * VEC);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (v + u * RED_THREADS < g.nv) use(u, (v + u * RED_THREADS) * VEC, m[u]);
+    }
+    if (blockIdx.x == 0 && (int)threadIdx.x < g.tail) point(g.nv * VEC + threadIdx.x);
 }
 
 template <typename S> struct RedVec {
     static constexpr int N = 16 / (int)sizeof(S);
     typedef S type __attribute__((ext_vector_type(N)));
-    typedef S mem __attribute__((ext_vector_type(N), aligned(sizeof(S))));  // rows start at any element
+    typedef S mem __attribute__((ext_vector_type(N), aligned(sizeof(S))));  // fields start at any element
 };
 
-// Rows of one array, or of two, that a wave reads together.
-constexpr int RED_ROWS1 = 8, RED_ROWS2 = 4;
+// Vectors of one array, or of two, that a thread reads together.
+constexpr int RED_TURNS1 = 8, RED_TURNS2 = 4;
+
+constexpr bool red_two(int op)
+{
+    return op == IGG_RED_SUM_RATIO || op == IGG_RED_HALF_SQDIFF || op == IGG_RED_DOT || op == IGG_RED_MAX_ABS_DIFF;
+}
+constexpr int red_turns(int op) { return red_two(op) ? RED_TURNS2 : RED_TURNS1; }
 
 // A thread's accumulators into one.
 template <int N>
@@ -142,39 +178,36 @@ __device__ __forceinline__ double red_lanes(int op, const double (&acc)[N])
 
 // Bound by the loads it has in flight (8 KB of one array or of two per wave)
 // and the ramp of a launch; the operation is a template argument because a
-// branch per point cost as much as the loads.  256 x 250 x 241 FP64: maximum
-// 56 -> 31 us, sum 53 -> 29 (123 MB), dot product 59 -> 43 (247 MB); 512^3:
-// maximum 363 -> 202 us (5.3 TB/s), dot product 423 -> 367 (5.9 TB/s), against
-// one row per work-group and one point per lane.  Loads without a branch: 301 x
-// 257 x 203 FP64 maximum 39 -> 31 us, 512^3 218 -> 202.
+// branch per point cost as much as the loads.  256 x 250 x 241 FP64: maximum 24
+// us, sum 24 (123 MB), dot product 43 (247 MB); 512^3: maximum 187 us (5.7
+// TB/s), dot product 350 (6.1 TB/s).
 template <typename S, int OP>
 __global__ void __launch_bounds__(RED_THREADS)
 k_reduce(const S *__restrict__ a, const S *__restrict__ b, RedRegion g, double *__restrict__ part)
 {
     using R = RedVec<S>;
-    constexpr bool TWO = OP == IGG_RED_SUM_RATIO || OP == IGG_RED_HALF_SQDIFF || OP == IGG_RED_DOT ||
-                         OP == IGG_RED_MAX_ABS_DIFF;
-    constexpr int ROWS = TWO ? RED_ROWS2 : RED_ROWS1;
+    constexpr bool TWO = red_two(OP);
+    constexpr int TURNS = red_turns(OP), IN = OP != IGG_RED_MAX && OP != IGG_RED_MIN;
     __shared__ double sh[RED_THREADS];
     double acc[R::N];  // one per element of a vector
 #pragma unroll
     for (int e = 0; e < R::N; ++e) acc[e] = identity(OP);
-    typename R::type va[ROWS], vb[ROWS];
-    red_walk<R::N, ROWS>(
+    typename R::type va[TURNS], vb[TURNS];
+    red_walk<R::N, TURNS, IN>(
         g,
-        [&](int q, int64_t p, auto n) {
-            if constexpr (n.value > 1) {
-                va[q] = *reinterpret_cast<const typename R::mem *>(a + p);
-                if (TWO) vb[q] = *reinterpret_cast<const typename R::mem *>(b + p);
-            } else {
-                va[q][0] = a[p];
-                if (TWO) vb[q][0] = b[p];
+        [&](int u, int64_t p) {
+            va[u] = *reinterpret_cast<const typename R::mem *>(a + p);
+            if (TWO) vb[u] = *reinterpret_cast<const typename R::mem *>(b + p);
+        },
+        [&](int u, int64_t, uint32_t m) {
+#pragma unroll
+            for (int e = 0; e < R::N; ++e) {
+                const double v = combine(OP, acc[e], term<S>(OP, va[u][e], TWO ? vb[u][e] : S(0)));
+                acc[e] = !IN || (m >> e & 1) ? v : acc[e];
             }
         },
-        [&](int q, int64_t, auto n, int skip) {
-#pragma unroll
-            for (int e = 0; e < n.value; ++e)
-                if (e >= skip) acc[e] = combine(OP, acc[e], term<S>(OP, va[q][e], TWO ? vb[q][e] : S(0)));
+        [&](int64_t p) {
+            if (!IN) acc[0] = combine(OP, acc[0], term<S>(OP, a[p], S(0)));
         });
     double v = block_combine(OP, red_lanes<R::N>(OP, acc), sh);
     // (the host may be waiting for it)
@@ -192,21 +225,24 @@ k_reduce_final(int op, int n, const double *__restrict__ part, double *__restric
     if (threadIdx.x == 0) *result = v;
 }
 
-static RedRegion red_region(const igg_field &a, bool all, int &blocks)
+// The walk of a field of vectors of vec points, and its launch.
+static RedRegion red_region(const igg_field &a, int vec, int turns, int &blocks)
 {
     RedRegion g{};
-    const int nx = (int)a.size[0], ny = (int)a.size[1], nz = (int)a.size[2], in = all ? 0 : 1;
-    g.nx = nx;
-    g.ny = ny;
-    g.i0 = g.j0 = g.k0 = in;
-    g.i1 = nx - in;
-    g.h = ny - 2 * in;
-    g.rows = (int64_t)g.h * (nz - 2 * in);
-    const int64_t want = (g.rows + RED_THREADS / 64 - 1) / (RED_THREADS / 64);
-    blocks = (int)(want < RED_BLOCKS ? (want < 1 ? 1 : want) : RED_BLOCKS);
-    const int64_t waves = (int64_t)blocks * (RED_THREADS / 64);
-    g.dj = (int)(waves % g.h);
-    g.dk = (int)(waves / g.h);
+    g.nx = (int)a.size[0];
+    g.ny = (int)a.size[1];
+    g.nz = (int)a.size[2];
+    g.nv = field_elems(a) / vec;
+    g.tail = (int)(field_elems(a) % vec);
+    const int64_t want = (g.nv + RED_THREADS * turns - 1) / (RED_THREADS * turns);
+    blocks = (int)(want < RED_BLOCKS ? want : RED_BLOCKS);
+    auto steps = [&](int64_t points, int &i, int &j, int &k) {
+        i = (int)(points % g.nx);
+        j = (int)(points / g.nx % g.ny);
+        k = (int)(points / g.nx / g.ny);
+    };
+    steps((int64_t)RED_THREADS * vec, g.ui, g.uj, g.uk);
+    steps((int64_t)(blocks - 1) * RED_THREADS * turns * vec, g.di, g.dj, g.dk);
     return g;
 }
 
@@ -215,7 +251,7 @@ template <typename S>
 static int launch_part(int op, const igg_field &a, const igg_field *b, double *part, int part_cap, int *blocks,
                        hipStream_t s)
 {
-    const RedRegion g = red_region(a, op == IGG_RED_MAX || op == IGG_RED_MIN, *blocks);
+    const RedRegion g = red_region(a, RedVec<S>::N, red_turns(op), *blocks);
     if (*blocks > part_cap)
         return fail(IGG_ERR_SIZE, "reduction needs " + std::to_string(*blocks) + " partial results, the buffer holds " +
                                       std::to_string(part_cap));
@@ -327,70 +363,41 @@ int launch_reduce(int op, const igg_field &a, const igg_field *b, double *out, h
 
 // ------------------------------------------------------- adjoint seed
 // lam = a - b on the inner points (a alone without b, zero without a), zero
-// on every halo point; with want_loss, the partial sums of 0.5*(a-b)^2.  The
-// inner rows are walked exactly as k_reduce walks them for
-// IGG_RED_HALF_SQDIFF, so the loss has the bits of that reduction.  The halo
-// rows and columns are zeroed in a second walk.
+// on every halo point, each vector stored whole; with part, the partial sums of
+// 0.5*(a-b)^2.  The field is walked exactly as k_reduce walks it for
+// IGG_RED_HALF_SQDIFF, so the loss has the bits of that reduction.
 template <typename S>
 __global__ void __launch_bounds__(RED_THREADS)
-k_seed(const S *__restrict__ a, const S *__restrict__ b, S *__restrict__ lam, int nz, RedRegion g,
-       double *__restrict__ part)
+k_seed(const S *__restrict__ a, const S *__restrict__ b, S *__restrict__ lam, RedRegion g, double *__restrict__ part)
 {
     using C = compute_t<S>;
     using R = RedVec<S>;
     __shared__ double sh[RED_THREADS];
     double acc[R::N] = {};
-    const int nx = g.nx, ny = g.ny;
-    typename R::type va[RED_ROWS2], vb[RED_ROWS2];
-    red_walk<R::N, RED_ROWS2>(
+    typename R::type va[RED_TURNS2], vb[RED_TURNS2];
+    red_walk<R::N, RED_TURNS2, 1>(
         g,
-        [&](int q, int64_t p, auto n) {
+        [&](int u, int64_t p) {
             if (!a) return;
-            if constexpr (n.value > 1) {
-                va[q] = *reinterpret_cast<const typename R::mem *>(a + p);
-                if (b) vb[q] = *reinterpret_cast<const typename R::mem *>(b + p);
-            } else {
-                va[q][0] = a[p];
-                if (b) vb[q][0] = b[p];
-            }
+            va[u] = *reinterpret_cast<const typename R::mem *>(a + p);
+            if (b) vb[u] = *reinterpret_cast<const typename R::mem *>(b + p);
         },
-        [&](int q, int64_t p, auto n, int skip) {
+        [&](int u, int64_t p, uint32_t m) {
             typename R::type v{};
 #pragma unroll
-            for (int e = 0; e < n.value; ++e) {
+            for (int e = 0; e < R::N; ++e) {
+                const bool in = m >> e & 1;
                 if (a && b) {
-                    v[e] = (S)((C)va[q][e] - (C)vb[q][e]);
-                    const double d = (double)(C)va[q][e] - (double)(C)vb[q][e];
-                    if (e >= skip) acc[e] += 0.5 * (d * d);
+                    v[e] = in ? (S)((C)va[u][e] - (C)vb[u][e]) : S(0);
+                    const double d = (double)(C)va[u][e] - (double)(C)vb[u][e];
+                    acc[e] = in ? acc[e] + 0.5 * (d * d) : acc[e];
                 } else if (a) {
-                    v[e] = va[q][e];
+                    v[e] = in ? va[u][e] : S(0);
                 }
             }
-            if constexpr (n.value > 1) *reinterpret_cast<typename R::mem *>(lam + p) = v;
-            else lam[p] = v[0];
-        });
-    const int64_t t = (int64_t)blockIdx.x * RED_THREADS + threadIdx.x, nt = (int64_t)gridDim.x * RED_THREADS;
-    // halo columns of the inner rows
-    for (int64_t r = t; r < g.rows; r += nt) {
-        const int64_t base = ((1 + r / g.h) * ny + 1 + r % g.h) * nx;
-        lam[base] = S(0);
-        lam[base + nx - 1] = S(0);
-    }
-    // halo rows: j = 0 and ny-1 of every plane, then every row of planes 0 and nz-1
-    const int64_t hrows = 2 * (int64_t)nz + 2 * (int64_t)(ny - 2);
-    for (int64_t r = blockIdx.x; r < hrows; r += gridDim.x) {
-        int j, k;
-        if (r < 2 * (int64_t)nz) {
-            j = (r & 1) ? ny - 1 : 0;
-            k = (int)(r >> 1);
-        } else {
-            const int64_t q = r - 2 * (int64_t)nz;
-            j = 1 + (int)(q >> 1);
-            k = (q & 1) ? nz - 1 : 0;
-        }
-        const int64_t base = (int64_t)k * nx * ny + (int64_t)j * nx;
-        for (int i = threadIdx.x; i < nx; i += RED_THREADS) lam[base + i] = S(0);
-    }
+            *reinterpret_cast<typename R::mem *>(lam + p) = v;
+        },
+        [&](int64_t p) { lam[p] = S(0); });
     if (part) {
         double v = block_combine(IGG_RED_HALF_SQDIFF, red_lanes<R::N>(IGG_RED_HALF_SQDIFF, acc), sh);
         if (threadIdx.x == 0) part[blockIdx.x] = v;
@@ -401,9 +408,9 @@ template <typename S>
 static int seed_typed(const igg_field *a, const igg_field *b, const igg_field &lam, double *part, int *blocks,
                       hipStream_t s)
 {
-    const RedRegion g = red_region(lam, false, *blocks);
+    const RedRegion g = red_region(lam, RedVec<S>::N, RED_TURNS2, *blocks);
     hipLaunchKernelGGL(k_seed<S>, dim3(*blocks), dim3(RED_THREADS), 0, s, a ? (const S *)a->data : nullptr,
-                       b ? (const S *)b->data : nullptr, (S *)lam.data, (int)lam.size[2], g, part);
+                       b ? (const S *)b->data : nullptr, (S *)lam.data, g, part);
     IGG_HIP(hipGetLastError());
     return IGG_OK;
 }
