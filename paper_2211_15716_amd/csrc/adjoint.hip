@@ -479,8 +479,9 @@ static int run_zmarch(const AdjArgs &a, const Box &b, hipStream_t s)
     z.nx = a.nx;
     z.ny = a.ny;
     z.nz = a.nz;
-    z.xa = (b.i0 / VEC) * VEC;
-    z.ntx = (b.i1 - z.xa + TW - 1) / TW;
+    const RowTiles t = row_tiles(b, VEC, TW);
+    z.xa = t.xa;
+    z.ntx = t.n;
     z.nty = (b.j1 - b.j0 + TH - 1) / TH;
     int depth = b.k1 - b.k0;
     int zc = env_int("IGG_ADJ_ZCHUNK", 0);
@@ -537,9 +538,8 @@ static int adjoint_inner(int dtype, const AdjArgs &a, const Box &b, hipStream_t 
     // 128-point rows where they leave a fifth fewer lanes past the rows' ends
     // (301 x 257 x 203 117 -> 94 us, 384^3 305 -> 267; where both fit alike
     // 512^3 600 against 628, 401 x 300 x 250 180 against 193)
-    const int n = b.i1 - b.i0 / 4 * 4, wide = (n + 255) / 256 * 256, half = (n + 127) / 128 * 128;
-    return half * 5 <= wide * 4 ? run_zmarch<float, 2, 64, 4, 1, FORM>(a, b, s)
-                                : run_zmarch<float, 4, 64, 4, 1, FORM>(a, b, s);
+    return narrow_pays(row_tiles(b, 4, 256), row_tiles(b, 2, 128)) ? run_zmarch<float, 2, 64, 4, 1, FORM>(a, b, s)
+                                                                   : run_zmarch<float, 4, 64, 4, 1, FORM>(a, b, s);
 }
 
 template <typename C, int FORM>
@@ -583,10 +583,14 @@ static int launch_edges(int dtype, void *A, const EdgeLines &ed, hipStream_t s)
 
 int launch_adjoint_inner(int dtype, const AdjArgs &a, const Box &b, hipStream_t s)
 {
-    // the z-march kernel addresses a plane with 32-bit offsets (2 GiB at most)
+    // the z-march kernel addresses a plane with 32-bit offsets (2 GiB at
+    // most), and leaves most of its lanes idle in rows of up to 36 points (two
+    // ranks of 13 x 1500 x 600 FP64 510 us by the box kernel against 957, FP32 265
+    // against 612; 34 x 800 x 500 475 against 508 and 254 against 350; 50 x 700 x
+    // 400 600 against 390 and 323 against 263)
     const int64_t plane = (int64_t)a.nx * a.ny * (dtype == IGG_F64 ? 8 : 4);
-    if (box_count(b) < zmarch_min_points() || plane + 16 >= ((int64_t)1 << 31) || a.nx < 4)
-    {
+    if (box_count(b) < zmarch_min_points() || plane + 16 >= ((int64_t)1 << 31) || a.nx < 4 ||
+        (rows_dispatched() && b.i1 - b.i0 <= 36)) {
         const int rc = launch_adjoint_boxes(dtype, a, &b, 1, s);
         return rc || !a.ed.total ? rc : launch_edges(dtype, a.lam_n, a.ed, s);
     }

@@ -418,27 +418,35 @@ static bool self_halo_ok()
 static bool step_is_small(int dtype, const int n[3])
 {
     const int64_t zm = zmarch_min_points(), points = (int64_t)(n[0] - 2) * (n[1] - 2) * (n[2] - 2);
-    if (zm != kZmarchMinPoints) return points < zm;
+    if (!rows_dispatched()) return points < zm;
     return n[1] <= 6 || points * 3 * elem_bytes(dtype) <= ((int64_t)(dtype == IGG_F16 ? 25 : 90) << 20);
 }
 
 // The same for the adjoint: five arrays of at most 96 MiB (128^3 FP64, 84 MB:
 // 23.4 us against 32.1; 160^3 FP32, 82 MB: 19.9 against 30.3; 200 x 180 x 100
 // FP64, 144 MB: 54.2 against 41.6 on inputs that were not in the caches, 37.6
-// against 42.1 in a loop).
-static bool adjoint_is_small(int dtype, int64_t points)
+// against 42.1 in a loop), and rows of up to 40 (FP64) or 64 points at any size,
+// which leave z-march tiles' lanes idle (42 x 700 x 450 FP64 188 against 196, 46 x
+// 700 x 420 189 against 188; 66 x 600 x 350 FP32 87 against 92, 72 x 600 x 320 89
+// against 86; 13 x 1500 x 600 163 against 456 and 79 against 291).
+static bool adjoint_is_small(int dtype, const int n[3])
 {
-    const int64_t zm = zmarch_min_points();
-    return zm == kZmarchMinPoints ? points * 5 * elem_bytes(dtype) <= ((int64_t)96 << 20) : points < zm;
+    const int64_t zm = zmarch_min_points(), points = (int64_t)(n[0] - 2) * (n[1] - 2) * (n[2] - 2);
+    if (!rows_dispatched()) return points < zm;
+    return n[0] - 2 <= (dtype == IGG_F64 ? 40 : 64) || points * 5 * elem_bytes(dtype) <= ((int64_t)96 << 20);
 }
 
-// The same for the flux form and its six arrays (160^3 FP32, 98 MB: 29.5 us
-// against 40.8 with the halo update; 200 x 180 x 100 FP64, 173 MB: 52.5
-// against 50.0).
-static bool flux_is_small(int dtype, int64_t points)
+// The same for the flux form: six arrays of at most 96 MiB (160^3 FP32, 98 MB:
+// 29.5 us against 40.8 with the halo update; 200 x 180 x 100 FP64, 173 MB: 52.5
+// against 50.0), and rows of up to 40 (FP64) or 88 cells at any size (34 x 800 x 500
+// FP64 196 against 204, on inputs that were not in the caches 197 against 220; 50 x
+// 700 x 400 193 against 167; 78 x 500 x 330 FP32 104 against 112 and 94 against
+// 114, 98 x 450 x 310 105 against 100 and 96 against 106).
+static bool flux_is_small(int dtype, const int n[3])
 {
-    const int64_t zm = zmarch_min_points();
-    return zm == kZmarchMinPoints ? points * 6 * elem_bytes(dtype) <= ((int64_t)96 << 20) : points < zm;
+    const int64_t zm = zmarch_min_points(), points = (int64_t)(n[0] - 2) * (n[1] - 2) * (n[2] - 2);
+    if (!rows_dispatched()) return points < zm;
+    return n[0] - 2 <= (dtype == IGG_F64 ? 40 : 88) || points * 6 * elem_bytes(dtype) <= ((int64_t)96 << 20);
 }
 
 // The step's launch arguments for rank r: its arrays, the fused x exchange
@@ -779,7 +787,7 @@ static int adjoint_step(int form, const igg_field *lam_n, const igg_field *lam_n
             a0.yz.kh = g.n[2] - g.ol[2];
         }
         if ((rc = timing_mark(s, 0))) return rc;
-        const bool small = adjoint_is_small(dt_, box_points(all));
+        const bool small = adjoint_is_small(dt_, g.n);
         if ((rc = small ? launch_adjoint_small(dt_, a0, s) : launch_adjoint_inner(dt_, a0, all, s))) return rc;
         if ((rc = timing_mark(s, 0))) return rc;
         if (g.timing) { g.t_launches++; g.t_points += box_points(all); }
@@ -891,7 +899,7 @@ static int flux_step_ranks(const igg_field *T2, const igg_field *T, const igg_fi
         // fields in one; slabs beside them only read their rows again (256^3
         // FP32 116 us with slabs on the helper stream, 107 without)
         if ((rc = timing_mark(s, 0))) return rc;
-        const bool small = flux_is_small(ty, box_points(all));
+        const bool small = flux_is_small(ty, g.n);
         if ((rc = small ? launch_flux_small(ty, args[0], s) : launch_flux_inner(ty, args[0], all, s))) return rc;
         if ((rc = timing_mark(s, 0))) return rc;
         if (g.timing) { g.t_launches++; g.t_points += box_points(all); }

@@ -383,8 +383,12 @@ static int run_fused_zmarch(const FluxArgs &a, const Box &b, hipStream_t s)
     z.b = b;
     z.g = FaceGeom{a.nx, a.ny, a.nz};
     z.xh = a.xh;
-    z.xa = (b.i0 / VEC) * VEC;
-    z.ntx = (b.i1 - z.xa + TW - 1) / TW;
+    RowTiles t = row_tiles(b, VEC, TW);
+    // (four FP64 outputs off their alignment cost more than one of several
+    // tiles: 258 x 300 x 170 on inputs out of the caches 147 us, 160 from i0)
+    if (sizeof(C) == 8 && t.n > 1) t = row_tiles(Box{b.i0 / VEC * VEC, b.i1, 0, 0, 0, 0}, VEC, TW);
+    z.xa = t.xa;
+    z.ntx = t.n;
     z.nty = (b.j1 - b.j0 + TH - 1) / TH;
     const int depth = b.k1 - b.k0;
     int zc = env_int_flux("IGG_FLUX_ZCHUNK", 0);
@@ -431,16 +435,26 @@ int launch_flux_boxes(int dtype, const FluxArgs &a, const Box *b, int nb, hipStr
 // were 3-12% slower (768^3 FP32 2147 us against 2093, 452 x 360 x 440 FP64 772
 // against 724; FP64 in 8 rows, 4 rows 740).  FP32 takes 128-cell rows where
 // they leave a fifth fewer lanes past the rows' ends (384^3 334 -> 289 us,
-// 301 x 257 x 203 122 -> 97).  Rows of any length are read and written in
-// vectors (255 x 190 x 131 FP32 52 -> 44 with the rows per thread).  Regions
-// below zmarch_min_points() take the box kernel.
+// 301 x 257 x 203 122 -> 97).  Tiles of 64 cells take rows of at most 64 (50 x
+// 700 x 400 FP64 257 -> 167, FP32 163 -> 118) and of 129 to 160, where they leave a
+// fourth of the lanes less (131 x 400 x 260 FP64 197 -> 149, FP32 114 -> 100; 194 x
+// 330 x 220 on inputs out of the caches FP64 167, 190 in tiles of 64).  Rows of
+// any length are read and written in vectors (255 x 190 x 131 FP32 52 -> 44 with
+// the rows per thread).  Regions below zmarch_min_points() and the shortest rows,
+// which leave most of a tile's lanes idle, take the box kernel (two ranks of 13
+// x 1500 x 600 FP64 792 us against 1020, FP32 374 against 532; 34 x 800 x 500 591
+// against 690, FP32 410 against 351).
 int launch_flux_inner(int dtype, const FluxArgs &a, const Box &b, hipStream_t s)
 {
-    if (box_count(b) < zmarch_min_points() || a.nx < 4) return launch_flux_boxes(dtype, a, &b, 1, s);
-    if (dtype == IGG_F64) return run_fused_zmarch<double, 2, 64, 8, 1>(a, b, s);
-    const int n = b.i1 - b.i0 / 4 * 4, wide = (n + 255) / 256 * 256, half = (n + 127) / 128 * 128;
-    return half * 5 <= wide * 4 ? run_fused_zmarch<float, 2, 64, 4, 1>(a, b, s)
-                                : run_fused_zmarch<float, 4, 64, 4, 1>(a, b, s);
+    const int row = b.i1 - b.i0;
+    if (box_count(b) < zmarch_min_points() || a.nx < 4 || (rows_dispatched() && row <= (dtype == IGG_F64 ? 40 : 20)))
+        return launch_flux_boxes(dtype, a, &b, 1, s);
+    const bool quarter = row <= 64 || (row > 128 && row <= 160);
+    if (dtype == IGG_F64)
+        return quarter ? run_fused_zmarch<double, 2, 32, 8, 1>(a, b, s) : run_fused_zmarch<double, 2, 64, 8, 1>(a, b, s);
+    if (quarter) return run_fused_zmarch<float, 2, 32, 8, 1>(a, b, s);
+    return narrow_pays(row_tiles(b, 4, 256), row_tiles(b, 2, 128)) ? run_fused_zmarch<float, 2, 64, 4, 1>(a, b, s)
+                                                                   : run_fused_zmarch<float, 4, 64, 4, 1>(a, b, s);
 }
 
 }  // namespace igg

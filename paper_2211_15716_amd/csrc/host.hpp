@@ -36,6 +36,10 @@ inline int64_t box_count(const Box &b)
 constexpr int64_t kZmarchMinPoints = (int64_t)1 << 21;
 int64_t zmarch_min_points();
 
+// Whether short rows have kernels of their own: unless the bound above is set,
+// which then alone decides.
+inline bool rows_dispatched() { return zmarch_min_points() == kZmarchMinPoints; }
+
 // Planes per z-march work-group: the largest of zc_max, zc_max/2, ... (at
 // least 4) that still gives `target` work-groups for `columns` tiles over
 // `depth` planes.  More, shorter marches balance the compute units better;
@@ -47,6 +51,21 @@ inline int zchunk_for_groups(int64_t columns, int depth, int zc_max, int64_t tar
     while (zc > 4 && columns * ((depth + zc - 1) / zc) < target) zc /= 2;
     return zc < 1 ? 1 : zc;
 }
+
+// Tiles of w points across the points i0 to i1 of a row, from x = xa on: at a
+// whole vector, or at i0 itself where that takes a tile less (130 x 400 x 260
+// FP64 adjoint 191 us -> 126, flux step 211 -> 130; 258 x 300 x 170 adjoint 134 ->
+// 121, FP32 flux step 85 -> 76).
+struct RowTiles {
+    int w, xa, n;
+};
+inline RowTiles row_tiles(const Box &b, int vec, int w)
+{
+    const int xa = b.i0 / vec * vec, n = (b.i1 - xa + w - 1) / w, m = (b.i1 - b.i0 + w - 1) / w;
+    return m < n ? RowTiles{w, b.i0, m} : RowTiles{w, xa, n};
+}
+// Whether tiles of b's width leave a fifth fewer lanes past the row's ends.
+inline bool narrow_pays(const RowTiles &a, const RowTiles &b) { return (int64_t)b.n * b.w * 5 <= (int64_t)a.n * a.w * 4; }
 
 // ------------------------------------------------------------------ state
 // The one implicit global grid of the process (the paper's calls take no
