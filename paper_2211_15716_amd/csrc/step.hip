@@ -937,7 +937,8 @@ static bool vec_ok(const StepArgs &a)
 // and 512^3; 16-byte loads over 512-point rows, or four rows per thread,
 // 6-19% slower at 512^3: more registers, fewer waves).
 // These shapes and work-group mappings measured fastest on MI355X at 512^3.
-// Rows shorter than a vector take one point per lane; regions below
+// Rows shorter than a vector, and FP32 rows of at most 64 points, take one point
+// per lane; regions below
 // zmarch_min_points() take the box kernel.
 // One inner-region launch, with the slab waves of yz (nyz boxes) run by
 // the launch's first work-groups when nyz > 0.
@@ -1008,7 +1009,9 @@ int launch_step_inner(int dtype, const StepArgs &a, const Box &b, hipStream_t s,
         return run_inner<double, 1, 64, 8, 2>(a, b, s, kInner, yz, nyz, pk);
     }
     if (dtype == IGG_F32) {
-        if (row_ok<float, 4>(a)) {
+        // (rows of at most 64 points: one per lane, two ranks of 66 x 600 x 350
+        // 109 -> 102 us, 20 x 1000 x 600 200 -> 187, 34 x 800 x 500 154 -> 158)
+        if (row_ok<float, 4>(a) && b.i1 - b.i0 > 64) {
             if (narrow_pays<float, 4>(b)) return run_inner<float, 4, 32, 8, 2>(a, b, s, kNarrowF32, yz, nyz, pk);
             // 256 x 32 tiles over 1024 threads of 2 rows for regions of at
             // least 2^26 points (4% faster than 256 x 16 tiles at 512^3)
