@@ -176,12 +176,17 @@ int ensure_device()
     // at every record, tens of microseconds per step at 512^3)
     IGG_HIP(hipEventCreateWithFlags(&g.ev_fork, hipEventDisableTiming | hipEventDisableSystemFence));
     IGG_HIP(hipEventCreateWithFlags(&g.ev_join, hipEventDisableTiming | hipEventDisableSystemFence));
-    // one plane of the largest field (n+1 per dimension) in FP64, rounded to 256 B
-    int64_t m0 = (int64_t)(g.n[1] + 1) * (g.n[2] + 1), m1 = (int64_t)(g.n[0] + 1) * (g.n[2] + 1),
-            m2 = (int64_t)(g.n[0] + 1) * (g.n[1] + 1);
-    int64_t cap = std::max(m0, std::max(m1, m2)) * 8;
-    g.halo_cap = (size_t)((cap + 255) / 256 * 256);
-    IGG_HIP(hipMalloc((void **)&g.halo_buf, g.halo_cap * 2 * 2 * IGG_MAX_FIELDS * g.nranks));
+    // Send and receive planes of one field each (one plane of the largest
+    // field, n+1 per dimension in FP64, rounded to 256 B).  One rank fills its
+    // halo from its own points and needs them only where the slabs pack (512^3:
+    // 67 MB).
+    if (g.nranks > 1 || g.slab_pack == 1) {
+        int64_t m0 = (int64_t)(g.n[1] + 1) * (g.n[2] + 1), m1 = (int64_t)(g.n[0] + 1) * (g.n[2] + 1),
+                m2 = (int64_t)(g.n[0] + 1) * (g.n[1] + 1);
+        int64_t cap = std::max(m0, std::max(m1, m2)) * 8;
+        g.halo_cap = (size_t)((cap + 255) / 256 * 256);
+        IGG_HIP(hipMalloc((void **)&g.halo_buf, g.halo_cap * 2 * 2 * IGG_MAX_FIELDS * g.nranks));
+    }
     {
         RedSlots first;  // allocated here, so that a reduction allocates nothing
         int rc;
@@ -599,13 +604,13 @@ static int step_ranks(const igg_field *T2, const igg_field *T, const igg_field *
     // exchange and unpack are one copy into the halo planes.
     if (P == 1 && g.fuse_x && g.slab_pack && g.periods[0] && g.periods[1] && g.periods[2]) {
         SlabPack pk{};
-        for (int d = 0; d < 2; ++d)
+        pk.direct = g.slab_pack == 2;
+        for (int d = 0; d < 2 && !pk.direct; ++d)
             for (int side = 0; side < 2; ++side) pk.send[d][side] = halo_send_plane(0, d, side);
         for (int d = 0; d < 3; ++d) {
             pk.ol[d] = g.ol[d];
             pk.per[d] = 1;
         }
-        pk.direct = g.slab_pack == 2;
         FusedStep ctx{dtype, args.data(), &pk};
         return run_split(
             split, dtype,
