@@ -20,8 +20,13 @@
  *     The caller owns every field.  Indices 0 and n-1 of each dimension are
  *     halo planes; 1..n-2 are the inner points.
  *   - `stream` is a hipStream_t (NULL = the null stream).  Calls are
- *     asynchronous and ordered with respect to it, except igg_reduce and
- *     diffusion_dt, which synchronise it to return a host value.
+ *     asynchronous and ordered with respect to it, except those that return
+ *     a value to the host: igg_reduce and diffusion_dt return when the value
+ *     has arrived, igg_adjoint_seed with a loss after synchronising the
+ *     stream.  Whatever was put into the stream before such a call is then
+ *     complete.  After igg_reduce and diffusion_dt the stream may still report
+ *     work for a moment (their own kernel, which has read its inputs, ending):
+ *     they synchronise it only where the value takes over 2 ms to arrive.
  *   - Argument checks all run on the host before any HIP call, so a call
  *     with invalid arguments fails without touching the GPU.
  *   - One grid exists per process (the paper's calls take no handle).  The
@@ -296,8 +301,8 @@ int diffusion_step_pair(const igg_field *T2, const igg_field *mid, const igg_fie
                         const igg_rounding *rnd, void *stream);
 
 /* Stable time step of Fig. 1: dt = min(dx^2,dy^2,dz^2)/lam/maximum(Ci)/6.1,
- * the maximum taken in FP64 over every point of Ci on the GPU.
- * Synchronises `stream`.  Errors: as igg_reduce, IGG_ERR_ARG for lam <= 0. */
+ * the maximum taken in FP64 over every point of Ci on the GPU.  Returns as
+ * igg_reduce does.  Errors: as igg_reduce, IGG_ERR_ARG for lam <= 0. */
 int diffusion_dt(const igg_field *Ci, double lam, double dx, double dy, double dz, double *dt,
                  void *stream);
 
@@ -411,8 +416,9 @@ int diffusion_flux_step_adjoint_ranks(const igg_field *lam_n, const igg_field *l
 /* FP64 reduction of one or two fields (IGG_RED_*); b is needed by
  * SUM_RATIO, HALF_SQDIFF, DOT and MAX_ABS_DIFF and ignored otherwise.  Any
  * element type; values are widened to FP64 before they are combined, in a
- * fixed order, so repeated calls give identical bits.  The result is written
- * to *out (host memory) after `stream` is synchronised.
+ * fixed order, so repeated calls give identical bits.  The call returns when
+ * the result is in *out (host memory); all work put into `stream` before it is
+ * complete then, the stream itself is not synchronised.
  * Errors: IGG_ERR_STATE, IGG_ERR_ARG, IGG_ERR_SIZE (a, b differ),
  * IGG_ERR_DTYPE, IGG_ERR_HIP. */
 int igg_reduce(int op, const igg_field *a, const igg_field *b, double *out, void *stream);
