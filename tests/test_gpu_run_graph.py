@@ -58,3 +58,70 @@ def test_a_captured_stream_records_the_steps(nt):
                 torch.cuda.synchronize()
                 assert torch.equal(out, want), (warm, replay)
                 assert torch.equal(T2 if out is T else T, before), (warm, replay)
+
+
+def _calls(T0, Ci, c, nt, split, want, before, calls=4):
+    """The same call again and again on the same buffers, their contents reset:
+    the first runs directly, the second captures, the others replay."""
+    T, T2 = T0.clone(), T0.clone()
+    launches = []
+    for call in range(calls):
+        T.copy_(T0)
+        T2.copy_(T0)
+        out = igg.diffusion_run(T, T2, Ci, *c, nt, split=split, graph=True)
+        launches.append(igg.timing_read()[1])
+        assert torch.ones(100, device="cuda").sum().item() == 100.0
+        assert (out is T) == (nt % 2 == 0)
+        assert torch.equal(out, want), (nt, call)
+        assert torch.equal(T2 if out is T else T, before), (nt, call)
+    return launches
+
+
+@pytest.mark.parametrize("n,split,dtype", [((32, 32, 32), (16, 2, 2), "f64"), ((66, 40, 36), (16, 2, 2), "f32"),
+                                           ((48, 40, 36), None, "f64"), ((160, 140, 120), (16, 2, 2), "f64"),
+                                           ((40, 34, 30), (16, 2, 2), "f16")])
+@pytest.mark.parametrize("periods", [(1, 1, 1), (0, 1, 0)])
+@pytest.mark.parametrize("sched", [None, "0", "1", "2", "3"])
+def test_repeated_calls_equal_single_steps(n, split, dtype, periods, sched, monkeypatch):
+    """Under every schedule, with pairs of steps (the default and schedule 3)
+    and without, nt below, at and above what one graph holds."""
+    if sched is not None:
+        monkeypatch.setenv("IGG_SCHEDULE", sched)
+    say("kept graph", n, split, dtype, periods, sched)
+    with grid(n, periods, zmarch_min=None):
+        T0, Ci, c = _problem(n, dtype)
+        assert igg.steps_per_launch(T0) == (2 if sched in (None, "3") else 1)
+        for nt in (2, 6, 7, 16, 37, 70):
+            want, before = _steps(T0, Ci, c, nt, split)
+            _calls(T0, Ci, c, nt, split, want, before)
+
+
+def test_calls_from_the_second_on_replay_a_graph():
+    """Kernel timing counts the launches made directly: all of the first call's,
+    and of the later ones only those a graph of 16 steps leaves over."""
+    n, nt = (40, 36, 34), 37
+    with grid(n, zmarch_min=None):
+        T0, Ci, c = _problem(n)
+        want, before = _steps(T0, Ci, c, nt)
+        igg.timing_enable(True)
+        assert _calls(T0, Ci, c, nt, None, want, before) == [nt] + 3 * [nt - 32]
+        igg.timing_enable(False)
+
+
+@pytest.mark.parametrize("where", ["side:300", "inner:300", "halo:300"])
+@pytest.mark.parametrize("pack", ["1", "2", "0"])
+def test_held_back_stream_in_the_kept_graph(where, pack, monkeypatch):
+    """A wait longer than a step put into one stream of the schedules, fork and
+    join inside the graph: replays give the bits of single steps."""
+    n, nt, split = (260, 140, 72), 7, (16, 2, 2)
+    monkeypatch.setenv("IGG_SLAB_PACK", pack)
+    monkeypatch.setenv("IGG_SCHEDULE", "2")
+    with grid(n, zmarch_min=None):
+        T0, Ci, c = _problem(n)
+        want, before = _steps(T0, Ci, c, nt, split)
+    monkeypatch.setenv("IGG_TEST_DELAY", where)
+    for sched in ("1", "0", "2", "3"):
+        monkeypatch.setenv("IGG_SCHEDULE", sched)
+        say("held back", where, "pack", pack, "schedule", sched)
+        with grid(n, zmarch_min=None):
+            _calls(T0, Ci, c, nt, split, want, before)
