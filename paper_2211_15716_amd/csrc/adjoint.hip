@@ -182,16 +182,10 @@ struct AdjTile {
 template <typename C, int VEC> struct AVec {
     typedef C type __attribute__((ext_vector_type(VEC)));
 };
-template <typename C> struct AVec<C, 1> {
-    typedef C type;
-};
 template <typename C, int VEC>
 __device__ __forceinline__ C el(const typename AVec<C, VEC>::type &v, int q)
 {
-    if constexpr (VEC == 1)
-        return v;
-    else
-        return v[q];
+    return v[q];
 }
 // element q of a vector for a q known only at run time
 template <typename C, int VEC>
@@ -206,27 +200,26 @@ __device__ __forceinline__ C el_dyn(const typename AVec<C, VEC>::type &v, int q)
 template <typename C, int VEC>
 __device__ __forceinline__ void set_el(typename AVec<C, VEC>::type &v, int q, C x)
 {
-    if constexpr (VEC == 1)
-        v = x;
-    else
-        v[q] = x;
+    v[q] = x;
 }
 
-// BX x TY threads, RY rows of VEC points per thread (the forward kernel's
-// tiling).  mu = Ci .* lp and T_n of plane k are staged in two
+// BX x TY threads, a row of VEC points per thread (the forward kernel's
+// tiling; the row stands in loops of one turn and its elements are read and
+// set through el and set_el: written out, the same arithmetic was scheduled
+// 2-7% slower, 512^3 FP64 1135 -> 1205 us).  mu = Ci .* lp and T_n of plane k are staged in two
 // double-buffered LDS tiles; lp, mu and T_n of planes k-1..k+1 (k+2 in
 // flight) sit in registers.  gCi is read and written once per point and
 // lam_n written once: non-temporal.  The products mu of the planes in
 // flight are formed when the queue rotates, after the plane's arithmetic,
 // so the loads are not waited for inside the plane (256^3: 3.5% faster).
-template <typename C, int VEC, int BX, int TY, int RY, int FORM, int WAVES>
+template <typename C, int VEC, int BX, int TY, int FORM, int WAVES>
 __global__ void __launch_bounds__(BX *TY) __attribute__((amdgpu_waves_per_eu(WAVES)))
 k_adj_zmarch(C *__restrict__ lam_n, const C *__restrict__ lp, const C *__restrict__ Tn,
              const C *__restrict__ Ci, C *__restrict__ gCi, AdjTile z, C a, C rx, C ry, C rz, C lamf)
 {
     using V = typename AVec<C, VEC>::type;
     static_assert(BX == 64, "a wave holds one thread row (the y/z image stores rely on it)");
-    constexpr int TW = BX * VEC, TH = TY * RY, LH = TH + 2, LW = TW + 2;
+    constexpr int RY = 1, TW = BX * VEC, TH = TY * RY, LH = TH + 2, LW = TW + 2;
     __shared__ C smu[2][LH][LW];
     __shared__ C sT[2][LH][LW];
     const int tx = threadIdx.x % BX, ty = threadIdx.x / BX;
@@ -373,12 +366,12 @@ k_adj_zmarch(C *__restrict__ lam_n, const C *__restrict__ lp, const C *__restric
                 const C m0 = el<C, VEC>(mc[r], q), t0 = el<C, VEC>(tc[r], q);
                 const C mxm = (q == 0) ? smu[buf][lr][lc_ - 1] : el<C, VEC>(mc[r], q - 1);
                 const C mxp = (q == VEC - 1) ? smu[buf][lr][lc_ + 1] : el<C, VEC>(mc[r], q + 1);
-                const C mym = (r == 0) ? smu[buf][lr - 1][lc_] : el<C, VEC>(mc[r - 1], q);
-                const C myp = (r == RY - 1) ? smu[buf][lr + 1][lc_] : el<C, VEC>(mc[r + 1], q);
+                const C mym = smu[buf][lr - 1][lc_];
+                const C myp = smu[buf][lr + 1][lc_];
                 const C txm = (q == 0) ? sT[buf][lr][lc_ - 1] : el<C, VEC>(tc[r], q - 1);
                 const C txp = (q == VEC - 1) ? sT[buf][lr][lc_ + 1] : el<C, VEC>(tc[r], q + 1);
-                const C tym = (r == 0) ? sT[buf][lr - 1][lc_] : el<C, VEC>(tc[r - 1], q);
-                const C typ = (r == RY - 1) ? sT[buf][lr + 1][lc_] : el<C, VEC>(tc[r + 1], q);
+                const C tym = sT[buf][lr - 1][lc_];
+                const C typ = sT[buf][lr + 1][lc_];
                 C ln, gg = el<C, VEC>(gc[r], q);
                 adj_cell<C, FORM>(el<C, VEC>(lc[r], q), m0, mxm, mxp, mym, myp, el<C, VEC>(mm[r], q),
                                   el<C, VEC>(mp[r], q), t0, txm, txp, tym, typ, el<C, VEC>(tm[r], q),
@@ -386,13 +379,11 @@ k_adj_zmarch(C *__restrict__ lam_n, const C *__restrict__ lp, const C *__restric
                 set_el<C, VEC>(lo, q, ln);
                 set_el<C, VEC>(go, q, gg);
             }
-            if constexpr (RY == 1) {
-                // the loads are waited for here: a wait after the stores
-                // would wait for the stores too
-                __asm__ volatile("" : "+v"(cn[r]), "+v"(ln2[r]), "+v"(tn[r]), "+v"(gn[r]));
-                __asm__ volatile("" : "+v"(hc_n[r]), "+v"(hl_n[r]), "+v"(hT_n[r]));
-                __asm__ volatile("" : "+v"(yc_n), "+v"(yl_n), "+v"(yT_n));
-            }
+            // the loads are waited for here: a wait after the stores would
+            // wait for the stores too
+            __asm__ volatile("" : "+v"(cn[r]), "+v"(ln2[r]), "+v"(tn[r]), "+v"(gn[r]));
+            __asm__ volatile("" : "+v"(hc_n[r]), "+v"(hl_n[r]), "+v"(hT_n[r]));
+            __asm__ volatile("" : "+v"(yc_n), "+v"(yl_n), "+v"(yT_n));
             const int64_t p = (int64_t)k * sxy + col[r];
             if (xin && i >= z.b.i0 && i + VEC <= z.b.i1) {
                 const uint32_t ob = (uint32_t)(col[r] * (int64_t)sizeof(C));
@@ -470,10 +461,10 @@ int launch_adjoint_boxes(int dtype, const AdjArgs &a, const Box *b, int nb, hipS
     return dtype == IGG_F64 ? run_boxes<double, 0>(a, b, nb, s) : run_boxes<float, 0>(a, b, nb, s);
 }
 
-template <typename C, int VEC, int BX, int TY, int RY, int FORM, int WAVES = 1>
+template <typename C, int VEC, int BX, int TY, int FORM, int WAVES = 1>
 static int run_zmarch(const AdjArgs &a, const Box &b, hipStream_t s)
 {
-    constexpr int TW = BX * VEC, TH = TY * RY;
+    constexpr int TW = BX * VEC, TH = TY;
     AdjTile z;
     z.b = b;
     z.nx = a.nx;
@@ -502,7 +493,7 @@ static int run_zmarch(const AdjArgs &a, const Box &b, hipStream_t s)
     z.main = (int)blocks;
     z.ed = a.ed;
     blocks += (a.ed.total + BX * TY - 1) / (BX * TY);
-    hipLaunchKernelGGL((k_adj_zmarch<C, VEC, BX, TY, RY, FORM, WAVES>), dim3((unsigned)blocks), dim3(BX * TY), 0, s,
+    hipLaunchKernelGGL((k_adj_zmarch<C, VEC, BX, TY, FORM, WAVES>), dim3((unsigned)blocks), dim3(BX * TY), 0, s,
                        (C *)a.lam_n, (const C *)a.lp, (const C *)a.Tn, (const C *)a.Ci, (C *)a.gCi, z,
                        (C)a.a, (C)a.rx, (C)a.ry, (C)a.rz, (C)a.lamf);
     IGG_HIP(hipGetLastError());
@@ -528,18 +519,18 @@ static int adjoint_inner(int dtype, const AdjArgs &a, const Box &b, hipStream_t 
     if (dtype == IGG_F64)
     {
         const int waves = env_int("IGG_ADJ_WAVES", 4);
-        if (waves != 4) return run_zmarch<double, 2, 64, 4, 1, FORM>(a, b, s);
+        if (waves != 4) return run_zmarch<double, 2, 64, 4, FORM>(a, b, s);
         // regions of 2^26 points and more: 16-row tiles over 1024 threads
         // (512^3: 4-10% faster than 4 rows on three boxes; 384^3 and 256^3
         // keep 4 rows, equal or faster there)
-        if (box_count(b) >= ((int64_t)1 << 26)) return run_zmarch<double, 2, 64, 16, 1, FORM, 4>(a, b, s);
-        return run_zmarch<double, 2, 64, 4, 1, FORM, 4>(a, b, s);
+        if (box_count(b) >= ((int64_t)1 << 26)) return run_zmarch<double, 2, 64, 16, FORM, 4>(a, b, s);
+        return run_zmarch<double, 2, 64, 4, FORM, 4>(a, b, s);
     }
     // 128-point rows where they leave a fifth fewer lanes past the rows' ends
     // (301 x 257 x 203 117 -> 94 us, 384^3 305 -> 267; where both fit alike
     // 512^3 600 against 628, 401 x 300 x 250 180 against 193)
-    return narrow_pays(row_tiles(b, 4, 256), row_tiles(b, 2, 128)) ? run_zmarch<float, 2, 64, 4, 1, FORM>(a, b, s)
-                                                                   : run_zmarch<float, 4, 64, 4, 1, FORM>(a, b, s);
+    return narrow_pays(row_tiles(b, 4, 256), row_tiles(b, 2, 128)) ? run_zmarch<float, 2, 64, 4, FORM>(a, b, s)
+                                                                   : run_zmarch<float, 4, 64, 4, FORM>(a, b, s);
 }
 
 template <typename C, int FORM>

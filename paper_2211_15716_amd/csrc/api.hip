@@ -304,7 +304,7 @@ static int check_spacings(double lam, double dt, double dx, double dy, double dz
 // (where the caller provides fused_launch) runs the slabs and the inner
 // region in one launch whose first work-groups take the slabs, and then
 // whatever halo update is left.  By default a caller with fused_launch (the
-// one-rank periodic step, whose slab kernel stores the y and z halo itself)
+// one-rank step, whose slab waves store the y and z halo themselves)
 // takes schedule 3: at 512^3 it is 0.8-2.6% faster than the unsplit step
 // while schedules 1 and 2 are slower, the slabs beside the inner launch
 // costing more bandwidth than the update they hide.  Otherwise large inner

@@ -146,26 +146,6 @@ template <typename C, int VEC> struct FVec {
     typedef C type __attribute__((ext_vector_type(VEC)));
     typedef C mem __attribute__((ext_vector_type(VEC), aligned(sizeof(C))));  // rows start at any element
 };
-template <typename C> struct FVec<C, 1> {
-    typedef C type;
-    typedef C mem;
-};
-template <typename C, int VEC>
-__device__ __forceinline__ C fel(const typename FVec<C, VEC>::type &v, int q)
-{
-    if constexpr (VEC == 1)
-        return v;
-    else
-        return v[q];
-}
-template <typename C, int VEC>
-__device__ __forceinline__ void fset(typename FVec<C, VEC>::type &v, int q, C x)
-{
-    if constexpr (VEC == 1)
-        v = x;
-    else
-        v[q] = x;
-}
 
 struct FluxTile {
     Box b;
@@ -174,21 +154,22 @@ struct FluxTile {
     FluxXH xh;
 };
 
-// z-march of the fused step: BX x TY threads, RY rows of VEC cells each;
-// T of planes k-1, k, k+1 (k+2 in flight) in registers, plane k in a
+// z-march of the fused step: BX x TY threads, a row of VEC cells each; T of
+// planes k-1, k, k+1 (k+2 in flight) in registers, plane k in a
 // double-buffered LDS tile for the x and y neighbours (the forward step
-// kernel's scheme).  T2, qy, qz leave as vectors where the cells of a
-// vector all lie in the box; qx rows are nx+1 long, so its stores are per
-// cell.
-template <typename C, int VEC, int BX, int TY, int RY, int WAVES>
-__global__ void __launch_bounds__(BX *TY) __attribute__((amdgpu_waves_per_eu(WAVES)))
+// kernel's scheme).  The four outputs leave as vectors where the cells of a
+// vector all lie in the box.  (Its one row per thread stands in loops of one
+// turn: without them the compiler copies the plane's body for a chunk's last
+// plane, 768^3 FP32 2113 us against 2087.)
+template <typename C, int VEC, int BX, int TY>
+__global__ void __launch_bounds__(BX *TY)
 k_flux_fused_zmarch(C *__restrict__ T2, C *__restrict__ qx, C *__restrict__ qy, C *__restrict__ qz,
                     const C *__restrict__ T, const C *__restrict__ Ci, FluxTile z, C lam, C dt, C rdx, C rdy,
                     C rdz)
 {
     using V = typename FVec<C, VEC>::type;
     using M = typename FVec<C, VEC>::mem;
-    constexpr int TW = BX * VEC, TH = TY * RY, LH = TH + 2, LW = TW + 2;
+    constexpr int RY = 1, TW = BX * VEC, TH = TY * RY, LH = TH + 2, LW = TW + 2;
     __shared__ C tile[2][LH][LW];
     const int tx = threadIdx.x % BX, ty = threadIdx.x / BX;
     int64_t gidx = blockIdx.x;
@@ -271,12 +252,12 @@ k_flux_fused_zmarch(C *__restrict__ T2, C *__restrict__ qx, C *__restrict__ qy, 
 #pragma unroll
         for (int r = 0; r < RY; ++r) {
 #pragma unroll
-            for (int q = 0; q < VEC; ++q) tile[buf][1 + ty * RY + r][1 + tx * VEC + q] = fel<C, VEC>(tc[r], q);
+            for (int q = 0; q < VEC; ++q) tile[buf][1 + ty * RY + r][1 + tx * VEC + q] = tc[r][q];
             if (own_h) tile[buf][1 + ty * RY + r][hcol] = hx[r];
         }
         if (hy) {
 #pragma unroll
-            for (int q = 0; q < VEC; ++q) tile[buf][hyrow][1 + tx * VEC + q] = fel<C, VEC>(yh, q);
+            for (int q = 0; q < VEC; ++q) tile[buf][hyrow][1 + tx * VEC + q] = yh[q];
         }
         __syncthreads();
 #pragma unroll
@@ -288,30 +269,26 @@ k_flux_fused_zmarch(C *__restrict__ T2, C *__restrict__ qx, C *__restrict__ qy, 
 #pragma unroll
             for (int q = 0; q < VEC; ++q) {
                 const int lc = 1 + tx * VEC + q;
-                const C t0 = fel<C, VEC>(tc[r], q);
-                const C txm = (q == 0) ? tile[buf][lr][lc - 1] : fel<C, VEC>(tc[r], q - 1);
-                const C txp = (q == VEC - 1) ? tile[buf][lr][lc + 1] : fel<C, VEC>(tc[r], q + 1);
-                const C tym = (r == 0) ? tile[buf][lr - 1][lc] : fel<C, VEC>(tc[r - 1], q);
-                const C typ = (r == RY - 1) ? tile[buf][lr + 1][lc] : fel<C, VEC>(tc[r + 1], q);
+                const C t0 = tc[r][q];
+                const C txm = (q == 0) ? tile[buf][lr][lc - 1] : tc[r][q - 1];
+                const C txp = (q == VEC - 1) ? tile[buf][lr][lc + 1] : tc[r][q + 1];
+                const C tym = tile[buf][lr - 1][lc];
+                const C typ = tile[buf][lr + 1][lc];
                 const C qxl = face_flux<C>(t0, txm, lam, rdx), qxu = face_flux<C>(txp, t0, lam, rdx);
                 const C qyl = face_flux<C>(t0, tym, lam, rdy), qyu = face_flux<C>(typ, t0, lam, rdy);
-                const C qzl = face_flux<C>(t0, fel<C, VEC>(tm[r], q), lam, rdz);
-                const C qzu = face_flux<C>(fel<C, VEC>(tp[r], q), t0, lam, rdz);
-                const C v2 =
-                    fma_(-dt * fel<C, VEC>(ci[r], q), flux_div<C>(qxl, qxu, qyl, qyu, qzl, qzu, rdx, rdy, rdz), t0);
-                fset<C, VEC>(o2, q, v2);
-                fset<C, VEC>(oy, q, qyl);
-                fset<C, VEC>(oz, q, qzl);
+                const C qzl = face_flux<C>(t0, tm[r][q], lam, rdz);
+                const C qzu = face_flux<C>(tp[r][q], t0, lam, rdz);
+                o2[q] = fma_(-dt * ci[r][q], flux_div<C>(qxl, qxu, qyl, qyu, qzl, qzu, rdx, rdy, rdz), t0);
+                oy[q] = qyl;
+                oz[q] = qzl;
                 oxl[q] = qxl;
                 oxu[q] = qxu;
                 oyu[q] = qyu;
                 ozu[q] = qzu;
             }
-            if constexpr (RY == 1) {
-                // the loads are waited for here: a wait after the stores
-                // would wait for the stores too
-                __asm__ volatile("" : "+v"(tn[0]), "+v"(cn[0]), "+v"(hn[0]), "+v"(yn));
-            }
+            // the loads are waited for here: a wait after the stores would
+            // wait for the stores too
+            __asm__ volatile("" : "+v"(tn[0]), "+v"(cn[0]), "+v"(hn[0]), "+v"(yn));
             const int j = jr[r];
             const int64_t p = (int64_t)k * sxy + col[r];
             const int64_t px = i + (int64_t)(nx + 1) * (j + (int64_t)ny * k);
@@ -323,7 +300,7 @@ k_flux_fused_zmarch(C *__restrict__ T2, C *__restrict__ qx, C *__restrict__ qy, 
                 __builtin_nontemporal_store(oz, reinterpret_cast<M *>(qz + p));
                 V ox;
 #pragma unroll
-                for (int q = 0; q < VEC; ++q) fset<C, VEC>(ox, q, oxl[q]);
+                for (int q = 0; q < VEC; ++q) ox[q] = oxl[q];
                 *reinterpret_cast<M *>(qx + px) = ox;
             }
 #pragma unroll
@@ -331,16 +308,15 @@ k_flux_fused_zmarch(C *__restrict__ T2, C *__restrict__ qx, C *__restrict__ qy, 
                 const int ii = i + q;
                 if (ii < z.b.i0 || ii >= z.b.i1) continue;
                 if (!full) {
-                    T2[p + q] = fel<C, VEC>(o2, q);
-                    qy[py + q] = fel<C, VEC>(oy, q);
-                    qz[p + q] = fel<C, VEC>(oz, q);
+                    T2[p + q] = o2[q];
+                    qy[py + q] = oy[q];
+                    qz[p + q] = oz[q];
                     qx[px + q] = oxl[q];
                 }
                 if (ii == nx - 2 || j == ny - 2 || k == z.g.nz - 2 ||
                     ((z.xh.on_lo || z.xh.on_hi) && (ii <= z.xh.ol || ii >= nx - z.xh.ol)))
-                    flux_extra_stores<C>(T2, qx, qy, qz, ii, j, k, p + q, px + q, py + q, z.g, z.xh,
-                                         fel<C, VEC>(o2, q), oxl[q], oxu[q], fel<C, VEC>(oy, q), oyu[q],
-                                         fel<C, VEC>(oz, q), ozu[q]);
+                    flux_extra_stores<C>(T2, qx, qy, qz, ii, j, k, p + q, px + q, py + q, z.g, z.xh, o2[q], oxl[q],
+                                         oxu[q], oy[q], oyu[q], oz[q], ozu[q]);
             }
         }
 #pragma unroll
@@ -375,10 +351,10 @@ static int run_fused_boxes(const FluxArgs &a, const Box *b, int nb, hipStream_t 
     return IGG_OK;
 }
 
-template <typename C, int VEC, int BX, int TY, int RY, int WAVES = 1>
+template <typename C, int VEC, int BX, int TY>
 static int run_fused_zmarch(const FluxArgs &a, const Box &b, hipStream_t s)
 {
-    constexpr int TW = BX * VEC, TH = TY * RY;
+    constexpr int TW = BX * VEC, TH = TY;
     FluxTile z{};
     z.b = b;
     z.g = FaceGeom{a.nx, a.ny, a.nz};
@@ -399,7 +375,7 @@ static int run_fused_zmarch(const FluxArgs &a, const Box &b, hipStream_t s)
     z.remap = env_int_flux("IGG_FLUX_REMAP", 2);
     const int64_t blocks = (int64_t)z.ntx * z.nty * ((depth + zc - 1) / zc);
     if (blocks <= 0) return IGG_OK;
-    hipLaunchKernelGGL((k_flux_fused_zmarch<C, VEC, BX, TY, RY, WAVES>), dim3((unsigned)blocks), dim3(BX * TY), 0, s,
+    hipLaunchKernelGGL((k_flux_fused_zmarch<C, VEC, BX, TY>), dim3((unsigned)blocks), dim3(BX * TY), 0, s,
                        (C *)a.T2, (C *)a.qx, (C *)a.qy, (C *)a.qz, (const C *)a.T, (const C *)a.Ci, z, (C)a.lam,
                        (C)a.dt, (C)a.rdx, (C)a.rdy, (C)a.rdz);
     IGG_HIP(hipGetLastError());
@@ -451,10 +427,10 @@ int launch_flux_inner(int dtype, const FluxArgs &a, const Box &b, hipStream_t s)
         return launch_flux_boxes(dtype, a, &b, 1, s);
     const bool quarter = row <= 64 || (row > 128 && row <= 160);
     if (dtype == IGG_F64)
-        return quarter ? run_fused_zmarch<double, 2, 32, 8, 1>(a, b, s) : run_fused_zmarch<double, 2, 64, 8, 1>(a, b, s);
-    if (quarter) return run_fused_zmarch<float, 2, 32, 8, 1>(a, b, s);
-    return narrow_pays(row_tiles(b, 4, 256), row_tiles(b, 2, 128)) ? run_fused_zmarch<float, 2, 64, 4, 1>(a, b, s)
-                                                                   : run_fused_zmarch<float, 4, 64, 4, 1>(a, b, s);
+        return quarter ? run_fused_zmarch<double, 2, 32, 8>(a, b, s) : run_fused_zmarch<double, 2, 64, 8>(a, b, s);
+    if (quarter) return run_fused_zmarch<float, 2, 32, 8>(a, b, s);
+    return narrow_pays(row_tiles(b, 4, 256), row_tiles(b, 2, 128)) ? run_fused_zmarch<float, 2, 64, 4>(a, b, s)
+                                                                   : run_fused_zmarch<float, 4, 64, 4>(a, b, s);
 }
 
 }  // namespace igg

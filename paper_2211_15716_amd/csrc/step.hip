@@ -109,9 +109,9 @@ k_step_boxes(S *__restrict__ T2, const S *__restrict__ T, const S *__restrict__ 
 // ends from memory.  No LDS and no barriers: the waves of a work-group are
 // independent.
 //
-// With `pack` set (one rank, every dimension periodic: the process is its
-// own neighbour) the kernel also writes the y and z send planes of the halo
-// update as it computes their points: the pack of the update fused into the
+// With `pack` set (one rank, its own neighbour in every periodic dimension)
+// the kernel also writes the y and z send planes of the halo update, in
+// periodic dimensions, as it computes their points: the pack of the update fused into the
 // stores, as the x exchange is.  An entry of a send plane that lies in an
 // x halo column, or in a halo row of the plane's other dimension, holds the
 // image of an inner point (the value the dimension-ordered update would
@@ -912,9 +912,10 @@ static int run_zmarch(const StepArgs &a, const Box *b, int nbox, hipStream_t s, 
 static bool aligned(const void *p, int bytes) { return ((uintptr_t)p % (uintptr_t)bytes) == 0; }
 
 // Rows of any length and alignment are read in vectors, which may run over
-// into the next row but not beyond it.  Against one point per lane: 511^3
-// FP64 672 -> 567 us, FP32 373 -> 303, FP16 with stochastic rounding 322 ->
-// 193; 401 x 300 x 250 161 -> 150, 92 -> 85, 102 -> 64.
+// into the next row but not beyond it (FP64: rows have 3 points at least).
+// Against one point per lane: 511^3 FP64 672 -> 567 us, FP32 373 -> 303, FP16
+// with stochastic rounding 322 -> 193; 401 x 300 x 250 161 -> 150, 92 -> 85, 102
+// -> 64.
 template <typename S, int VEC>
 static bool row_ok(const StepArgs &a)
 {
@@ -937,8 +938,8 @@ static bool vec_ok(const StepArgs &a)
 // and 512^3; 16-byte loads over 512-point rows, or four rows per thread,
 // 6-19% slower at 512^3: more registers, fewer waves).
 // These shapes and work-group mappings measured fastest on MI355X at 512^3.
-// Rows shorter than a vector, and FP32 rows of at most 64 points, take one point
-// per lane; regions below
+// Rows shorter than a vector (FP32 and FP16) and FP32 rows of at most 64 points
+// take one point per lane; regions below
 // zmarch_min_points() take the box kernel.
 // One inner-region launch, with the slab waves of yz (nyz boxes) run by
 // the launch's first work-groups when nyz > 0.
@@ -993,20 +994,17 @@ int launch_step_inner(int dtype, const StepArgs &a, const Box &b, hipStream_t s,
         return box_count(b) > 0 ? launch_step_boxes(dtype, a, &b, 1, s) : IGG_OK;
     }
     if (dtype == IGG_F64) {
-        if (row_ok<double, 2>(a)) {
-            if (narrow_pays<double, 2>(b)) return run_inner<double, 2, 32, 8, 2>(a, b, s, kInner, yz, nyz, pk);
-            // a 128 x 16 tile over 512 threads of 2 rows (108 registers, 4
-            // waves per SIMD): 2-3% faster at 256^3 and 384^3 than 4 rows per
-            // thread, 5% slower at 512^3, so regions below 2^26 points take it
-            static const char *kMidEnv = "IGG_FP64_MIDTILE_MAX_POINTS";
-            const char *e = getenv(kMidEnv);
-            const int64_t mid_max = (e && *e) ? atoll(e) : ((int64_t)1 << 26);
-            if (box_count(b) < mid_max) return run_inner<double, 2, 64, 8, 2>(a, b, s, kInner, yz, nyz, pk);
-            // 32-row tiles over 512 threads of 4 rows: fewer y-halo rows per
-            // point than 16-row tiles of 256 threads (512^3: 0.8% faster)
-            return run_inner<double, 2, 64, 8, 4>(a, b, s, kInner, yz, nyz, pk);
-        }
-        return run_inner<double, 1, 64, 8, 2>(a, b, s, kInner, yz, nyz, pk);
+        if (narrow_pays<double, 2>(b)) return run_inner<double, 2, 32, 8, 2>(a, b, s, kInner, yz, nyz, pk);
+        // a 128 x 16 tile over 512 threads of 2 rows (108 registers, 4
+        // waves per SIMD): 2-3% faster at 256^3 and 384^3 than 4 rows per
+        // thread, 5% slower at 512^3, so regions below 2^26 points take it
+        static const char *kMidEnv = "IGG_FP64_MIDTILE_MAX_POINTS";
+        const char *e = getenv(kMidEnv);
+        const int64_t mid_max = (e && *e) ? atoll(e) : ((int64_t)1 << 26);
+        if (box_count(b) < mid_max) return run_inner<double, 2, 64, 8, 2>(a, b, s, kInner, yz, nyz, pk);
+        // 32-row tiles over 512 threads of 4 rows: fewer y-halo rows per
+        // point than 16-row tiles of 256 threads (512^3: 0.8% faster)
+        return run_inner<double, 2, 64, 8, 4>(a, b, s, kInner, yz, nyz, pk);
     }
     if (dtype == IGG_F32) {
         // (rows of at most 64 points: one per lane, two ranks of 66 x 600 x 350
@@ -1106,10 +1104,7 @@ int launch_step_slabs(int dtype, const StepArgs &a, const Split &sp, const SlabP
         if (sp.kind[q] == 1) yz[n++] = sp.boundary[q];
     if (n == 0) return IGG_OK;
     if (n > 4) return fail(IGG_ERR_ARG, "internal: more than four y/z slabs");
-    if (dtype == IGG_F64) {
-        if (row_ok<double, 2>(a)) return run_slabs<double, 2>(a, yz, n, pk, s);
-        return run_slabs<double, 1>(a, yz, n, pk, s);
-    }
+    if (dtype == IGG_F64) return run_slabs<double, 2>(a, yz, n, pk, s);
     if (dtype == IGG_F32) {
         if (row_ok<float, 4>(a)) return run_slabs<float, 4>(a, yz, n, pk, s);
         return run_slabs<float, 1>(a, yz, n, pk, s);
