@@ -427,22 +427,25 @@ static bool step_is_small(int dtype, const int n[3])
     return n[1] <= 6 || points * 3 * elem_bytes(dtype) <= ((int64_t)(dtype == IGG_F16 ? 25 : 90) << 20);
 }
 
-// The same for the adjoint: five arrays of at most 84 MiB in FP64 and 96 MiB in
-// FP32 (128^3 FP64, 76 MiB: 23.4 us against 32.1; 160^3 FP32, 75 MiB: 19.9
-// against 30.3).  FP64 from 84 to 96 MiB is 2-25% faster than with the z-march
-// where all five arrays are in the caches, but 3-7% slower in a reverse sweep of
-// single steps, whose states T_n come from snapshots that are not, and 9-25% on
-// inputs of which none is; FP32 there 19-40% faster, as fast and 4-8% slower.  And
-// rows of up to 40 (FP64) or 64 points at any size, which leave z-march tiles'
-// lanes idle (42 x 700 x 450 FP64 188 against 196, 46 x 700 x 420 189 against 188;
-// 66 x 600 x 350 FP32 87 against 92, 72 x 600 x 320 89 against 86; 13 x 1500 x 600
-// 163 against 456 and 79 against 291).
+// The same for the adjoint: five arrays of at most 96 MiB (128^3 FP64, 76 MiB:
+// 23.4 us against 32.1; 160^3 FP32, 75 MiB: 19.9 against 30.3), but 84 MiB in FP64
+// where the z-march's tiles leave fewer than a third of their lanes idle.  There,
+// from 84 MiB on, this kernel is 2-25% faster with all five arrays in the caches,
+// but 3-7% slower in a reverse sweep of single steps, whose states T_n come from
+// snapshots that are not, and 9-25% on inputs of which none is; with more lanes
+// idle it is 26-39% faster and 9% slower to 6% faster (136 x 104 x 184 28 against 39
+// us, 49.5 against 52.6); FP32 19-40% faster, as fast and 4-8% slower.  And rows of
+// up to 40 (FP64) or 64 points at any size, which leave z-march tiles' lanes idle
+// (42 x 700 x 450 FP64 188 against 196, 46 x 700 x 420 189 against 188; 66 x 600 x
+// 350 FP32 87 against 92, 72 x 600 x 320 89 against 86; 13 x 1500 x 600 163 against
+// 456 and 79 against 291).
 static bool adjoint_is_small(int dtype, const int n[3])
 {
     const int64_t zm = zmarch_min_points(), points = (int64_t)(n[0] - 2) * (n[1] - 2) * (n[2] - 2);
     if (!rows_dispatched()) return points < zm;
-    return n[0] - 2 <= (dtype == IGG_F64 ? 40 : 64) ||
-           points * 5 * elem_bytes(dtype) <= ((int64_t)(dtype == IGG_F64 ? 84 : 96) << 20);
+    const RowTiles t = row_tiles(Box{1, n[0] - 1, 1, n[1] - 1, 1, n[2] - 1}, 2, 128);
+    const bool full = dtype == IGG_F64 && (int64_t)3 * (n[0] - 2) > (int64_t)2 * t.n * t.w;
+    return n[0] - 2 <= (dtype == IGG_F64 ? 40 : 64) || points * 5 * elem_bytes(dtype) <= ((int64_t)(full ? 84 : 96) << 20);
 }
 
 // The same for the flux form: six arrays of at most 96 MiB (160^3 FP32, 98 MB:

@@ -78,13 +78,14 @@ def test_short_rows_take_the_small_grid_kernel(form, dtype, row):
             assert ("_small" in name) == (more == 0) and ("_zmarch" in name) == (more == 1), name
 
 
-# the last plane with which five arrays of inner points fit 84 MiB (FP64) or 96
-# (FP32), and one plane more
-@pytest.mark.parametrize("dtype,nz", [(torch.float64, 136), (torch.float32, 309)])
+# the last plane with which five arrays of inner points fit 84 MiB (FP64 in rows
+# that fill tiles of 128 points) or 96, and one plane more
+@pytest.mark.parametrize("dtype,nx,nz", [(torch.float64, 130, 136), (torch.float64, 136, 148),
+                                         (torch.float32, 130, 309)])
 @pytest.mark.parametrize("step", [igg.diffusion_step_adjoint, igg.diffusion_flux_step_adjoint])
-def test_adjoint_of_the_small_grid_bound(step, dtype, nz):
+def test_adjoint_of_the_small_grid_bound(step, dtype, nx, nz):
     for more in (0, 1):
-        n = (130, 130, nz + more)
+        n = (nx, 130, nz + more)
         say("adjoint at the small-grid bound", dtype, n)
         with grid(n, (1, 1, 1), zmarch_min=None):
             F, c = _fields(n, dtype)
