@@ -44,11 +44,12 @@ inline bool rows_dispatched() { return zmarch_min_points() == kZmarchMinPoints; 
 // least 4) that still gives `target` work-groups for `columns` tiles over
 // `depth` planes.  More, shorter marches balance the compute units better;
 // the planes two chunks share are read at about the same time, mostly from
-// cache, so short chunks add little traffic.
+// cache, so short chunks add little traffic (FP64 adjoint of fewer than 2048
+// work-groups of 6 planes: 4 planes 2.5-3.5% faster than 3, 110 grids).
 inline int zchunk_for_groups(int64_t columns, int depth, int zc_max, int64_t target = 2048)
 {
     int zc = zc_max;
-    while (zc > 4 && columns * ((depth + zc - 1) / zc) < target) zc /= 2;
+    while (zc > 4 && columns * ((depth + zc - 1) / zc) < target) zc = std::max(zc / 2, 4);
     return zc < 1 ? 1 : zc;
 }
 

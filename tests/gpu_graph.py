@@ -16,6 +16,11 @@ VERBOSE = 1       # hipGraphDebugDotFlagsVerbose
 
 def kernels(call):
     """Names (mangled) of the kernels `call` launches on the current stream."""
+    return [name for name, _ in launches(call)]
+
+
+def launches(call):
+    """(mangled name, work-groups in x) of the kernels `call` launches."""
     hip = igg.load()  # resolves the runtime's symbols too
     stream = torch.cuda.Stream()
     handle, graph = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p()
@@ -36,4 +41,5 @@ def kernels(call):
     finally:
         assert hip.hipGraphDestroy(graph) == 0
         os.unlink(path)
-    return re.findall(r"\{ID \| \d+ \| (\S+?)\\<", text)
+    found = re.findall(r"\{ID \| \d+ \| (\S+?)\\<\\<\\<\((\d+),", text)
+    return [(name, int(groups)) for name, groups in found]

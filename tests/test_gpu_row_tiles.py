@@ -8,7 +8,7 @@ from paper_2211_15716_amd import diffusion, igg
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 from gpu_common import grid, say  # noqa: E402
-from gpu_graph import kernels  # noqa: E402
+from gpu_graph import kernels, launches  # noqa: E402
 
 
 def _fields(n, dtype, ranks=1):
@@ -93,6 +93,20 @@ def test_adjoint_of_the_small_grid_bound(step, dtype, nx, nz):
             step(*F, *c)
             name = kernels(lambda: step(*F, *c))[0]
             assert ("_small" in name) == (more == 0) and ("_zmarch" in name) == (more == 1), name
+
+
+# 32 tiles of 128 x 4 points over 256 planes: fewer than 2048 work-groups of 6
+# planes, so the least chunk, 4 planes
+@pytest.mark.parametrize("step", [igg.diffusion_step_adjoint, igg.diffusion_flux_step_adjoint])
+def test_adjoint_marches_four_planes_at_least(step):
+    n = (130, 130, 258)
+    say("adjoint chunks", n)
+    with grid(n, (1, 1, 1), zmarch_min=None):
+        F, c = _fields(n, torch.float64)
+        F = [f[0] for f in F]
+        step(*F, *c)
+        name, groups = launches(lambda: step(*F, *c))[0]
+        assert "k_adj_zmarch" in name and groups == 32 * 256 // 4, (name, groups)
 
 
 @pytest.mark.parametrize("form,dtype,row", [("adjoint", torch.float64, 36), ("adjoint", torch.float32, 36),
