@@ -938,8 +938,8 @@ static bool vec_ok(const StepArgs &a)
 // and 512^3; 16-byte loads over 512-point rows, or four rows per thread,
 // 6-19% slower at 512^3: more registers, fewer waves).
 // These shapes and work-group mappings measured fastest on MI355X at 512^3.
-// Rows shorter than a vector (FP32 and FP16) and FP32 rows of at most 64 points
-// take one point per lane; regions below
+// Rows shorter than a vector (FP32 and FP16) and rows of at most 64 points in FP32
+// and in FP16 with stochastic rounding take one point per lane; regions below
 // zmarch_min_points() take the box kernel.
 // One inner-region launch, with the slab waves of yz (nyz boxes) run by
 // the launch's first work-groups when nyz > 0.
@@ -1019,6 +1019,11 @@ int launch_step_inner(int dtype, const StepArgs &a, const Box &b, hipStream_t s,
         }
         return run_inner<float, 1, 64, 8, 2>(a, b, s, kInner, yz, nyz, pk);
     }
+    // (stochastic stores in rows of at most 64 points: one per lane, 50 x 376 x 438
+    // 41.5 -> 38.4 us, 64 x 400 x 450 43.7 -> 40.8, 30 x 800 x 600 95.7 -> 93.2;
+    // rounded to nearest 28.8 -> 31.8, 30.6 -> 34.5 and 63.4 -> 76.0)
+    if (a.stochastic && rows_dispatched() && b.i1 - b.i0 <= 64)
+        return run_inner<_Float16, 1, 64, 8, 2>(a, b, s, kInnerF16, yz, nyz, pk);
     if (row_ok<_Float16, 4>(a) && narrow_pays<_Float16, 4>(b))
         return run_inner<_Float16, 4, 32, 8, 2>(a, b, s, kInnerF16, yz, nyz, pk);
     if (row_ok<_Float16, 4>(a)) return run_inner<_Float16, 4, 64, 4, 2>(a, b, s, kInnerF16, yz, nyz, pk);

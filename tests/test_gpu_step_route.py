@@ -86,3 +86,23 @@ def test_flat_grids(dtype, n, periods, monkeypatch):
 def test_slabs_only_where_a_period_needs_them(dtype, n, overlaps, periods, monkeypatch):
     say("slabs", dtype, n, overlaps, periods)
     _same_as_general(n, periods, overlaps, dtype, 0, monkeypatch, "k_step_")
+
+
+# FP16 rows of at most 64 points, whose stochastic stores take one point per
+# lane, and one more, against 4-point vectors (every region marched)
+@pytest.mark.parametrize("periods", [(1, 1, 1), (0, 1, 0), (1, 0, 1)])
+@pytest.mark.parametrize("nx", [34, 50, 65, 66, 67])
+def test_short_rows_with_stochastic_stores(nx, periods):
+    n = (nx, 400, 380)
+    say("short rows, stochastic", n, periods)
+    out = []
+    for zmin in (None, 0):
+        with grid(n, periods, zmarch_min=zmin):
+            T2, T, Ci, c = _fields(n, "f16")
+            for mode, one in (("stochastic", nx <= 66 and zmin is None), ("nearest", False)):
+                rnd = igg.rounding(mode, 3, 5)
+                igg.diffusion_step(T2, T, Ci, *c, rnd=rnd)
+                out.append(T2.clone())
+                name = kernels(lambda: igg.diffusion_step(T2, T, Ci, *c, rnd=rnd))[0]
+                assert "k_step_zmarchIDF16_Li%dE" % (1 if one else 4) in name, name
+    assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
