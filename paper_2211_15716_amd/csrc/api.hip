@@ -176,6 +176,7 @@ int ensure_device()
     // at every record, tens of microseconds per step at 512^3)
     IGG_HIP(hipEventCreateWithFlags(&g.ev_fork, hipEventDisableTiming | hipEventDisableSystemFence));
     IGG_HIP(hipEventCreateWithFlags(&g.ev_join, hipEventDisableTiming | hipEventDisableSystemFence));
+    IGG_HIP(hipEventCreateWithFlags(&g.ev_run, hipEventDisableTiming | hipEventDisableSystemFence));
     // Send and receive planes of one field each (one plane of the largest
     // field, n+1 per dimension in FP64, rounded to 256 B).  One rank fills its
     // halo from its own points and needs them only where the slabs pack (512^3:
@@ -197,6 +198,19 @@ int ensure_device()
     return IGG_OK;
 }
 
+// Destroys the time loop's kept graph, after the last of its replays: nothing
+// says that a graph may be destroyed while it runs.
+static int drop_run_graph()
+{
+    Grid &g = grid();
+    if (!g.run_exec) return IGG_OK;
+    IGG_HIP(hipEventSynchronize(g.ev_run));
+    const hipGraphExec_t exec = g.run_exec;
+    g.run_exec = nullptr;
+    IGG_HIP(hipGraphExecDestroy(exec));
+    return IGG_OK;
+}
+
 static int release_device()
 {
     Grid &g = grid();
@@ -206,21 +220,22 @@ static int release_device()
         if (e != hipSuccess && rc == IGG_OK) rc = hip_fail(e, w);
     };
     chk(hipStreamSynchronize(g.side), "hipStreamSynchronize(side)");
+    const int rc_graph = drop_run_graph();
     chk(hipFree(g.halo_buf), "hipFree(halo_buf)");
     for (double *p : g.red_free) chk(hipHostFree(p), "hipHostFree(red_free)");
     g.red_free.clear();
     chk(hipEventDestroy(g.ev_fork), "hipEventDestroy");
     chk(hipEventDestroy(g.ev_join), "hipEventDestroy");
+    chk(hipEventDestroy(g.ev_run), "hipEventDestroy");
     for (hipEvent_t e : g.tev) chk(hipEventDestroy(e), "hipEventDestroy(timing)");
     chk(hipStreamDestroy(g.side), "hipStreamDestroy(side)");
-    if (g.run_exec) chk(hipGraphExecDestroy(g.run_exec), "hipGraphExecDestroy");
     if (g.cap) chk(hipStreamDestroy(g.cap), "hipStreamDestroy(cap)");
     g.run_exec = nullptr;
     g.cap = nullptr;
     g.run_key.clear();
     g.tev.clear();
     g.dev_ready = false;
-    return rc;
+    return rc ? rc : rc_graph;
 }
 
 // events made when timing is switched on: 1024 timed launches
@@ -1222,8 +1237,7 @@ int diffusion_run(const igg_field *T, const igg_field *T2, const igg_field *Ci, 
         // a second time in a row: the capture takes the host longer than the
         // launches it saves in one call (96 x 80 x 64, 50 steps: 226 us with a
         // capture per call, 180 without)
-        if (g.run_exec) IGG_HIP(hipGraphExecDestroy(g.run_exec));
-        g.run_exec = nullptr;
+        if ((rc = drop_run_graph())) return rc;
         g.run_key = key;
         return direct();
     }
@@ -1260,6 +1274,7 @@ int diffusion_run(const igg_field *T, const igg_field *T2, const igg_field *Ci, 
         IGG_HIP(hipGraphLaunch(g.run_exec, s));
         it += nrec * (npair ? 2 : 1);
     }
+    IGG_HIP(hipEventRecord(g.ev_run, s));
     for (int p = replays * nrec; p < npair; ++p)
         if ((rc = pair(s))) return rc;
     while (it < nt)

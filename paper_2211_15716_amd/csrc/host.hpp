@@ -83,6 +83,7 @@ struct Grid {
     hipStream_t side = nullptr;       // helper stream: boundary slabs + halo chain
     hipEvent_t ev_fork = nullptr;     // caller stream -> helper stream
     hipEvent_t ev_join = nullptr;     // helper stream -> caller stream
+    hipEvent_t ev_run = nullptr;      // after the last replay of run_exec
 
     int nranks = 1;                     // virtual ranks held by this process (product of dims)
     unsigned char *halo_buf = nullptr;  // send and receive planes of every rank

@@ -292,8 +292,8 @@ def diffusion_flux_step_adjoint_ranks(lam_ns, lam_np1s, T_ns, Cis, gCis, lam, dt
 
 def diffusion_run(T, T2, Ci, lam, dt, dx, dy, dz, nt, split=(16, 2, 2), rnd=None, graph=True, stream=None):
     """nt steps of the Fig. 1 time loop on the buffers T and T2 (swapped each
-    step); with graph=True the library replays a captured HIP graph of two
-    steps.  Returns the tensor holding the final state (T or T2)."""
+    step); with graph=True the library replays a captured HIP graph from the
+    second call in a row with the same arguments on.  Returns the tensor holding the final state (T or T2)."""
     fb = ctypes.c_int(0)
     r = ctypes.byref(rnd) if rnd is not None else None
     f, f2, fc = field(T), field(T2), field(Ci)

@@ -125,3 +125,26 @@ def test_held_back_stream_in_the_kept_graph(where, pack, monkeypatch):
         say("held back", where, "pack", pack, "schedule", sched)
         with grid(n, zmarch_min=None):
             _calls(T0, Ci, c, nt, split, want, before)
+
+
+def test_other_arguments_wait_for_the_replays(monkeypatch):
+    """A call with other arguments drops the kept graph: only when its last
+    replay, still in flight when the call is made, has ended.  (Single steps,
+    all of them in graphs of 16.)"""
+    monkeypatch.setenv("IGG_SCHEDULE", "2")
+    n, nt = (128, 128, 128), 400
+    with grid(n, zmarch_min=None):
+        T0, Ci, c = _problem(n)
+        want, _ = _steps(T0, Ci, c, 3 * nt)
+        T, T2 = T0.clone(), T0.clone()
+        other = T0.clone(), T0.clone()
+        for _ in range(3):  # directly, captured, replayed
+            out = igg.diffusion_run(T, T2, Ci, *c, nt, graph=True)
+        replayed = torch.cuda.Event()
+        replayed.record()
+        say("other arguments after", nt, "steps")
+        igg.diffusion_run(*other, Ci, *c, nt, graph=True)
+        assert replayed.query()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        assert torch.equal(other[0], _steps(T0, Ci, c, nt)[0])
