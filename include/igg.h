@@ -268,10 +268,11 @@ int diffusion_step_ranks(const igg_field *T2, const igg_field *T, const igg_fiel
  *          loop are captured once into a HIP graph on a library stream and
  *          replayed on `stream`; the steps left over, and a first call, run
  *          directly.  The graph is kept for later calls with identical
- *          arguments (and pair count) and dropped when any differs: such a call
- *          waits for the last replay of the old graph.  For grids
- *          small enough that launch latency dominates.  On a stream that is
- *          being captured the steps run (and are captured) directly.
+ *          arguments (and pair count) and put aside when any differs (graphs
+ *          put aside are destroyed with the grid, or 16 at a time, when the
+ *          call waits for the device).  For grids small enough that launch
+ *          latency dominates.  On a stream that is being captured the steps
+ *          run (and are captured) directly.
  *          Stochastic rounding needs a new counter every step, so it refuses
  *          use_graph = 1.
  * Results are bit-identical for both values of use_graph.

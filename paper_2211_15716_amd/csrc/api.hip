@@ -176,7 +176,6 @@ int ensure_device()
     // at every record, tens of microseconds per step at 512^3)
     IGG_HIP(hipEventCreateWithFlags(&g.ev_fork, hipEventDisableTiming | hipEventDisableSystemFence));
     IGG_HIP(hipEventCreateWithFlags(&g.ev_join, hipEventDisableTiming | hipEventDisableSystemFence));
-    IGG_HIP(hipEventCreateWithFlags(&g.ev_run, hipEventDisableTiming | hipEventDisableSystemFence));
     // Send and receive planes of one field each (one plane of the largest
     // field, n+1 per dimension in FP64, rounded to 256 B).  One rank fills its
     // halo from its own points and needs them only where the slabs pack (512^3:
@@ -198,17 +197,26 @@ int ensure_device()
     return IGG_OK;
 }
 
-// Destroys the time loop's kept graph, after the last of its replays: nothing
-// says that a graph may be destroyed while it runs.
-static int drop_run_graph()
+// Puts the time loop's kept graph aside: nothing says that a graph may be
+// destroyed while it runs, and its replays may be queued still.  Those put aside
+// are destroyed together when there are 16 (or all of them, with the grid),
+// after the device's work.  (An event behind every call's replays to wait for
+// instead: 50 -> 53 us for a loop of 48 x 176 x 45 in one replay.)
+static int retire_run_graph(bool all)
 {
     Grid &g = grid();
-    if (!g.run_exec) return IGG_OK;
-    IGG_HIP(hipEventSynchronize(g.ev_run));
-    const hipGraphExec_t exec = g.run_exec;
+    if (g.run_exec) g.run_old.push_back(g.run_exec);
     g.run_exec = nullptr;
-    IGG_HIP(hipGraphExecDestroy(exec));
-    return IGG_OK;
+    if (g.run_old.empty() || (!all && g.run_old.size() < 16)) return IGG_OK;
+    IGG_HIP(hipDeviceSynchronize());
+    std::vector<hipGraphExec_t> old;
+    old.swap(g.run_old);
+    int rc = IGG_OK;
+    for (hipGraphExec_t e : old) {
+        const hipError_t h = hipGraphExecDestroy(e);
+        if (h != hipSuccess && rc == IGG_OK) rc = hip_fail(h, "hipGraphExecDestroy");
+    }
+    return rc;
 }
 
 static int release_device()
@@ -220,17 +228,15 @@ static int release_device()
         if (e != hipSuccess && rc == IGG_OK) rc = hip_fail(e, w);
     };
     chk(hipStreamSynchronize(g.side), "hipStreamSynchronize(side)");
-    const int rc_graph = drop_run_graph();
+    const int rc_graph = retire_run_graph(true);
     chk(hipFree(g.halo_buf), "hipFree(halo_buf)");
     for (double *p : g.red_free) chk(hipHostFree(p), "hipHostFree(red_free)");
     g.red_free.clear();
     chk(hipEventDestroy(g.ev_fork), "hipEventDestroy");
     chk(hipEventDestroy(g.ev_join), "hipEventDestroy");
-    chk(hipEventDestroy(g.ev_run), "hipEventDestroy");
     for (hipEvent_t e : g.tev) chk(hipEventDestroy(e), "hipEventDestroy(timing)");
     chk(hipStreamDestroy(g.side), "hipStreamDestroy(side)");
     if (g.cap) chk(hipStreamDestroy(g.cap), "hipStreamDestroy(cap)");
-    g.run_exec = nullptr;
     g.cap = nullptr;
     g.run_key.clear();
     g.tev.clear();
@@ -1237,7 +1243,7 @@ int diffusion_run(const igg_field *T, const igg_field *T2, const igg_field *Ci, 
         // a second time in a row: the capture takes the host longer than the
         // launches it saves in one call (96 x 80 x 64, 50 steps: 226 us with a
         // capture per call, 180 without)
-        if ((rc = drop_run_graph())) return rc;
+        if ((rc = retire_run_graph(false))) return rc;
         g.run_key = key;
         return direct();
     }
@@ -1274,7 +1280,6 @@ int diffusion_run(const igg_field *T, const igg_field *T2, const igg_field *Ci, 
         IGG_HIP(hipGraphLaunch(g.run_exec, s));
         it += nrec * (npair ? 2 : 1);
     }
-    IGG_HIP(hipEventRecord(g.ev_run, s));
     for (int p = replays * nrec; p < npair; ++p)
         if ((rc = pair(s))) return rc;
     while (it < nt)

@@ -83,7 +83,6 @@ struct Grid {
     hipStream_t side = nullptr;       // helper stream: boundary slabs + halo chain
     hipEvent_t ev_fork = nullptr;     // caller stream -> helper stream
     hipEvent_t ev_join = nullptr;     // helper stream -> caller stream
-    hipEvent_t ev_run = nullptr;      // after the last replay of run_exec
 
     int nranks = 1;                     // virtual ranks held by this process (product of dims)
     unsigned char *halo_buf = nullptr;  // send and receive planes of every rank
@@ -103,6 +102,7 @@ struct Grid {
     // stream, kept while every argument the kernels take stays the same
     hipStream_t cap = nullptr;
     hipGraphExec_t run_exec = nullptr;
+    std::vector<hipGraphExec_t> run_old;  // kept before, not destroyed yet (retire_run_graph)
     std::vector<unsigned char> run_key;
 
     bool timing = false;
